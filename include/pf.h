@@ -164,7 +164,7 @@ int pf_symbolic_set_mapping(pf_symbolic sym, const int32_t* lanes_per_level);
 /* Launch shape of the level-scheduled kernels: threads per workgroup (64,
  * 128, 256 or 512; 0 = by batch size: 512 up to 512 cases, else 256) and the LDS
  * budget in bytes of the tail, the largest run of top levels whose values
- * (64 bytes per filled slot, 48 per node) are factorised and solved in LDS
+ * (64 bytes per filled slot, 56 per node) are factorised and solved in LDS
  * (0 = none, at most 161792 so that 2 KB of LDS stay for reductions;
  * default 65536).  The Newton kernel's LDS copy of every bus's (e, f)
  * (16 n bytes) is used only when it fits this budget too, so a budget of

@@ -53,7 +53,7 @@ size_t HostSym::dev_bytes() const
                                           &ydiag,     &Rp,        &Ri,      &Rs,     &level_ptr,
                                           &level_nodes, &level_g, &node_info, &slot_info, &rl,
                                           &upd,       &t_node,    &t_slot,  &t_rl,   &t_upd,
-                                          &t_lptr,    &t_pk,      &from,    &to,     &sub_idx,
+                                          &t_lev,     &t_op,      &from,    &to,     &sub_idx,
                                           &sub_ptr,   &sub_cum};
     size_t total = 0;
     for (auto* a : arrs) total += align256(std::max<size_t>(a->size(), 1) * sizeof(int32_t));
@@ -359,8 +359,8 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
 // The LDS tail: the largest run of top levels whose values, with the
 // Newton kernel's PV bitmask, fit the budget.
 // Its top may be a clique chain: single-node levels where every node is
-// adjacent to all nodes above it in the filled graph.  That part is
-// factorised and solved densely (right-looking, one barrier per pivot).
+// adjacent to all nodes above it in the filled graph.  That part is solved
+// densely (column by column on one wavefront).
 void build_tail(HostSym& s, int64_t budget)
 {
     const int nlev = (int)s.level_ptr.size() - 1;
@@ -376,7 +376,9 @@ void build_tail(HostSym& s, int64_t budget)
                 ++k2;
                 t2 += s.Lp[j + 1] - s.Lp[j];
             }
-            if (tail_bytes(k2, t2) + pv_mask_bytes(s.n) > budget || t2 > 65535) break;
+            if (tail_bytes(k2, t2) + pv_mask_bytes(s.n) > budget || t2 > kTailIndexMax ||
+                k2 > kTailIndexMax)
+                break;
             K = k2;
             TS = t2;
             L = l;
@@ -391,8 +393,8 @@ void build_tail(HostSym& s, int64_t budget)
     s.t_slot.clear();
     s.t_rl.clear();
     s.t_upd.clear();
-    s.t_pk.clear();
-    s.t_lptr.assign(1, 0);
+    s.t_lev.clear();
+    s.t_op.clear();
     build_subtrees(s);
     if (K == 0) return;
 
@@ -423,7 +425,6 @@ void build_tail(HostSym& s, int64_t budget)
             loc[s.level_nodes[x]] = (int32_t)tnodes.size();
             tnodes.push_back(s.level_nodes[x]);
         }
-        s.t_lptr.push_back((int32_t)tnodes.size());
     }
     const int32_t kfirst = (int32_t)K - s.tail_clique;  // first local node of the clique
     auto in_clique = [&](int p) { return loc[p] >= kfirst; };
@@ -474,39 +475,106 @@ void build_tail(HostSym& s, int64_t budget)
                     s.t_upd.push_back(s.Ub[u]);
                 }
             t[6] = (int32_t)(s.t_upd.size() / 2);
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int u = s.Up[q]; u < s.Up[q + 1]; ++u) {
-                    const int i = owner[s.Ub[u]];
-                    if (loc[i] >= 0 && in_clique(i) == (pass == 1)) {
-                        s.t_upd.push_back(sloc[s.Ua[u]]);
-                        s.t_upd.push_back(sloc[s.Ub[u]]);
-                    }
-                }
-                if (pass == 0) t[10] = (int32_t)(s.t_upd.size() / 2);
-            }
-            t[7] = (int32_t)(s.t_upd.size() / 2);
             t[8] = s.perm[j];
             t[9] = (int32_t)jl;
         }
     }
-    // packed copies of the local lists (local indices are below 2^16: the
-    // tail's slots fit in LDS)
-    auto pack = [&](const std::vector<int32_t>& src, int32_t b, int32_t e) {
-        const int32_t start = (int32_t)(s.t_pk.size() / 4);
-        for (int32_t u = b; u < e; ++u)
-            s.t_pk.push_back((int32_t)((uint32_t)src[2 * (size_t)u] |
-                                       ((uint32_t)src[2 * (size_t)u + 1] << 16)));
-        while (s.t_pk.size() % 4) s.t_pk.push_back(0);
-        return start;
+    build_tail_ops(s);
+}
+
+// The tail's operations by level (layouts documented with DevSym).
+void build_tail_ops(HostSym& s)
+{
+    const int nT = (int)s.level_ptr.size() - 1 - s.tail_level;
+    const int K = s.tail_nodes, TS = s.tail_slots, kf = K - s.tail_clique;
+    const int x0 = s.level_ptr[s.tail_level];
+    auto slot0 = [&](int jl) { return s.t_node[12 * (size_t)jl + 3]; };
+    auto slot1 = [&](int jl) { return s.t_node[12 * (size_t)jl + 4]; };
+    auto high = [&](int t) { return s.t_slot[12 * (size_t)t + 1]; };
+    std::vector<int32_t> own(TS);
+    for (int jl = 0; jl < K; ++jl)
+        for (int t = slot0(jl); t < slot1(jl); ++t) own[t] = jl;
+    s.t_lev.assign(8 * (size_t)nT, 0);
+    struct Term {
+        int32_t d, a, b, j;  // d: a slot, or TS + a node (its diagonal)
     };
-    for (int64_t jl = 0; jl < K; ++jl) {
-        int32_t* r = &s.t_node[12 * (size_t)jl];
-        r[9] = pack(s.t_rl, r[6], r[7]);
+    std::vector<Term> terms;
+    std::vector<int32_t> dst, count((size_t)TS + K, 0), at((size_t)TS + K, 0);
+    auto put = [&](size_t i, uint32_t d, uint32_t a, uint32_t b, uint32_t j, uint32_t next) {
+        s.t_op[2 * i] = (int32_t)(d | a << 12 | (b & 255u) << 24);
+        s.t_op[2 * i + 1] = (int32_t)(b >> 8 | j << 4 | next << 16);
+    };
+    for (int tl = 0; tl < nT; ++tl) {
+        const int j0 = s.level_ptr[s.tail_level + tl] - x0;
+        const int j1 = s.level_ptr[s.tail_level + tl + 1] - x0;
+        terms.clear();
+        dst.clear();
+        auto term = [&](int32_t d, int32_t a, int32_t b, int32_t j) {
+            if (count[d]++ == 0) dst.push_back(d);
+            terms.push_back({d, a, b, j});
+        };
+        for (int jl = j0; jl < j1; ++jl)
+            for (int b = slot0(jl); b < slot1(jl); ++b) {
+                const int k = high(b);
+                term(TS + k, b, b, jl);
+                int d = slot0(k);
+                for (int a = b + 1; a < slot1(jl); ++a) {
+                    while (high(d) != high(a)) ++d;  // present: the filled pattern is closed
+                    term(d, a, b, jl);
+                }
+            }
+        // slots before diagonals, destinations with more terms first; the
+        // first terms of all destinations, then each one's further terms
+        std::sort(dst.begin(), dst.end(), [&](int32_t u, int32_t v) {
+            if ((u < TS) != (v < TS)) return u < TS;
+            if (count[u] != count[v]) return count[u] > count[v];
+            return u < v;
+        });
+        const int32_t op0 = (int32_t)(s.t_op.size() / 2);
+        s.t_op.resize(s.t_op.size() + 2 * terms.size());
+        int32_t ns = 0, more = op0 + (int32_t)dst.size();
+        for (size_t i = 0; i < dst.size(); ++i) {
+            const int32_t d = dst[i];
+            ns += d < TS;
+            at[d] = op0 + (int32_t)i;  // where its next term goes
+        }
+        // offsets from a destination's first term to its second
+        std::vector<int32_t> second(dst.size());
+        for (size_t i = 0; i < dst.size(); ++i) {
+            second[i] = more;
+            more += count[dst[i]] - 1;
+        }
+        for (const Term& q : terms) {
+            const int32_t p = at[q.d];
+            const bool first = p < op0 + (int32_t)dst.size();
+            const bool last = --count[q.d] == 0;
+            const int32_t nx = first ? second[p - op0] : p + 1;
+            put(p, q.d < TS ? q.d : q.d - TS, q.a, q.b, q.j, last ? 0 : nx - p);
+            at[q.d] = nx;
+        }
+        int32_t* r = &s.t_lev[8 * (size_t)tl];
+        r[0] = op0;
+        r[1] = ns;
+        r[2] = (int32_t)dst.size();
     }
-    for (int64_t t = 0; t < TS; ++t) {
-        int32_t* u = &s.t_slot[12 * (size_t)t];
-        u[11] = pack(s.t_upd, u[6], u[7]);
+    // backward: the slots whose higher neighbour is on the level and below
+    // the clique, by that neighbour; S(j) lies on one path to the root, so a
+    // node has at most one slot into a level
+    std::vector<int32_t> ptr(K + 1, 0);
+    for (int t = 0; t < TS; ++t) ++ptr[high(t) + 1];
+    for (int k = 0; k < K; ++k) ptr[k + 1] += ptr[k];
+    const size_t op0 = s.t_op.size() / 2;
+    s.t_op.resize(s.t_op.size() + 2 * ((size_t)ptr[kf] + 1));
+    for (int tl = 0; tl < nT; ++tl) {
+        const int j0 = std::min(kf, s.level_ptr[s.tail_level + tl] - x0);
+        const int j1 = std::min(kf, s.level_ptr[s.tail_level + tl + 1] - x0);
+        s.t_lev[8 * (size_t)tl + 4] = (int32_t)op0 + ptr[j0];
+        s.t_lev[8 * (size_t)tl + 5] = ptr[j1] - ptr[j0];
     }
+    for (int t = 0; t < TS; ++t)
+        if (high(t) < kf) put(op0 + ptr[high(t)]++, own[t], t, high(t), 0, 0);
+    // stands in for the first operation of an empty level
+    put(s.t_op.size() / 2 - 1, 0, 0, 0, 0, 0);
 }
 
 void build_subtrees(HostSym& s)

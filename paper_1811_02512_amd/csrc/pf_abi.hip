@@ -306,8 +306,8 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     d.t_slot = reinterpret_cast<const int4*>(put(h.t_slot));
     d.t_rl = reinterpret_cast<const int2*>(put(h.t_rl));
     d.t_upd = reinterpret_cast<const int2*>(put(h.t_upd));
-    d.t_lptr = put(h.t_lptr);
-    d.t_pk = reinterpret_cast<const uint4*>(put(h.t_pk));
+    d.t_lev = reinterpret_cast<const int4*>(put(h.t_lev));
+    d.t_op = reinterpret_cast<const uint2*>(put(h.t_op));
     d.sub_cut = h.sub_cut;
     d.sub_roots = h.sub_roots;
     d.sub_idx = put(h.sub_idx);

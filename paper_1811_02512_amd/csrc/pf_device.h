@@ -70,6 +70,14 @@ constexpr int kNoPivot = 0x7fffffff;
 
 __device__ __forceinline__ void mark_pivot(int* s_bad, int x) { atomicMin(s_bad, x); }
 
+// The workgroup's size in a scalar register: blockDim.x is a load from the
+// dispatch's argument block, which the compiler repeats inside loops (and
+// waits for, with everything else in flight) rather than keeping its result.
+__device__ __forceinline__ int wg_size()
+{
+    return __builtin_amdgcn_readfirstlane((int)blockDim.x);
+}
+
 // Orders the LDS accesses of one wavefront's lanes (they run in lockstep,
 // and a wavefront's LDS operations are performed in issue order).
 __device__ __forceinline__ void wave_sync()
@@ -619,15 +627,16 @@ template <class P, class F>
 __device__ __forceinline__ void for_nodes(const P& par, const DevSym& S, int l0, int l1, bool up,
                                           F&& fn)
 {
+    const int T = wg_size();
     for (int li = l0; li < l1; ++li) {
         const int l = up ? li : l1 - 1 - (li - l0);
-        const int g = S.level_g[l];
+        const int g = S.level_g[l];  // a power of two
+        const int lg = ilog2(g);
         const int beg = S.level_ptr[l];
         const int cnt = S.level_ptr[l + 1] - beg;
-        const int gpb = blockDim.x / g;
-        const int step = gpb * par.size();
+        const int step = (T >> lg) * par.size();
         const int lane = threadIdx.x & (g - 1);
-        int idx = (int)(threadIdx.x / g) * par.size() + par.rank();
+        int idx = (int)(threadIdx.x >> lg) * par.size() + par.rank();
         NodeRec cur = idx < cnt ? load_rec(S, beg + idx) : NodeRec{};
         while (idx < cnt) {
             const int nxt = idx + step;
@@ -655,14 +664,16 @@ __device__ __forceinline__ void for_sub_levels(const DevSym& S, int k0, int k1, 
                                                bool up, F&& fn)
 {
     const int R1 = S.sub_roots + 1;
+    const int T = wg_size();
     for (int li = l0; li < l1; ++li) {
         const int l = up ? li : l1 - 1 - (li - l0);
         const int g = S.level_g[l];
         const int b = S.level_ptr[l];
         const int e1 = b + S.sub_ptr[l * R1 + k1];
-        const int gpb = blockDim.x / g;
+        const int lg = ilog2(g);
+        const int gpb = T >> lg;
         const int lane = threadIdx.x & (g - 1);
-        int e = b + S.sub_ptr[l * R1 + k0] + (int)threadIdx.x / g;
+        int e = b + S.sub_ptr[l * R1 + k0] + (int)(threadIdx.x >> lg);
         int x = e < e1 ? S.sub_idx[e] : 0;
         NodeRec cur = e < e1 ? load_rec(S, x) : NodeRec{};
         while (e < e1) {
@@ -705,63 +716,6 @@ __device__ __forceinline__ void sub_share(const DevSym& S, const P& par, int& k0
     k0 = s_k[0];
     k1 = s_k[1];
     __syncthreads();
-}
-
-// Runs fn(jl, lane, g) over tail levels [t0, t1) (tail-local numbering).
-template <class F>
-__device__ __forceinline__ void for_tail_range(const DevSym& S, int t0, int t1, bool up, F&& fn)
-{
-    for (int ti = t0; ti < t1; ++ti) {
-        const int tl = up ? ti : t1 - 1 - (ti - t0);
-        const int g = S.level_g[S.tail_level + tl];
-        const int beg = S.t_lptr[tl];
-        const int cnt = S.t_lptr[tl + 1] - beg;
-        const int gpb = blockDim.x / g;
-        const int grp = threadIdx.x / g;
-        const int lane = threadIdx.x & (g - 1);
-        for (int base = 0; base < cnt; base += gpb) {
-            const int idx = base + grp;
-            if (idx < cnt) fn(beg + idx, lane, g);
-        }
-        __syncthreads();
-    }
-}
-
-// As for_tail_range, passing fn(jl, the three parts of t_node[jl], lane, g);
-// each thread's first record of the next level is requested before the
-// barrier that ends the current one, so it is in registers when that level
-// starts.
-template <class F>
-__device__ __forceinline__ void for_tail_pf(const DevSym& S, int t0, int t1, bool up, F&& fn)
-{
-    if (t0 >= t1) return;
-    int g = 1, beg = 0, cnt = 0;
-    int4 ra = make_int4(0, 0, 0, 0), rb = ra, rc = ra;
-    auto fetch = [&](int tl) {
-        g = S.level_g[S.tail_level + tl];
-        beg = S.t_lptr[tl];
-        cnt = S.t_lptr[tl + 1] - beg;
-        const int idx = threadIdx.x / g;
-        const int jl = beg + (idx < cnt ? idx : 0);
-        ra = S.t_node[3 * jl];
-        rb = S.t_node[3 * jl + 1];
-        rc = S.t_node[3 * jl + 2];
-    };
-    fetch(up ? t0 : t1 - 1);
-    for (int ti = t0; ti < t1; ++ti) {
-        const int gg = g, b0 = beg, c0 = cnt;
-        const int4 a0 = ra, a1 = rb, a2 = rc;
-        if (ti + 1 < t1) fetch(up ? ti + 1 : t1 - 2 - (ti - t0));
-        const int gpb = blockDim.x / gg, grp = threadIdx.x / gg, lane = threadIdx.x & (gg - 1);
-        for (int base = 0; base < c0; base += gpb) {
-            const int idx = base + grp;
-            if (idx >= c0) continue;
-            const int jl = b0 + idx;
-            if (base == 0) fn(jl, a0, a1, a2, lane, gg);
-            else fn(jl, S.t_node[3 * jl], S.t_node[3 * jl + 1], S.t_node[3 * jl + 2], lane, gg);
-        }
-        __syncthreads();
-    }
 }
 
 // Block updates of one destination slot from pairs (a, b) = (slot(i;k), slot(i;j)):
@@ -859,71 +813,122 @@ __device__ __forceinline__ void apply_updates2(const int2* __restrict__ upd, int
     }
 }
 
-// Word k of a 16-byte load of a packed list.
-__device__ __forceinline__ uint32_t pk_word(const uint4& q, int k)
+// An operation of the tail (t_op, see DevSym).
+struct TailOp {
+    int d, a, b, j, next;
+};
+__device__ __forceinline__ TailOp tail_op(const uint2& q)
 {
-    return k == 0 ? q.x : k == 1 ? q.y : k == 2 ? q.z : q.w;
+    return {(int)(q.x & 0xfff), (int)(q.x >> 12 & 0xfff), (int)(q.x >> 24 | (q.y & 0xf) << 8),
+            (int)(q.y >> 4 & 0xfff), (int)(q.y >> 16)};
 }
 
-// Updates of one tail destination from its packed local pair list (np
-// pairs starting at load l, the first two loads q0, q1 already requested):
-// eight pairs per step, the next two loads in flight; updates in list order.
-__device__ __forceinline__ void apply_packed_lds(const uint4* __restrict__ pk, int l, int np,
-                                                 uint4 q0, uint4 q1, const double* sLU, Blk& Wk,
-                                                 Blk& Vk)
+// Runs fn(op, index, slot) for the operations of the tail levels [0, nt), one
+// thread per operation, with a workgroup barrier after every level: PART 0
+// the right-looking updates, upward (slot: the destination is a slot), PART 1
+// the backward operations, downward, PART 2 the updates of diagonals only,
+// upward.  A level takes well under a microsecond, less than a load that
+// misses L1, so each lane of a wavefront holds the table entry of one of 64
+// levels (read back by lane index), and a thread's first operation of each
+// of the next kAhead levels is in flight, in registers of its own (moving
+// one to another register would wait for it) and requested in any case (the
+// first of the level stands in for an absent one, so that the number of
+// requests in flight is known and the oldest can be waited for alone).
+template <int PART, class F>
+__device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
 {
-    for (int k = 0; k < np; k += 8) {
-        const int i = l + (k >> 2);
-        uint4 n0 = make_uint4(0, 0, 0, 0), n1 = n0;
-        if (k + 8 < np) n0 = pk[i + 2];
-        if (k + 12 < np) n1 = pk[i + 3];
+    constexpr int kAhead = 4;
+    const int T = wg_size();
+    for (int i0 = 0; i0 < nt; i0 += kWave) {
+        const int m = nt - i0 < kWave ? nt - i0 : kWave;
+        int h0, hs, hn;
+        {
+            const int l = threadIdx.x & (kWave - 1);
+            const int i = i0 + (l < m ? l : m - 1);
+            const int4 h = S.t_lev[PART == 1 ? 2 * (nt - 1 - i) + 1 : 2 * i];
+            h0 = PART == 2 ? h.x + h.y : h.x;
+            hs = PART == 0 ? h.y : 0;
+            hn = PART == 0 ? h.z : PART == 1 ? h.y : h.z - h.y;
+        }
+        auto first = [&](int i) {
+            const int l = i < m ? i : m - 1;
+            const int n = __builtin_amdgcn_readlane(hn, l);
+            return S.t_op[__builtin_amdgcn_readlane(h0, l) +
+                          ((int)threadIdx.x < n ? (int)threadIdx.x : 0)];
+        };
+        uint2 q[kAhead];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            if (k + c < np) {
-                const uint32_t v = pk_word(c < 4 ? q0 : q1, c & 3);
-                const int a = v & 0xffff, b = v >> 16;
-                bmsub(Wk, bload(sLU + 8 * a), bload(sLU + 8 * b + 4));
-                bmsub(Vk, bload(sLU + 8 * b), bload(sLU + 8 * a + 4));
+        for (int k = 0; k < kAhead; ++k) q[k] = first(k);
+        for (int i = 0; i < m; i += kAhead) {
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                if (i + k >= m) break;
+                const int op0 = __builtin_amdgcn_readlane(h0, i + k);
+                const int ns = __builtin_amdgcn_readlane(hs, i + k);
+                const int n = __builtin_amdgcn_readlane(hn, i + k);
+                if ((int)threadIdx.x < n) fn(q[k], op0 + (int)threadIdx.x, (int)threadIdx.x < ns);
+                for (int t = threadIdx.x + T; t < n; t += T)
+                    fn(S.t_op[op0 + t], op0 + t, t < ns);
+                q[k] = first(i + k + kAhead);
+                __syncthreads();
             }
         }
-        q0 = n0;
-        q1 = n1;
     }
 }
 
-// Updates of two tail destinations from their packed local pair lists
-// (n1, n2 pairs starting at loads l1, l2; words (slot(i;k), slot(i;j))):
-// four pairs of each per step, the next step's loads in flight.  The order
-// of the updates of each destination is the list order.
-__device__ __forceinline__ void apply_packed2_lds(const uint4* __restrict__ pk, int l1, int n1,
-                                                  int l2, int n2, const double* sLU, Blk& Wk,
-                                                  Blk& Vk, Blk& Wk2, Blk& Vk2)
-{
-    uint4 q1 = pk[n1 > 0 ? l1 : 0], q2 = pk[n2 > 0 ? l2 : 0];
-    for (int k = 0; k < n1 || k < n2; k += 4) {
-        const int i = (k >> 2) + 1;
-        const uint4 q1n = pk[k + 4 < n1 ? l1 + i : 0];
-        const uint4 q2n = pk[k + 4 < n2 ? l2 + i : 0];
-        // one pair of each destination in flight at a time (register budget)
-#pragma unroll 1
-        for (int c = 0; c < 4; ++c) {
-            if (k + c < n1) {
-                const uint32_t v = pk_word(q1, c);
-                const int a = v & 0xffff, b = v >> 16;
-                bmsub(Wk, bload(sLU + 8 * a), bload(sLU + 8 * b + 4));
-                bmsub(Vk, bload(sLU + 8 * b), bload(sLU + 8 * a + 4));
-            }
-            if (k + c < n2) {
-                const uint32_t v = pk_word(q2, c);
-                const int a = v & 0xffff, b = v >> 16;
-                bmsub(Wk2, bload(sLU + 8 * a), bload(sLU + 8 * b + 4));
-                bmsub(Vk2, bload(sLU + 8 * b), bload(sLU + 8 * a + 4));
-            }
-        }
-        q1 = q1n;
-        q2 = q2n;
+// The tail's values in LDS: the four 16-byte rows of the slot records (W,
+// then V or U) as separate arrays of TS, so that lanes on consecutive slots
+// read consecutive 16-byte words (records of 64 bytes would put four lanes
+// on each bank), then the nodes' pivot blocks and the rhs.
+struct TailLds {
+    double2* r;  // TS x 4 rows
+    double* d;   // K x 4
+    double* y;   // K x 2
+    double* q;   // K: one over the pivot block's determinant
+    int TS;
+    __device__ __forceinline__ explicit TailLds(const DevSym& S)
+        : r(reinterpret_cast<double2*>(pf_smem)),
+          d(pf_smem + 8 * S.tail_slots),
+          y(d + 4 * S.tail_nodes),
+          q(y + 2 * S.tail_nodes),
+          TS(S.tail_slots)
+    {
     }
-}
+    // pivot block of node j and its inverse
+    __device__ __forceinline__ void setD(int j, const Blk& v) const
+    {
+        bstore(d + 4 * j, v);
+        q[j] = 1.0 / (v.a * v.d - v.b * v.c);
+    }
+    __device__ __forceinline__ Blk Dinv(int j) const
+    {
+        const Blk v = bload(d + 4 * j);
+        const double i = q[j];
+        return {v.d * i, -v.b * i, -v.c * i, v.a * i};
+    }
+    __device__ __forceinline__ Blk get(int row, int t) const
+    {
+        const double2 u = r[row * TS + t], v = r[(row + 1) * TS + t];
+        return {u.x, u.y, v.x, v.y};
+    }
+    __device__ __forceinline__ void put(int row, int t, const Blk& v) const
+    {
+        r[row * TS + t] = make_double2(v.a, v.b);
+        r[(row + 1) * TS + t] = make_double2(v.c, v.d);
+    }
+    __device__ __forceinline__ Blk W(int t) const { return get(0, t); }
+    __device__ __forceinline__ Blk U(int t) const { return get(2, t); }
+    __device__ __forceinline__ void setW(int t, const Blk& v) const { put(0, t, v); }
+    __device__ __forceinline__ void setU(int t, const Blk& v) const { put(2, t, v); }
+    __device__ __forceinline__ double2 yv(int j) const
+    {
+        return *reinterpret_cast<const double2*>(y + 2 * j);
+    }
+    __device__ __forceinline__ void sety(int j, double a, double b) const
+    {
+        *reinterpret_cast<double2*>(y + 2 * j) = make_double2(a, b);
+    }
+};
 
 // Group sums of a block and, with rhs, of a 2-vector, all six interleaved.
 __device__ __forceinline__ void gsum_blk(Blk& v, double& z0, double& z1, bool rhs, int g)
@@ -1079,13 +1084,20 @@ __device__ __forceinline__ int clique_slot(int c0, int KC, int a, int b)
 // The LDS tail of the factorisation.
 // Phase A (all threads, no ordering): every tail diagonal, rhs entry and
 //   slot takes the updates of descendants outside the tail (global memory).
-// Phase B: the tail levels below the clique, in order, in LDS.
-// Phase C: clique entries take the updates of tail nodes below the clique.
-// Phase D: the clique as a dense block, right-looking: at pivot a every
-//   thread forms D_a^-1 and y_a itself, then the trailing blocks (k, l) are
-//   updated in parallel, A_kl -= W_ka D_a^-1 V_al, with one barrier per
-//   pivot; row a is normalised (U_al = D_a^-1 V_al) during pivot a + 1,
-//   when nobody reads it any more.
+// Phase B: the levels upward, right-looking: once a level's pivots are
+//   final, every block above that one of its nodes j updates (A_kl -= W_kj
+//   D_j^-1 V_jl, the rhs with the diagonal) is one operation of the level's
+//   list (t_op), one thread each, the terms of a destination with several
+//   such nodes in one thread in a fixed order; one barrier per level.  The
+//   level's cost is one short chain (operands from LDS, the products, for a
+//   diagonal the determinant's reciprocal) instead of a node's whole
+//   lower-neighbour list and a slot's update list (up to 44 pairs) in one
+//   lane.  Bound by that chain, and on levels with an operation for every
+//   thread by the operations' LDS reads (15 of 16 bytes each).  Measured per
+//   Newton step: 200 buses, 31 levels, 31 us left-looking -> 22 us; 10,000
+//   buses, 256 cases, 56 levels, about 190 -> 100 us.
+// Phase C: all rows normalised at once (U_jk = D_j^-1 V_jk, y_j); the pivots
+//   stay as they are in LDS.
 // WRITE stores the tail's factors to global memory.
 // With a Spread split, every workgroup of the launch takes a share of phase
 // A and leaves its results in the tail's own places in global memory (the
@@ -1097,11 +1109,9 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                                             int64_t lu, const View& wr, int64_t rhs, int* s_bad,
                                             const P& par = P{})
 {
-    const int K = S.tail_nodes, TS = S.tail_slots, KC = S.tail_clique;
+    const int K = S.tail_nodes, TS = S.tail_slots;
     const int nT = S.nlev - S.tail_level;
-    double* sLU = pf_smem;             // TS x 8: W, then V -> U
-    double* sD = pf_smem + 8 * TS;     // K x 4: accumulated pivot, then D^-1
-    double* sy = sD + 4 * K;           // K x 2: accumulated rhs, then y
+    const TailLds L(S);
     const int a0 = P::kSpread ? par.rank() * (int)blockDim.x + (int)threadIdx.x : threadIdx.x;
     const int as = P::kSpread ? par.size() * (int)blockDim.x : blockDim.x;
     for (int it = a0; it < K + TS; it += as) {
@@ -1159,9 +1169,8 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                 w.put(4 * (int64_t)t0.x, acc);
                 if (FWD) wr.put2(rhs + 2 * (int64_t)t0.x, make_double2(z0, z1));
             } else {
-                bstore(sD + 4 * it, acc);
-                sy[2 * it] = z0;
-                sy[2 * it + 1] = z1;
+                L.setD(it, acc);
+                L.sety(it, z0, z1);
             }
         } else {
             const int t = it - K;
@@ -1175,8 +1184,8 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                 w.put(lu + 8 * (int64_t)a.x, Wk);
                 w.put(lu + 8 * (int64_t)a.x + 4, Vk);
             } else {
-                bstore(sLU + 8 * t, Wk);
-                bstore(sLU + 8 * t + 4, Vk);
+                L.setW(t, Wk);
+                L.setU(t, Vk);
             }
         }
     }
@@ -1186,218 +1195,85 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
         for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
             if (it < K) {
                 const int j = S.t_node[3 * it].x;
-                bstore(sD + 4 * it, w.blk(4 * (int64_t)j));
+                L.setD(it, w.blk(4 * (int64_t)j));
                 const double2 z = FWD ? wr.v2(rhs + 2 * (int64_t)j) : make_double2(0.0, 0.0);
-                sy[2 * it] = z.x;
-                sy[2 * it + 1] = z.y;
+                L.sety(it, z.x, z.y);
             } else {
                 const int t = it - K;
                 const int64_t sg = lu + 8 * (int64_t)S.t_slot[3 * t].x;
-                bstore(sLU + 8 * t, w.blk(sg));
-                bstore(sLU + 8 * t + 4, w.blk(sg + 4));
+                L.setW(t, w.blk(sg));
+                L.setU(t, w.blk(sg + 4));
             }
         }
     }
     __syncthreads();
-    // Each level's node records arrive before its barrier; a lane's first
-    // slot record and that slot's first packed pair loads are requested
-    // before the lower-neighbour sums, so the slot loop starts on indices
-    // already in registers.
-    for_tail_pf(S, 0, nT - KC, true, [&](int jl, const int4& t0, const int4& t1, const int4&,
-                                         int lane, int g) {
-        const int4 z4 = make_int4(0, 0, 0, 0);
-        const uint4 zq = make_uint4(0, 0, 0, 0);
-        int t = t0.w + lane;
-        int4 sb = z4, sc = z4;
-        if (t < t1.x) {
-            sb = S.t_slot[3 * t + 1];
-            sc = S.t_slot[3 * t + 2];
-        }
-        int r = t1.z + lane;
-        int2 e = make_int2(0, 0);
-        if (r < t1.w) e = S.t_rl[r];
-        int np = sb.w - sb.z;
-        uint4 q0 = zq, q1 = zq;
-        if (np > 0) q0 = S.t_pk[sc.w];
-        if (np > 4) q1 = S.t_pk[sc.w + 1];
-        Blk ds = bzero();
-        double z0 = 0.0, z1 = 0.0;
-        for (; r < t1.w; r += g) {
-            const int2 en = upd_at(S.t_rl, r + g, t1.w);
-            const Blk wv = bload(sLU + 8 * e.y);
-            bmadd(ds, wv, bload(sLU + 8 * e.y + 4));
-            if (FWD) mvadd(z0, z1, wv, sy[2 * e.x], sy[2 * e.x + 1]);
-            e = en;
-        }
-        if (g > 1) {
-            gsum_blk(ds, z0, z1, FWD, g);
-        }
-        const Blk A = bload(sD + 4 * jl);
-        bool ok;
-        const Blk Di = binv({A.a - ds.a, A.b - ds.b, A.c - ds.c, A.d - ds.d}, ok);
-        for (; t < t1.x; t += g) {
-            const int tn = t + g;
-            int4 sbn = z4, scn = z4;
-            if (tn < t1.x) {
-                sbn = S.t_slot[3 * tn + 1];
-                scn = S.t_slot[3 * tn + 2];
-            }
-            Blk Wk = bload(sLU + 8 * t), Vk = bload(sLU + 8 * t + 4);
-            apply_packed_lds(S.t_pk, sc.w, np, q0, q1, sLU, Wk, Vk);
-            bstore(sLU + 8 * t, Wk);
-            bstore(sLU + 8 * t + 4, bmul(Di, Vk));
-            sc = scn;
-            np = sbn.w - sbn.z;
-            q0 = zq;
-            q1 = zq;
-            if (np > 0) q0 = S.t_pk[sc.w];
-            if (np > 4) q1 = S.t_pk[sc.w + 1];
-        }
-        if (lane == 0) {
-            if (!ok) mark_pivot(s_bad, S.level_ptr[S.tail_level] + jl);
-            bstore(sD + 4 * jl, Di);
-            if (FWD) {
-                double y0 = 0.0, y1 = 0.0;
-                mvadd(y0, y1, Di, sy[2 * jl] - z0, sy[2 * jl + 1] - z1);
-                sy[2 * jl] = y0;
-                sy[2 * jl + 1] = y1;
-            }
-        }
-    });
-    if (KC > 0) {
-        const int kf = K - KC;
-        const int c0 = S.t_node[3 * kf].w;  // first local slot of the clique
-        // phase C: clique diagonals, rhs and slots take the tail updates from below
-        for (int it = threadIdx.x; it < KC + (TS - c0); it += blockDim.x) {
-            if (it < KC) {
-                // the packed local R list, below-clique part (its prefix)
-                const int jl = kf + it;
-                const int4 t1 = S.t_node[3 * jl + 1];
-                const int4 t2 = S.t_node[3 * jl + 2];
-                const int nR = t2.x - t1.z;
-                Blk acc = bload(sD + 4 * jl);
-                double z0 = sy[2 * jl], z1 = sy[2 * jl + 1];
-                uint4 q = S.t_pk[nR > 0 ? t2.y : 0];
-                for (int k = 0; k < nR; k += 4) {
-                    const uint4 qn = S.t_pk[k + 4 < nR ? t2.y + (k >> 2) + 1 : 0];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        if (k + c < nR) {
-                            const uint32_t v = pk_word(q, c);
-                            const int il = v & 0xffff, sl = v >> 16;
-                            const Blk wv = bload(sLU + 8 * sl);
-                            bmsub(acc, wv, bload(sLU + 8 * sl + 4));
-                            if (FWD) {
-                                z0 = fma(-wv.a, sy[2 * il], fma(-wv.b, sy[2 * il + 1], z0));
-                                z1 = fma(-wv.c, sy[2 * il], fma(-wv.d, sy[2 * il + 1], z1));
-                            }
-                        }
-                    }
-                    q = qn;
-                }
-                bstore(sD + 4 * jl, acc);
-                sy[2 * jl] = z0;
-                sy[2 * jl + 1] = z1;
-            } else {
-                // the packed local pair list, below-clique part (its prefix)
-                const int t = c0 + (it - KC);
-                const int4 b = S.t_slot[3 * t + 1];
-                const int4 c = S.t_slot[3 * t + 2];
-                Blk Wk = bload(sLU + 8 * t), Vk = bload(sLU + 8 * t + 4);
-                Blk W2 = bzero(), V2 = bzero();
-                apply_packed2_lds(S.t_pk, c.w, c.z - b.z, 0, 0, sLU, Wk, Vk, W2, V2);
-                bstore(sLU + 8 * t, Wk);
-                bstore(sLU + 8 * t + 4, Vk);
-            }
-        }
-        __syncthreads();
-        // phase D: dense right-looking over the clique's pivots.  Pivots with a
-        // large trailing block use every thread, one barrier each; the last
-        // ones (at most two updates per lane of one wavefront) run on the
-        // first wavefront alone, without workgroup barriers.
-        Blk Dprev = bzero();
-        double yp0 = 0.0, yp1 = 0.0;
-        auto pivot = [&](int a, int stride) {
-            const int m = KC - 1 - a;  // trailing size
-            Blk Di = bzero();
-            double ya0 = 0.0, ya1 = 0.0;
-            if (a < KC) {
-                const int ja = kf + a;
-                bool ok;
-                Di = binv(bload(sD + 4 * ja), ok);
-                if (!ok && threadIdx.x == 0) mark_pivot(s_bad, S.level_ptr[S.tail_level] + ja);
-                if (FWD) mvadd(ya0, ya1, Di, sy[2 * ja], sy[2 * ja + 1]);
-            }
-            const int nupd = (a < KC) ? m * m : 0;
-            const int nnorm = (a > 0) ? (KC - a) + 1 : 0;  // row a-1 slots + its pivot
-            for (int it = threadIdx.x; it < nupd + nnorm; it += stride) {
-                if (it < nupd) {
-                    const unsigned q = (unsigned)it / (unsigned)m;
-                    const int k = a + 1 + (int)q, l = a + 1 + (it - (int)q * m);
-                    const Blk Wka = bload(sLU + 8 * clique_slot(c0, KC, a, k));
-                    const Blk Ual = bmul(Di, bload(sLU + 8 * clique_slot(c0, KC, a, l) + 4));
-                    const int jk = kf + k;
-                    if (k == l) {
-                        Blk d = bload(sD + 4 * jk);
-                        bmsub(d, Wka, Ual);
-                        bstore(sD + 4 * jk, d);
-                        if (FWD) {
-                            sy[2 * jk] = fma(-Wka.a, ya0, fma(-Wka.b, ya1, sy[2 * jk]));
-                            sy[2 * jk + 1] = fma(-Wka.c, ya0, fma(-Wka.d, ya1, sy[2 * jk + 1]));
-                        }
-                    } else if (k > l) {
-                        double* p = sLU + 8 * clique_slot(c0, KC, l, k);
-                        Blk v = bload(p);
-                        bmsub(v, Wka, Ual);
-                        bstore(p, v);
-                    } else {
-                        double* p = sLU + 8 * clique_slot(c0, KC, k, l) + 4;
-                        Blk v = bload(p);
-                        bmsub(v, Wka, Ual);
-                        bstore(p, v);
-                    }
-                } else {
-                    const int r = it - nupd;  // normalise row a-1
-                    const int jp = kf + a - 1;
-                    if (r < KC - a) {
-                        double* p = sLU + 8 * clique_slot(c0, KC, a - 1, a + r) + 4;
-                        bstore(p, bmul(Dprev, bload(p)));
-                    } else {
-                        bstore(sD + 4 * jp, Dprev);
-                        if (FWD) {
-                            sy[2 * jp] = yp0;
-                            sy[2 * jp + 1] = yp1;
-                        }
-                    }
-                }
-            }
-            Dprev = Di;
-            yp0 = ya0;
-            yp1 = ya1;
+    for_tail_ops<0>(S, nT, [&](uint2 q, int at, bool slot) {
+        // One form for both kinds, so that a wavefront holding both runs one
+        // path: A -= W_a D_j^-1 V_b with A = W_d, or the diagonal D_d; then
+        // B -= W_b D_j^-1 X with B = V_d and X = V_a, or (a diagonal, a = b)
+        // B = z_d and X = z_j, as the first column of a block.
+        TailOp o = tail_op(q);
+        double2* const a0 = slot ? L.r + o.d : reinterpret_cast<double2*>(L.d) + 2 * o.d;
+        double2* const a1 = slot ? L.r + TS + o.d : a0 + 1;
+        double2* const b0 = slot ? L.r + 2 * TS + o.d : reinterpret_cast<double2*>(L.y) + o.d;
+        double2* const b1 = slot ? L.r + 3 * TS + o.d : b0;
+        auto as_block = [&](const double2& u, const double2& v) {
+            return Blk{u.x, slot ? u.y : 0.0, slot ? v.x : u.y, slot ? v.y : 0.0};
         };
-        int a = 0;
-        for (; a <= KC && (KC - 1 - a) * (KC - 1 - a) > 2 * kWave; ++a) {
-            pivot(a, blockDim.x);
-            __syncthreads();
+        Blk A, B;
+        {
+            const double2 u = *a0, v = *a1;
+            A = {u.x, u.y, v.x, v.y};
+            B = as_block(*b0, *b1);
         }
-        if (threadIdx.x < kWave) {
-            for (int b = a; b <= KC; ++b) {
-                pivot(b, kWave);
-                wave_sync();
+        for (;;) {
+            const double2* const x0 =
+                slot ? L.r + 2 * TS + o.a : reinterpret_cast<const double2*>(L.y) + o.j;
+            const double2* const x1 = slot ? L.r + 3 * TS + o.a : x0;
+            const Blk Wa = L.W(o.a), Wb = L.W(o.b), Vb = L.U(o.b);
+            const Blk X = as_block(*x0, *x1);
+            const Blk Di = L.Dinv(o.j);
+            bmsub(A, Wa, bmul(Di, Vb));
+            bmsub(B, Wb, bmul(Di, X));
+            if (!o.next) break;
+            at += o.next;
+            o = tail_op(S.t_op[at]);
+        }
+        *a0 = make_double2(A.a, A.b);
+        *a1 = make_double2(A.c, A.d);
+        *b0 = make_double2(B.a, slot ? B.b : B.c);
+        if (slot) *b1 = make_double2(B.c, B.d);
+        else L.q[o.d] = 1.0 / (A.a * A.d - A.b * A.c);
+    });
+    for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
+        if (it < K) {
+            const Blk D = bload(L.d + 4 * it);
+            bool ok;
+            (void)binv(D, ok);
+            if (!ok) mark_pivot(s_bad, S.level_ptr[S.tail_level] + it);
+            if (FWD) {
+                const double2 z = L.yv(it);
+                const Blk Di = L.Dinv(it);
+                double y0 = 0.0, y1 = 0.0;
+                mvadd(y0, y1, Di, z.x, z.y);
+                L.sety(it, y0, y1);
             }
+        } else {
+            const int t = it - K;
+            L.setU(t, bmul(L.Dinv(S.t_slot[3 * t + 2].y), L.U(t)));
         }
-        __syncthreads();
     }
+    __syncthreads();
     if (WRITE) {
         for (int t = threadIdx.x; t < TS; t += blockDim.x) {
             const int s = S.t_slot[3 * t].x;
-            w.put(lu + 8 * (int64_t)s, bload(sLU + 8 * t));
-            w.put(lu + 8 * (int64_t)s + 4, bload(sLU + 8 * t + 4));
+            w.put(lu + 8 * (int64_t)s, L.W(t));
+            w.put(lu + 8 * (int64_t)s + 4, L.U(t));
         }
         for (int jl = threadIdx.x; jl < K; jl += blockDim.x) {
             const int j = S.t_node[3 * jl].x;
-            w.put(4 * (int64_t)j, bload(sD + 4 * jl));
-            if (FWD) wr.put2(rhs + 2 * (int64_t)j, make_double2(sy[2 * jl], sy[2 * jl + 1]));
+            w.put(4 * (int64_t)j, L.Dinv(jl));
+            if (FWD) wr.put2(rhs + 2 * (int64_t)j, L.yv(jl));
         }
         __syncthreads();
     }
@@ -1423,7 +1299,10 @@ __device__ __forceinline__ void apply_step(const View& w, int64_t rec, bool pv, 
 
 // Backward substitution of the tail from LDS: x_j = y_j - sum U_jk x_k.  The
 // clique goes first, on the first wavefront alone, column-oriented: once x_a
-// is final, y_k -= U_ka x_a for every clique node k below a.  The x of the
+// is final, y_k -= U_ka x_a for every clique node k below a.  Every node
+// below the clique then takes the clique's terms, and the levels follow
+// downward, column-oriented too: one thread per slot whose higher neighbour
+// is on the level (each lower node has at most one of them).  The x of the
 // tail nodes are written to the rhs (for the levels below) and, with UPDATE,
 // applied to the bus records in one parallel pass at the end, so that no
 // level waits for a bus-record load.  With xs (the solution vector in LDS by
@@ -1434,43 +1313,50 @@ template <bool UPDATE>
 __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, int64_t rhs,
                                               int64_t bus_off, PvMask type, double2* xs)
 {
-    const int K = S.tail_nodes, TS = S.tail_slots, KC = S.tail_clique;
+    const int K = S.tail_nodes, KC = S.tail_clique;
     const int nT = S.nlev - S.tail_level;
-    const double* sLU = pf_smem;
-    double* sy = pf_smem + 8 * TS + 4 * K;
+    const TailLds L(S);
+    double* const sy = L.y;
+    const int kf = K - KC;
     if (KC > 0) {
+        const int c0 = S.t_node[3 * kf].w;
         if (threadIdx.x < kWave) {
-            const int kf = K - KC;
-            const int c0 = S.t_node[3 * kf].w;
             for (int a = KC - 1; a > 0; --a) {
                 const int ja = kf + a;
-                const double x0 = sy[2 * ja], x1 = sy[2 * ja + 1];
+                const double2 x = L.yv(ja);
                 for (int k = threadIdx.x; k < a; k += kWave) {
                     const int jk = kf + k;
-                    const Blk U = bload(sLU + 8 * clique_slot(c0, KC, k, a) + 4);
-                    sy[2 * jk] = fma(-U.a, x0, fma(-U.b, x1, sy[2 * jk]));
-                    sy[2 * jk + 1] = fma(-U.c, x0, fma(-U.d, x1, sy[2 * jk + 1]));
+                    const Blk U = L.U(clique_slot(c0, KC, k, a));
+                    const double2 y = L.yv(jk);
+                    L.sety(jk, fma(-U.a, x.x, fma(-U.b, x.y, y.x)),
+                           fma(-U.c, x.x, fma(-U.d, x.y, y.y)));
                 }
                 wave_sync();
             }
         }
         __syncthreads();
+        // the clique's terms of every node below it
+        for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
+            const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
+            double2 y = L.yv(jl);
+            for (int t = t1 - 1; t >= t0; --t) {  // the clique's are the last ones
+                const int k = S.t_slot[3 * t].y;
+                if (k < kf) break;
+                const Blk U = L.U(t);
+                const double2 x = L.yv(k);
+                y.x = fma(-U.a, x.x, fma(-U.b, x.y, y.x));
+                y.y = fma(-U.c, x.x, fma(-U.d, x.y, y.y));
+            }
+            L.sety(jl, y.x, y.y);
+        }
+        __syncthreads();
     }
-    for_tail_range(S, 0, nT - KC, false, [&](int jl, int lane, int g) {
-        const int4 t0 = S.t_node[3 * jl];
-        const int4 t1 = S.t_node[3 * jl + 1];
-        double a0 = 0.0, a1 = 0.0;
-        for (int t = t0.w + lane; t < t1.x; t += g) {
-            const int kl = S.t_slot[3 * t].y;
-            mvadd(a0, a1, bload(sLU + 8 * t + 4), sy[2 * kl], sy[2 * kl + 1]);
-        }
-        if (g > 1) {
-            gsum2(a0, a1, g);
-        }
-        if (lane == 0) {
-            sy[2 * jl] -= a0;
-            sy[2 * jl + 1] -= a1;
-        }
+    for_tail_ops<1>(S, nT - KC, [&](uint2 q, int, bool) {
+        const TailOp o = tail_op(q);
+        const Blk U = L.U(o.a);
+        const double2 x = L.yv(o.b), y = L.yv(o.d);
+        L.sety(o.d, fma(-U.a, x.x, fma(-U.b, x.y, y.x)),
+               fma(-U.c, x.x, fma(-U.d, x.y, y.y)));
     });
     if (xs) {
         double2 xr[4];

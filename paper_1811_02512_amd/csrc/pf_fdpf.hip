@@ -205,33 +205,25 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
         sy[jl] = z;
     }
     __syncthreads();
+    // the levels below the clique, right-looking: the diagonal operations of
+    // the factorisation's lists carry the rhs terms z_k -= w_kj (z_j / d_j)
     const int nT = S.nlev - S.tail_level, KC = S.tail_clique;
-    for_tail_pf(S, 0, nT - KC, true, [&](int jl, const int4&, const int4& b, const int4&,
-                                         int lane, int g) {
-        double z = 0.0;
-        for (int r = b.z + lane; r < b.w; r += g) {
-            const int2 e = S.t_rl[r];
-            z = fma(t.wu[e.y].x, sy[e.x], z);
+    const int kf = S.tail_nodes - KC;
+    for_tail_ops<2>(S, nT - KC, [&](uint2 q, int at, bool) {
+        TailOp o = tail_op(q);
+        double z = sy[o.d];
+        for (;;) {
+            z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
+            if (!o.next) break;
+            at += o.next;
+            o = tail_op(S.t_op[at]);
         }
-        if (g > 1) z = gsum(z, g);
-        if (lane == 0) sy[jl] = t.d[jl] * (sy[jl] - z);
+        sy[o.d] = z;
     });
+    for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) sy[jl] *= t.d[jl];
     if (KC > 0) {
-        // the clique (every node adjacent to all above it): first the terms of
-        // the tail nodes below it, all clique nodes at once; then the clique
-        // column by column on the first wavefront (no workgroup barriers)
-        const int kf = S.tail_nodes - KC;
-        for (int c = threadIdx.x; c < KC; c += blockDim.x) {
-            const int jl = kf + c;
-            const int4 b = S.t_node[3 * jl + 1], cm = S.t_node[3 * jl + 2];
-            double z = 0.0;
-            for (int r = b.z; r < cm.x; ++r) {
-                const int2 e = S.t_rl[r];
-                z = fma(t.wu[e.y].x, sy[e.x], z);
-            }
-            sy[jl] -= z;
-        }
-        __syncthreads();
+        // the clique (every node adjacent to all above it) column by column
+        // on the first wavefront (no workgroup barriers)
         if (threadIdx.x < kWave) {
             const int c0 = S.t_node[3 * kf].w;
             for (int q = 0; q < KC; ++q) {
@@ -242,8 +234,8 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
                 wave_sync();
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
 }
 
 // Backward substitution of the tail levels in LDS, downward; then, in one
@@ -256,11 +248,13 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
 {
     const int comp = ANGLE ? 0 : 1;
     const int nT = S.nlev - S.tail_level, KC = S.tail_clique;
+    const int kf = S.tail_nodes - KC;
     if (KC > 0) {
         // the clique first, column by column on the first wavefront: once x_q
-        // is final, y_k -= u_kq x_q for every clique node k below q
+        // is final, y_k -= u_kq x_q for every clique node k below q; then the
+        // clique's terms of every node below it
         if (threadIdx.x < kWave) {
-            const int kf = S.tail_nodes - KC, c0 = S.t_node[3 * kf].w;
+            const int c0 = S.t_node[3 * kf].w;
             for (int q = KC - 1; q > 0; --q) {
                 const double xq = sy[kf + q];
                 for (int k = threadIdx.x; k < q; k += kWave)
@@ -269,13 +263,21 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
             }
         }
         __syncthreads();
+        for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
+            const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
+            double y = sy[jl];
+            for (int q = t1 - 1; q >= t0; --q) {
+                const int k = S.t_slot[3 * q].y;
+                if (k < kf) break;
+                y = fma(-t.wu[q].y, sy[k], y);
+            }
+            sy[jl] = y;
+        }
+        __syncthreads();
     }
-    for_tail_pf(S, 0, nT - KC, false, [&](int jl, const int4& a, const int4& b, const int4&,
-                                          int lane, int g) {
-        double s = 0.0;
-        for (int q = a.w + lane; q < b.x; q += g) s = fma(t.wu[q].y, sy[S.t_slot[3 * q].y], s);
-        if (g > 1) s = gsum(s, g);
-        if (lane == 0) sy[jl] -= s;
+    for_tail_ops<1>(S, nT - KC, [&](uint2 q, int, bool) {
+        const TailOp o = tail_op(q);
+        sy[o.d] = fma(-t.wu[o.a].y, sy[o.b], sy[o.d]);
     });
     __syncthreads();
     for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x) {

@@ -30,26 +30,29 @@ namespace pf {
 // values fit in LDS, are factorised and solved in LDS.  Every higher
 // neighbour of a tail node is itself in the tail.  Local numbering: tail
 // nodes 0..K-1 in level order, tail slots 0..TS-1 in node order.
-//   t_node[jl] (3 x int4): {j, bus, ydiag, sl0}, {sl1, rn0, rn1, rt1}, {rmid, pk, 0, 0}
+//   t_node[jl] (3 x int4): {j, bus, ydiag, sl0}, {sl1, rn0, rn1, rt1}, {rmid, 0, 0, 0}
 //     [sl0, sl1) local slots, [rn0, rn1) lower neighbours outside the tail
 //     as (i, slot) global pairs in t_rl, [rn1, rt1) lower neighbours inside
 //     the tail as (local i, local slot) pairs in t_rl, those below the
 //     clique first: [rn1, rmid) below, [rmid, rt1) in the clique
-//   t_slot[t] (3 x int4): {s, kl, bus_k, ylo}, {yup, un0, un1, ut1},
-//                         {bus_j, jl, umid, pk}
+//   t_slot[t] (3 x int4): {s, kl, bus_k, ylo}, {yup, un0, un1, 0},
+//                         {bus_j, jl, 0, 0}
 //     s = global slot, kl = local node of k, [un0, un1) update pairs from
-//     outside the tail (global slots) and [un1, ut1) from inside (local),
-//     [un1, umid) from below the clique, [umid, ut1) from the clique;
-//     jl = local node owning the slot
+//     outside the tail (global slots); jl = local node owning the slot
 //   The clique is the last tail_clique local nodes: a chain of single-node
 //   levels, each adjacent to every node above it (local slot of clique pair
 //   (a, b), a < b, is t_node[a].sl0 + b - a - 1).
-//   t_lptr[l - tail_level .. ]: local node range of each tail level
-//   t_pk: the local lists again, packed: each 32-bit word holds a local pair
-//     (lo 16 bits, hi 16 bits), four words per 16-byte load; a node's local
-//     lower neighbours [rn1, rt1) start at load t_node.pk, a slot's local
-//     update pairs [un1, ut1) at load t_slot.pk; each list is padded to
-//     whole loads
+//   t_op (uint2, four 12-bit local indices and a 16-bit offset): {d | a << 12
+//     | (b & 255) << 24, b >> 8 | j << 4 | next << 16}
+//   t_lev[2 l] = {op0, ns, nd, 0}: the right-looking operations of tail level
+//     l, one per destination d and node j of the level:
+//     operations op0 .. op0 + ns - 1 update slots (W_d -= W_a D_j^-1 V_b,
+//     V_d -= W_b D_j^-1 V_a), op0 + ns .. op0 + nd - 1 diagonals and the rhs
+//     (a = b: D_d -= W_a D_j^-1 V_a, z_d -= W_a D_j^-1 z_j); an operation's
+//     next > 0 names another term of its destination, `next` places on
+//   t_lev[2 l + 1] = {op0, nb, 0, 0}: the backward operations of level l
+//     below the clique: x_d -= U_a x_b for every slot a whose higher
+//     neighbour b is on the level (d owns the slot)
 struct DevSym {
     int32_t n, m, nn, slack;
     int32_t nnz_y, nnz_l, nlev, pad0;
@@ -92,8 +95,8 @@ struct DevSym {
     const int4* t_slot;      // 3 TS
     const int2* t_rl;
     const int2* t_upd;
-    const int32_t* t_lptr;   // nlev - tail_level + 1
-    const uint4* t_pk;
+    const int4* t_lev;       // 2 (nlev - tail_level)
+    const uint2* t_op;
     // Subtrees below a cut level (the group of workgroups that a spread
     // batch of grids gives a case hands each workgroup whole subtrees there,
     // so those levels need workgroup barriers only; a one-case spread launch
@@ -125,7 +128,7 @@ struct HostSym {
     // tail
     int32_t tail_level = 0, tail_nodes = 0, tail_slots = 0, tail_lds = 0, tail_clique = 0;
     int64_t tail_budget = 64 * 1024;
-    std::vector<int32_t> t_node, t_slot, t_rl, t_upd, t_lptr, t_pk;
+    std::vector<int32_t> t_node, t_slot, t_rl, t_upd, t_lev, t_op;
     // subtrees below a cut level (DevSym); rebuilt with the tail
     int32_t sub_cut = 0, sub_roots = 0;
     std::vector<int32_t> sub_idx, sub_ptr, sub_cum;
@@ -168,8 +171,13 @@ struct HostSym {
 };
 
 // LDS bytes of a tail with K nodes and TS slots: W and U (or V) blocks per
-// slot, D^-1 and the forward vector per node.
-inline int64_t tail_bytes(int64_t K, int64_t TS) { return TS * 64 + K * 48; }
+// slot; the pivot block, the forward vector and the reciprocal of the pivot's
+// determinant per node (an odd count of the latter padded to 16 bytes).
+inline int64_t tail_bytes(int64_t K, int64_t TS) { return TS * 64 + K * 48 + (K + 1) / 2 * 16; }
+
+// Tail nodes and slots have 12-bit local indices (t_op); the largest LDS
+// budget holds fewer of either.
+constexpr int64_t kTailIndexMax = 4095;
 
 // LDS bytes of the PV bitmask the Newton kernel keeps after the tail (one bit
 // per bus, whole 64-bit ballot words).
@@ -183,6 +191,7 @@ void default_mapping(HostSym& s);
 // (Re)builds the LDS tail for an LDS budget in bytes (0 disables it), and
 // the subtrees below the cut level under it.
 void build_tail(HostSym& s, int64_t budget);
+void build_tail_ops(HostSym& s);
 // Subtrees of the levels below the tail for spread launches: the highest cut
 // at or below the tail level with at least kSubMinRoots roots (none if no
 // such level).
