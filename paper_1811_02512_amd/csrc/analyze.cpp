@@ -44,6 +44,93 @@ void merge_without(const std::vector<int32_t>& a, const std::vector<int32_t>& b,
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// One level's right-looking terms by destination, for the operation lists:
+// destinations below `slots` are slots, from there on diagonals.  Layout of
+// the positions that place() is given, from 0: every destination's first
+// term (slots, then diagonals), then the second terms of the destinations
+// that have one (slots, then diagonals), then the further terms, each
+// destination's together.  Within a kind, destinations with more terms come
+// first, so a thread finds its second term without reading the first.
+struct LevelTerms {
+    struct Term {
+        int32_t d, a, b, j;
+    };
+    std::vector<Term> terms;
+    std::vector<int32_t> dst, third, count, at, seq;
+    int32_t slots = 0;
+    int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0;  // nd: slots and diagonals
+
+    LevelTerms(int32_t slots_, int32_t nodes)
+        : count((size_t)slots_ + nodes, 0),
+          at((size_t)slots_ + nodes, 0),
+          seq((size_t)slots_ + nodes, 0),
+          slots(slots_)
+    {
+    }
+    void start()
+    {
+        terms.clear();
+        dst.clear();
+    }
+    void add(int32_t d, int32_t a, int32_t b, int32_t j)
+    {
+        if (count[d]++ == 0) dst.push_back(d);
+        terms.push_back({d, a, b, j});
+    }
+    // The terms of node j with slots [s0, s1), higher(t) the neighbour of
+    // slot t and first(k) the first slot of k: slots are indexed alike.
+    template <class H, class F>
+    void add_node(int32_t j, int32_t s0, int32_t s1, H&& higher, F&& first)
+    {
+        for (int32_t b = s0; b < s1; ++b) {
+            const int32_t k = higher(b);
+            add(slots + k, b, b, j);
+            int32_t d = first(k);
+            for (int32_t a = b + 1; a < s1; ++a) {
+                while (higher(d) != higher(a)) ++d;  // present: the filled pattern is closed
+                add(d, a, b, j);
+            }
+        }
+    }
+    // place(position, destination, term, offset of its next term or 0)
+    template <class F>
+    void place(F&& fn)
+    {
+        std::sort(dst.begin(), dst.end(), [&](int32_t u, int32_t v) {
+            if ((u < slots) != (v < slots)) return u < slots;
+            if (count[u] != count[v]) return count[u] > count[v];
+            return u < v;
+        });
+        const int32_t n = (int32_t)dst.size();
+        ns = ns2 = nd2 = 0;
+        nd = n;
+        for (int32_t d : dst) {
+            ns += d < slots;
+            (d < slots ? ns2 : nd2) += count[d] > 1;
+        }
+        int32_t more = n + ns2 + nd2;
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t d = dst[i];
+            at[d] = i;  // index among the destinations
+            seq[d] = 0;
+        }
+        third.assign(n, 0);
+        for (int32_t i = 0; i < n; ++i) {
+            third[i] = more;
+            more += std::max(0, count[dst[i]] - 2);
+        }
+        for (const Term& q : terms) {
+            const int32_t i = at[q.d], k = seq[q.d]++;
+            const int32_t second = n + (i < ns ? i : ns2 + i - ns);
+            const int32_t p = k == 0 ? i : k == 1 ? second : third[i] + k - 2;
+            const bool last = k + 1 == count[q.d];
+            const int32_t nx = k == 0 ? second : third[i] + k - 1;
+            fn(p, q.d < slots ? q.d : q.d - slots, q, last ? 0 : nx - p);
+        }
+        for (int32_t d : dst) count[d] = 0;
+    }
+};
+
 }  // namespace
 
 size_t HostSym::dev_bytes() const
@@ -495,67 +582,25 @@ void build_tail_ops(HostSym& s)
     for (int jl = 0; jl < K; ++jl)
         for (int t = slot0(jl); t < slot1(jl); ++t) own[t] = jl;
     s.t_lev.assign(8 * (size_t)nT, 0);
-    struct Term {
-        int32_t d, a, b, j;  // d: a slot, or TS + a node (its diagonal)
-    };
-    std::vector<Term> terms;
-    std::vector<int32_t> dst, count((size_t)TS + K, 0), at((size_t)TS + K, 0);
+    LevelTerms lt(TS, K);
     auto put = [&](size_t i, uint32_t d, uint32_t a, uint32_t b, uint32_t j, uint32_t next) {
         s.t_op[2 * i] = (int32_t)(d | a << 12 | (b & 255u) << 24);
         s.t_op[2 * i + 1] = (int32_t)(b >> 8 | j << 4 | next << 16);
     };
     for (int tl = 0; tl < nT; ++tl) {
-        const int j0 = s.level_ptr[s.tail_level + tl] - x0;
-        const int j1 = s.level_ptr[s.tail_level + tl + 1] - x0;
-        terms.clear();
-        dst.clear();
-        auto term = [&](int32_t d, int32_t a, int32_t b, int32_t j) {
-            if (count[d]++ == 0) dst.push_back(d);
-            terms.push_back({d, a, b, j});
-        };
-        for (int jl = j0; jl < j1; ++jl)
-            for (int b = slot0(jl); b < slot1(jl); ++b) {
-                const int k = high(b);
-                term(TS + k, b, b, jl);
-                int d = slot0(k);
-                for (int a = b + 1; a < slot1(jl); ++a) {
-                    while (high(d) != high(a)) ++d;  // present: the filled pattern is closed
-                    term(d, a, b, jl);
-                }
-            }
-        // slots before diagonals, destinations with more terms first; the
-        // first terms of all destinations, then each one's further terms
-        std::sort(dst.begin(), dst.end(), [&](int32_t u, int32_t v) {
-            if ((u < TS) != (v < TS)) return u < TS;
-            if (count[u] != count[v]) return count[u] > count[v];
-            return u < v;
+        lt.start();
+        for (int x = s.level_ptr[s.tail_level + tl]; x < s.level_ptr[s.tail_level + tl + 1]; ++x)
+            lt.add_node(x - x0, slot0(x - x0), slot1(x - x0), high, slot0);
+        const size_t op0 = s.t_op.size() / 2;
+        s.t_op.resize(s.t_op.size() + 2 * lt.terms.size());
+        lt.place([&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
+            put(op0 + i, d, q.a, q.b, q.j, next);
         });
-        const int32_t op0 = (int32_t)(s.t_op.size() / 2);
-        s.t_op.resize(s.t_op.size() + 2 * terms.size());
-        int32_t ns = 0, more = op0 + (int32_t)dst.size();
-        for (size_t i = 0; i < dst.size(); ++i) {
-            const int32_t d = dst[i];
-            ns += d < TS;
-            at[d] = op0 + (int32_t)i;  // where its next term goes
-        }
-        // offsets from a destination's first term to its second
-        std::vector<int32_t> second(dst.size());
-        for (size_t i = 0; i < dst.size(); ++i) {
-            second[i] = more;
-            more += count[dst[i]] - 1;
-        }
-        for (const Term& q : terms) {
-            const int32_t p = at[q.d];
-            const bool first = p < op0 + (int32_t)dst.size();
-            const bool last = --count[q.d] == 0;
-            const int32_t nx = first ? second[p - op0] : p + 1;
-            put(p, q.d < TS ? q.d : q.d - TS, q.a, q.b, q.j, last ? 0 : nx - p);
-            at[q.d] = nx;
-        }
         int32_t* r = &s.t_lev[8 * (size_t)tl];
-        r[0] = op0;
-        r[1] = ns;
-        r[2] = (int32_t)dst.size();
+        r[0] = (int32_t)op0;
+        r[1] = lt.ns;
+        r[2] = lt.nd;
+        r[3] = lt.ns2 | lt.nd2 << 16;
     }
     // backward: the slots whose higher neighbour is on the level and below
     // the clique, by that neighbour; S(j) lies on one path to the root, so a

@@ -49,7 +49,7 @@ using namespace pf;
 // ===========================================================================
 // device helpers
 // ===========================================================================
-extern __shared__ double pf_smem[];  // dynamic LDS: tail, (e, f) copy, vectors, PV mask
+extern __shared__ __align__(16) double pf_smem[];  // dynamic LDS: tail, (e, f) copy, vectors, PV mask
 
 namespace {
 
@@ -127,7 +127,9 @@ __device__ __forceinline__ int case_of_block(int b, int C, int B)
         const int hi = b / span, rem = b - hi * span;
         c = (hi * kXcds + (rem & (kXcds - 1))) * C + rem / kXcds;
     }
-    return c < B ? c : -1;
+    // the divisions run on the vector unit: back to a scalar, so that all the
+    // case's base addresses are scalars too
+    return __builtin_amdgcn_readfirstlane(c < B ? c : -1);
 }
 
 // Filled values of case c (64-byte chunks).
@@ -823,54 +825,150 @@ __device__ __forceinline__ TailOp tail_op(const uint2& q)
             (int)(q.y >> 4 & 0xfff), (int)(q.y >> 16)};
 }
 
-// Runs fn(op, index, slot) for the operations of the tail levels [0, nt), one
-// thread per operation, with a workgroup barrier after every level: PART 0
-// the right-looking updates, upward (slot: the destination is a slot), PART 1
-// the backward operations, downward, PART 2 the updates of diagonals only,
-// upward.  A level takes well under a microsecond, less than a load that
-// misses L1, so each lane of a wavefront holds the table entry of one of 64
-// levels (read back by lane index), and a thread's first operation of each
-// of the next kAhead levels is in flight, in registers of its own (moving
-// one to another register would wait for it) and requested in any case (the
-// first of the level stands in for an absent one, so that the number of
-// requests in flight is known and the oldest can be waited for alone).
-template <int PART, class F>
+// The tail's level loops: each lane of a wavefront holds the table entry of
+// one of 64 levels (read back by lane index, where all lanes are active), and
+// a thread's operations of the next kTailAhead levels are requested together
+// while the current ones run (a level takes less time than a load that misses
+// L1), an absent one's place taken by the level's first.
+constexpr int kTailAhead = 4;
+
+// Runs fn(op) for the backward operations of the tail levels [0, nt),
+// downward, one thread each, or with FWD, fn(op, second, index of second) for
+// the updates of diagonals, upward, one thread per destination (second: its
+// second term on the level, if op.next says that there is one); a workgroup
+// barrier after every level.
+template <bool FWD, class F>
 __device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
 {
-    constexpr int kAhead = 4;
     const int T = wg_size();
+    struct Head {
+        int op0, n, two, n2;  // first operation, count; the same of second ones
+    };
     for (int i0 = 0; i0 < nt; i0 += kWave) {
         const int m = nt - i0 < kWave ? nt - i0 : kWave;
-        int h0, hs, hn;
+        Head mine{0, 0, 0, 0};
         {
             const int l = threadIdx.x & (kWave - 1);
             const int i = i0 + (l < m ? l : m - 1);
-            const int4 h = S.t_lev[PART == 1 ? 2 * (nt - 1 - i) + 1 : 2 * i];
-            h0 = PART == 2 ? h.x + h.y : h.x;
-            hs = PART == 0 ? h.y : 0;
-            hn = PART == 0 ? h.z : PART == 1 ? h.y : h.z - h.y;
+            const int4 h = S.t_lev[FWD ? 2 * i : 2 * (nt - 1 - i) + 1];
+            if (FWD) mine = {h.x + h.y, h.z - h.y, h.x + h.z + (h.w & 0xffff), h.w >> 16};
+            else mine = {h.x, h.y, 0, 0};
         }
-        auto first = [&](int i) {
-            const int l = i < m ? i : m - 1;
-            const int n = __builtin_amdgcn_readlane(hn, l);
-            return S.t_op[__builtin_amdgcn_readlane(h0, l) +
-                          ((int)threadIdx.x < n ? (int)threadIdx.x : 0)];
+        auto head = [&](int l) {
+            const int k = l < m ? l : m - 1;
+            return Head{__builtin_amdgcn_readlane(mine.op0, k),
+                        __builtin_amdgcn_readlane(mine.n, k),
+                        FWD ? __builtin_amdgcn_readlane(mine.two, k) : 0,
+                        FWD ? __builtin_amdgcn_readlane(mine.n2, k) : 0};
         };
-        uint2 q[kAhead];
+        auto first = [&](const Head& h, int t) { return S.t_op[h.op0 + (t < h.n ? t : 0)]; };
+        auto second = [&](const Head& h, int t) { return S.t_op[t < h.n2 ? h.two + t : h.op0]; };
+        auto go = [&](const Head& h, int t, const uint2& q, const uint2& r) {
+            if constexpr (FWD) fn(q, r, h.two + t);
+            else fn(q);
+        };
+        uint2 q[kTailAhead], r[kTailAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) q[k] = first(k);
-        for (int i = 0; i < m; i += kAhead) {
+        for (int k = 0; k < kTailAhead; ++k) {
+            const Head h = head(k);
+            q[k] = first(h, threadIdx.x);
+            if (FWD) r[k] = second(h, threadIdx.x);
+        }
+        for (int i = 0; i < m; i += kTailAhead) {
+            uint2 qn[kTailAhead], rn[kTailAhead];
 #pragma unroll
-            for (int k = 0; k < kAhead; ++k) {
+            for (int k = 0; k < kTailAhead; ++k) {
+                const Head h = head(i + k + kTailAhead);
+                qn[k] = first(h, threadIdx.x);
+                if (FWD) rn[k] = second(h, threadIdx.x);
+            }
+#pragma unroll
+            for (int k = 0; k < kTailAhead; ++k) {
                 if (i + k >= m) break;
-                const int op0 = __builtin_amdgcn_readlane(h0, i + k);
-                const int ns = __builtin_amdgcn_readlane(hs, i + k);
-                const int n = __builtin_amdgcn_readlane(hn, i + k);
-                if ((int)threadIdx.x < n) fn(q[k], op0 + (int)threadIdx.x, (int)threadIdx.x < ns);
-                for (int t = threadIdx.x + T; t < n; t += T)
-                    fn(S.t_op[op0 + t], op0 + t, t < ns);
-                q[k] = first(i + k + kAhead);
+                const Head h = head(i + k);
+                if ((int)threadIdx.x < h.n) go(h, threadIdx.x, q[k], r[k]);
+                for (int t = threadIdx.x + T; t < h.n; t += T)
+                    go(h, t, first(h, t), FWD ? second(h, t) : make_uint2(0, 0));
                 __syncthreads();
+            }
+#pragma unroll
+            for (int k = 0; k < kTailAhead; ++k) {
+                q[k] = qn[k];
+                if (FWD) r[k] = rn[k];
+            }
+        }
+    }
+}
+
+// Runs the right-looking updates of the tail levels [0, nt), upward, with a
+// workgroup barrier after every level: quad(op, second, index of second, slot)
+// with four lanes per destination on levels that a quarter of the workgroup's
+// threads cover, else lane(same) with one thread per destination.
+template <class Q, class F>
+__device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& quad, F&& lane)
+{
+    const int T = wg_size(), nq = T >> 2;
+    const int lq = (int)threadIdx.x >> 2;
+    struct Head {
+        int op0, ns, n, ns2, nd2;
+        __device__ __forceinline__ int one(int i) const { return op0 + (i < n ? i : 0); }
+        // position of destination index i's second operation
+        __device__ __forceinline__ int two(int i) const
+        {
+            const bool slot = i < ns;
+            const int k = slot ? i : i - ns;
+            return k < (slot ? ns2 : nd2) ? op0 + n + (slot ? 0 : ns2) + k : op0;
+        }
+    };
+    for (int i0 = 0; i0 < nt; i0 += kWave) {
+        const int m = nt - i0 < kWave ? nt - i0 : kWave;
+        int4 mine;
+        {
+            const int l = threadIdx.x & (kWave - 1);
+            mine = S.t_lev[2 * (i0 + (l < m ? l : m - 1))];
+        }
+        auto head = [&](int l) {
+            const int k = l < m ? l : m - 1;
+            const int c2 = __builtin_amdgcn_readlane(mine.w, k);
+            return Head{__builtin_amdgcn_readlane(mine.x, k), __builtin_amdgcn_readlane(mine.y, k),
+                        __builtin_amdgcn_readlane(mine.z, k), c2 & 0xffff, c2 >> 16};
+        };
+        // this thread's destination on a level
+        auto mine_of = [&](const Head& h) { return h.n <= nq ? lq : (int)threadIdx.x; };
+        uint2 q[kTailAhead], r[kTailAhead];
+#pragma unroll
+        for (int k = 0; k < kTailAhead; ++k) {
+            const Head h = head(k);
+            q[k] = S.t_op[h.one(mine_of(h))];
+            r[k] = S.t_op[h.two(mine_of(h))];
+        }
+        for (int i = 0; i < m; i += kTailAhead) {
+            uint2 qn[kTailAhead], rn[kTailAhead];
+#pragma unroll
+            for (int k = 0; k < kTailAhead; ++k) {
+                const Head h = head(i + k + kTailAhead);
+                qn[k] = S.t_op[h.one(mine_of(h))];
+                rn[k] = S.t_op[h.two(mine_of(h))];
+            }
+#pragma unroll
+            for (int k = 0; k < kTailAhead; ++k) {
+                if (i + k >= m) break;
+                const Head h = head(i + k);
+                const int t = mine_of(h);
+                if (h.n <= nq) {
+                    if (t < h.n) quad(q[k], r[k], [&]() { return h.two(t); }, t < h.ns);
+                } else {
+                    if (t < h.n) lane(q[k], r[k], [&]() { return h.two(t); }, t < h.ns);
+                    for (int u = t + T; u < h.n; u += T)
+                        lane(S.t_op[h.one(u)], S.t_op[h.two(u)], [&]() { return h.two(u); },
+                             u < h.ns);
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int k = 0; k < kTailAhead; ++k) {
+                q[k] = qn[k];
+                r[k] = rn[k];
             }
         }
     }
@@ -1086,16 +1184,19 @@ __device__ __forceinline__ int clique_slot(int c0, int KC, int a, int b)
 //   slot takes the updates of descendants outside the tail (global memory).
 // Phase B: the levels upward, right-looking: once a level's pivots are
 //   final, every block above that one of its nodes j updates (A_kl -= W_kj
-//   D_j^-1 V_jl, the rhs with the diagonal) is one operation of the level's
-//   list (t_op), one thread each, the terms of a destination with several
-//   such nodes in one thread in a fixed order; one barrier per level.  The
-//   level's cost is one short chain (operands from LDS, the products, for a
-//   diagonal the determinant's reciprocal) instead of a node's whole
-//   lower-neighbour list and a slot's update list (up to 44 pairs) in one
-//   lane.  Bound by that chain, and on levels with an operation for every
-//   thread by the operations' LDS reads (15 of 16 bytes each).  Measured per
-//   Newton step: 200 buses, 31 levels, 31 us left-looking -> 22 us; 10,000
-//   buses, 256 cases, 56 levels, about 190 -> 100 us.
+//   D_j^-1 V_jl, the rhs with the diagonal) is one destination of the level's
+//   operation list (t_op), the terms of a destination with several such nodes
+//   in a fixed order; one barrier per level.  A level costs one short chain
+//   (operands from LDS, the products, for a diagonal the determinant's
+//   reciprocal) instead of a node's whole lower-neighbour list and a slot's
+//   update list (up to 44 pairs) in one lane.  It is bound by the
+//   instructions of that chain: on a level with few destinations a quad of
+//   lanes shares one, a row of the result each (8 products per lane instead
+//   of 32); with more than a quarter as many destinations as threads one
+//   thread takes one, where further rounds of quads would cost more.
+//   Measured per Newton step: 200 buses, 31 levels, 31 us left-looking, 22
+//   us with one thread per destination, 20 us so; 10,000 buses, 256 cases,
+//   56 levels and the updates from below, 237, 143 and 103 us.
 // Phase C: all rows normalised at once (U_jk = D_j^-1 V_jk, y_j); the pivots
 //   stay as they are in LDS.
 // WRITE stores the tail's factors to global memory.
@@ -1207,44 +1308,88 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
         }
     }
     __syncthreads();
-    for_tail_ops<0>(S, nT, [&](uint2 q, int at, bool slot) {
-        // One form for both kinds, so that a wavefront holding both runs one
-        // path: A -= W_a D_j^-1 V_b with A = W_d, or the diagonal D_d; then
-        // B -= W_b D_j^-1 X with B = V_d and X = V_a, or (a diagonal, a = b)
-        // B = z_d and X = z_j, as the first column of a block.
-        TailOp o = tail_op(q);
-        double2* const a0 = slot ? L.r + o.d : reinterpret_cast<double2*>(L.d) + 2 * o.d;
-        double2* const a1 = slot ? L.r + TS + o.d : a0 + 1;
-        double2* const b0 = slot ? L.r + 2 * TS + o.d : reinterpret_cast<double2*>(L.y) + o.d;
-        double2* const b1 = slot ? L.r + 3 * TS + o.d : b0;
+    // The terms of a destination from its first operation on.
+    auto terms = [&](const uint2& q, const uint2& second, auto&& at2, auto&& term) {
+        TailOp e = tail_op(q);
+        term(e);
+        if (!e.next) return;
+        e = tail_op(second);
+        term(e);
+        if (!e.next) return;
+        int at = at2();
+        do {
+            at += e.next;
+            e = tail_op(S.t_op[at]);
+            term(e);
+        } while (e.next);
+    };
+    // A quad of lanes per destination, a row of the result each: lanes 0 and
+    // 1 the rows of W_d -= W_a D_j^-1 V_b (or of the diagonal), lanes 2 and 3
+    // those of V_d -= W_b D_j^-1 V_a (or the entries of z_d -= W_a D_j^-1
+    // z_j), as a row of the left block times D_j^-1, then times the right
+    // block.
+    const int row = (int)threadIdx.x & 1;
+    const bool hi = ((int)threadIdx.x & 2) != 0;
+    auto quad = [&](const uint2& q, const uint2& second, auto&& at2, bool slot) {
+        const int d = tail_op(q).d;
+        const bool zrow = hi && !slot;
+        double* const dst = slot ? reinterpret_cast<double*>(L.r + (2 * hi + row) * TS + d)
+                                 : hi ? L.y + 2 * d + row : L.d + 4 * d + 2 * row;
+        double a0 = dst[0], a1 = dst[1];
+        terms(q, second, at2, [&](const TailOp& e) {
+            const double2 l = L.r[row * TS + (hi ? e.b : e.a)];
+            const double2* const right =
+                zrow ? reinterpret_cast<const double2*>(L.y) + e.j
+                     : L.r + 2 * TS + (hi ? e.a : e.b);
+            const double2 u = right[0], v = right[zrow ? 0 : TS];
+            const Blk D = bload(L.d + 4 * e.j);
+            const double i = L.q[e.j];
+            const double t0 = (l.x * D.d - l.y * D.c) * i;
+            const double t1 = (l.y * D.a - l.x * D.b) * i;
+            a0 = fma(-t0, u.x, fma(-t1, zrow ? v.y : v.x, a0));
+            a1 = fma(-t0, u.y, fma(-t1, v.y, a1));
+        });
+        dst[0] = a0;
+        if (!zrow) dst[1] = a1;
+        if (!slot) {
+            // the pivot's determinant from its two rows
+            const double b0 = dpp_peer<0xB1>(a0), b1 = dpp_peer<0xB1>(a1);
+            if (!hi && row == 0) L.q[d] = 1.0 / (a0 * b1 - a1 * b0);
+        }
+    };
+    // One thread per destination, one form for both kinds, so that a wavefront
+    // holding both runs one path: A -= W_a D_j^-1 V_b with A = W_d or the
+    // diagonal D_d, and B -= W_b D_j^-1 X with B = V_d, X = V_a, or (a = b)
+    // B = z_d, X = z_j as the first column of a block.
+    auto lane = [&](const uint2& q, const uint2& second, auto&& at2, bool slot) {
+        const int d = tail_op(q).d;
+        double2* const a0 = slot ? L.r + d : reinterpret_cast<double2*>(L.d) + 2 * d;
+        double2* const a1 = slot ? L.r + TS + d : a0 + 1;
+        double2* const b0 = slot ? L.r + 2 * TS + d : reinterpret_cast<double2*>(L.y) + d;
+        double2* const b1 = slot ? L.r + 3 * TS + d : b0;
         auto as_block = [&](const double2& u, const double2& v) {
             return Blk{u.x, slot ? u.y : 0.0, slot ? v.x : u.y, slot ? v.y : 0.0};
         };
-        Blk A, B;
-        {
-            const double2 u = *a0, v = *a1;
-            A = {u.x, u.y, v.x, v.y};
-            B = as_block(*b0, *b1);
-        }
-        for (;;) {
+        const double2 u = *a0, v = *a1;
+        Blk A = {u.x, u.y, v.x, v.y};
+        Blk B = as_block(*b0, *b1);
+        terms(q, second, at2, [&](const TailOp& e) {
             const double2* const x0 =
-                slot ? L.r + 2 * TS + o.a : reinterpret_cast<const double2*>(L.y) + o.j;
-            const double2* const x1 = slot ? L.r + 3 * TS + o.a : x0;
-            const Blk Wa = L.W(o.a), Wb = L.W(o.b), Vb = L.U(o.b);
+                slot ? L.r + 2 * TS + e.a : reinterpret_cast<const double2*>(L.y) + e.j;
+            const double2* const x1 = slot ? L.r + 3 * TS + e.a : x0;
+            const Blk Wa = L.W(e.a), Wb = L.W(e.b), Vb = L.U(e.b);
             const Blk X = as_block(*x0, *x1);
-            const Blk Di = L.Dinv(o.j);
+            const Blk Di = L.Dinv(e.j);
             bmsub(A, Wa, bmul(Di, Vb));
             bmsub(B, Wb, bmul(Di, X));
-            if (!o.next) break;
-            at += o.next;
-            o = tail_op(S.t_op[at]);
-        }
+        });
         *a0 = make_double2(A.a, A.b);
         *a1 = make_double2(A.c, A.d);
         *b0 = make_double2(B.a, slot ? B.b : B.c);
         if (slot) *b1 = make_double2(B.c, B.d);
-        else L.q[o.d] = 1.0 / (A.a * A.d - A.b * A.c);
-    });
+        else L.q[d] = 1.0 / (A.a * A.d - A.b * A.c);
+    };
+    for_tail_updates(S, nT, quad, lane);
     for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
         if (it < K) {
             const Blk D = bload(L.d + 4 * it);
@@ -1351,7 +1496,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         }
         __syncthreads();
     }
-    for_tail_ops<1>(S, nT - KC, [&](uint2 q, int, bool) {
+    for_tail_ops<false>(S, nT - KC, [&](const uint2& q) {
         const TailOp o = tail_op(q);
         const Blk U = L.U(o.a);
         const double2 x = L.yv(o.b), y = L.yv(o.d);

@@ -209,16 +209,20 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
     // the factorisation's lists carry the rhs terms z_k -= w_kj (z_j / d_j)
     const int nT = S.nlev - S.tail_level, KC = S.tail_clique;
     const int kf = S.tail_nodes - KC;
-    for_tail_ops<2>(S, nT - KC, [&](uint2 q, int at, bool) {
+    for_tail_ops<true>(S, nT - KC, [&](const uint2& q, const uint2& second, int at) {
         TailOp o = tail_op(q);
-        double z = sy[o.d];
-        for (;;) {
+        const int d = o.d;
+        double z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], sy[d]);
+        if (o.next) {
+            o = tail_op(second);
             z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
-            if (!o.next) break;
-            at += o.next;
-            o = tail_op(S.t_op[at]);
+            while (o.next) {
+                at += o.next;
+                o = tail_op(S.t_op[at]);
+                z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
+            }
         }
-        sy[o.d] = z;
+        sy[d] = z;
     });
     for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) sy[jl] *= t.d[jl];
     if (KC > 0) {
@@ -275,7 +279,7 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         }
         __syncthreads();
     }
-    for_tail_ops<1>(S, nT - KC, [&](uint2 q, int, bool) {
+    for_tail_ops<false>(S, nT - KC, [&](const uint2& q) {
         const TailOp o = tail_op(q);
         sy[o.d] = fma(-t.wu[o.a].y, sy[o.b], sy[o.d]);
     });

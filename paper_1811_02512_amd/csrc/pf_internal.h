@@ -44,12 +44,13 @@ namespace pf {
 //   (a, b), a < b, is t_node[a].sl0 + b - a - 1).
 //   t_op (uint2, four 12-bit local indices and a 16-bit offset): {d | a << 12
 //     | (b & 255) << 24, b >> 8 | j << 4 | next << 16}
-//   t_lev[2 l] = {op0, ns, nd, 0}: the right-looking operations of tail level
-//     l, one per destination d and node j of the level:
-//     operations op0 .. op0 + ns - 1 update slots (W_d -= W_a D_j^-1 V_b,
-//     V_d -= W_b D_j^-1 V_a), op0 + ns .. op0 + nd - 1 diagonals and the rhs
-//     (a = b: D_d -= W_a D_j^-1 V_a, z_d -= W_a D_j^-1 z_j); an operation's
-//     next > 0 names another term of its destination, `next` places on
+//   t_lev[2 l] = {op0, ns, nd, ns2 | nd2 << 16}: the right-looking operations
+//     of tail level l, one per destination d and node j of the level: at op0
+//     every destination's first, ns on slots (W_d -= W_a D_j^-1 V_b, V_d -=
+//     W_b D_j^-1 V_a), to nd on diagonals and the rhs (a = b: D_d -= W_a
+//     D_j^-1 V_a, z_d -= W_a D_j^-1 z_j); then the second ones of the first
+//     ns2 slots and the first nd2 diagonals, then further ones; next > 0: the
+//     destination's next operation is that many places on
 //   t_lev[2 l + 1] = {op0, nb, 0, 0}: the backward operations of level l
 //     below the clique: x_d -= U_a x_b for every slot a whose higher
 //     neighbour b is on the level (d owns the slot)
