@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -19,12 +20,36 @@ KERNEL_FILES = ("pf_abi.hip", "pf_newton.hip", "pf_fdpf.hip", "pf_se.hip")
 # Packed fp32 instructions are kept off for every device compile.
 DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-Xclang", "-target-feature", "-Xclang",
                 "-packed-fp32-ops"]
+USAGE = "-Rpass-analysis=kernel-resource-usage"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-I", INCLUDE, "-I", CSRC]
+
+
+def _no_scratch(lines):
+    """Refuses a kernel that uses scratch memory.  The compiler has placed
+    the spill of a vector register where only some lanes were active (in the
+    join of a branch, before the lanes were enabled again), so that the others
+    reloaded garbage; kept in registers the kernels are right, and faster."""
+    name = ""
+    for line in lines:
+        if "Function Name: " in line:
+            name = line.split("Function Name: ")[1].split()[0]
+        m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+        if m and int(m.group(1)):
+            raise RuntimeError(f"build failed: {name} uses {m.group(1)} bytes of scratch per "
+                               "lane; lower its register use")
 
 
 def _run(cmd):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    out = "\n".join(l for l in r.stdout.splitlines()
+    lines = r.stdout.splitlines()
+    if USAGE in cmd:
+        _no_scratch(lines)
+        # the remarks come with three lines of source each
+        cut = [i for i, l in enumerate(lines) if "[-Rpass-analysis" in l]
+        drop = {j for i in cut for j in range(i, min(i + 3, len(lines)))
+                if j == i or "|" in lines[j]}
+        lines = [l for i, l in enumerate(lines) if i not in drop]
+    out = "\n".join(l for l in lines
                     if "packed-fp32-ops" not in l and l.strip() != "1 warning generated.")
     if r.returncode != 0:
         raise RuntimeError("build failed: " + " ".join(cmd) + "\n" + r.stdout)
@@ -41,7 +66,7 @@ def build(verbose: bool = False) -> str:
         objs.append(obj)
     for src in KERNEL_FILES:
         obj = os.path.join(BUILD, src + ".o")
-        _run([HIPCC, *COMMON, *DEVICE_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
+        _run([HIPCC, *COMMON, *DEVICE_FLAGS, USAGE, "-c", os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", *DEVICE_FLAGS, "-o", tmp, *objs])
