@@ -47,7 +47,8 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // One level's right-looking terms by destination, for the operation lists:
 // destinations below `slots` are slots, from there on diagonals.  Layout of
 // the positions that place() is given, from 0: every destination's first
-// term (slots, then diagonals), then the second terms of the destinations
+// term (slots, padded to a multiple of `pad` where diagonals follow, then
+// diagonals), then the second terms of the destinations
 // that have one (slots, then diagonals), then the further terms, each
 // destination's together.  Within a kind, destinations with more terms come
 // first, so a thread finds its second term without reading the first.
@@ -58,7 +59,8 @@ struct LevelTerms {
     std::vector<Term> terms;
     std::vector<int32_t> dst, third, count, at, seq;
     int32_t slots = 0;
-    int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0;  // nd: slots and diagonals
+    // ns: slots (padded), nd: slots and diagonals, total: all positions
+    int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0, total = 0;
 
     LevelTerms(int32_t slots_, int32_t nodes)
         : count((size_t)slots_ + nodes, 0),
@@ -94,7 +96,7 @@ struct LevelTerms {
     }
     // place(position, destination, term, offset of its next term or 0)
     template <class F>
-    void place(F&& fn)
+    void place(int32_t pad, F&& fn)
     {
         std::sort(dst.begin(), dst.end(), [&](int32_t u, int32_t v) {
             if ((u < slots) != (v < slots)) return u < slots;
@@ -102,13 +104,15 @@ struct LevelTerms {
             return u < v;
         });
         const int32_t n = (int32_t)dst.size();
-        ns = ns2 = nd2 = 0;
-        nd = n;
+        int32_t real = 0;
+        ns2 = nd2 = 0;
         for (int32_t d : dst) {
-            ns += d < slots;
+            real += d < slots;
             (d < slots ? ns2 : nd2) += count[d] > 1;
         }
-        int32_t more = n + ns2 + nd2;
+        ns = n > real ? (real + pad - 1) / pad * pad : real;
+        nd = ns + n - real;
+        int32_t more = nd + ns2 + nd2;
         for (int32_t i = 0; i < n; ++i) {
             const int32_t d = dst[i];
             at[d] = i;  // index among the destinations
@@ -119,10 +123,12 @@ struct LevelTerms {
             third[i] = more;
             more += std::max(0, count[dst[i]] - 2);
         }
+        total = more;
         for (const Term& q : terms) {
             const int32_t i = at[q.d], k = seq[q.d]++;
-            const int32_t second = n + (i < ns ? i : ns2 + i - ns);
-            const int32_t p = k == 0 ? i : k == 1 ? second : third[i] + k - 2;
+            const int32_t first = i < real ? i : ns + i - real;
+            const int32_t second = nd + (i < real ? i : ns2 + i - real);
+            const int32_t p = k == 0 ? first : k == 1 ? second : third[i] + k - 2;
             const bool last = k + 1 == count[q.d];
             const int32_t nx = k == 0 ? second : third[i] + k - 1;
             fn(p, q.d < slots ? q.d : q.d - slots, q, last ? 0 : nx - p);
@@ -139,9 +145,10 @@ size_t HostSym::dev_bytes() const
                                           &pos,       &Lp,        &Li,      &ylo,    &yup,
                                           &ydiag,     &Rp,        &Ri,      &Rs,     &level_ptr,
                                           &level_nodes, &level_g, &node_info, &slot_info, &rl,
-                                          &upd,       &t_node,    &t_slot,  &t_rl,   &t_upd,
+                                          &upd,       &t_node,    &t_slot,  &t_rl,
                                           &t_lev,     &t_op,      &from,    &to,     &sub_idx,
-                                          &sub_ptr,   &sub_cum};
+                                          &sub_ptr,   &sub_cum,   &u_node,  &u_slot,  &u_rl,
+                                          &u_upd,     &g_lev,     &g_op,    &g_next};
     size_t total = 0;
     for (auto* a : arrs) total += align256(std::max<size_t>(a->size(), 1) * sizeof(int32_t));
     return total;
@@ -479,10 +486,10 @@ void build_tail(HostSym& s, int64_t budget)
     s.t_node.clear();
     s.t_slot.clear();
     s.t_rl.clear();
-    s.t_upd.clear();
     s.t_lev.clear();
     s.t_op.clear();
     build_subtrees(s);
+    build_upper(s);
     if (K == 0) return;
 
     // clique chain at the top of the tail: level nlev-1-d holds one node
@@ -503,9 +510,7 @@ void build_tail(HostSym& s, int64_t budget)
     }
 
     const int64_t nnzl = (int64_t)s.Li.size();
-    std::vector<int32_t> loc(nn, -1), sloc(nnzl, -1), owner(nnzl, -1);
-    for (int p = 0; p < nn; ++p)
-        for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) owner[q] = p;
+    std::vector<int32_t> loc(nn, -1), sloc(nnzl, -1);
     std::vector<int32_t> tnodes;
     for (int l = L; l < nlev; ++l) {
         for (int x = s.level_ptr[l]; x < s.level_ptr[l + 1]; ++x) {
@@ -519,7 +524,7 @@ void build_tail(HostSym& s, int64_t budget)
     for (int j : tnodes)
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) sloc[q] = ts++;
     s.t_node.assign(12 * (size_t)K, 0);
-    s.t_slot.assign(12 * (size_t)TS, 0);
+    s.t_slot.assign(4 * (size_t)TS, 0);
     int32_t run = 0;
     for (size_t jl = 0; jl < tnodes.size(); ++jl) {
         const int j = tnodes[jl];
@@ -549,24 +554,87 @@ void build_tail(HostSym& s, int64_t budget)
         }
         r[7] = (int32_t)(s.t_rl.size() / 2);
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) {
-            int32_t* t = &s.t_slot[12 * (size_t)sloc[q]];
+            int32_t* t = &s.t_slot[4 * (size_t)sloc[q]];
             t[0] = q;
             t[1] = loc[s.Li[q]];
-            t[2] = s.perm[s.Li[q]];
-            t[3] = s.ylo[q];
-            t[4] = s.yup[q];
-            t[5] = (int32_t)(s.t_upd.size() / 2);
-            for (int u = s.Up[q]; u < s.Up[q + 1]; ++u)
-                if (loc[owner[s.Ub[u]]] < 0) {
-                    s.t_upd.push_back(s.Ua[u]);
-                    s.t_upd.push_back(s.Ub[u]);
-                }
-            t[6] = (int32_t)(s.t_upd.size() / 2);
-            t[8] = s.perm[j];
-            t[9] = (int32_t)jl;
+            t[2] = (int32_t)jl;
         }
     }
     build_tail_ops(s);
+}
+
+// The upper levels of a spread launch, from mid_level on: the tail and below
+// it the levels of at most kMidWidth nodes.  Their updates from lower levels
+// (pulled in one pass), and the right-looking operations of those below the
+// tail.
+void build_upper(HostSym& s)
+{
+    const int nlev = (int)s.level_ptr.size() - 1;
+    int M = s.tail_level;
+    while (M > 0 && s.level_ptr[M] - s.level_ptr[M - 1] <= kMidWidth) --M;
+    s.mid_level = M;
+    for (auto* v : {&s.u_node, &s.u_slot, &s.u_rl, &s.u_upd, &s.g_lev, &s.g_op, &s.g_next})
+        v->clear();
+    const int x1 = s.level_ptr[M];  // first node (level order) of the upper levels
+    std::vector<int32_t> owner(s.Li.size());
+    for (int p = 0; p < s.nn; ++p)
+        for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) owner[q] = p;
+    // part 0: below the upper levels; part 1: the upper levels below the tail
+    auto part = [&](int p) { return s.level[p] <= M ? 0 : s.level[p] <= s.tail_level ? 1 : 2; };
+    for (int x = x1; x < s.nn; ++x) {
+        const int j = s.level_nodes[x];
+        int32_t r[3] = {(int32_t)(s.u_rl.size() / 2), 0, 0};
+        for (int k = 0; k < 2; ++k) {
+            for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q)
+                if (part(s.Ri[q]) == k) {
+                    s.u_rl.push_back(s.Ri[q]);
+                    s.u_rl.push_back(s.Rs[q]);
+                }
+            r[k + 1] = (int32_t)(s.u_rl.size() / 2);
+        }
+        s.u_node.insert(s.u_node.end(),
+                        {j, s.perm[j], s.ydiag[j], r[2], r[0], r[1], s.Lp[j], s.Lp[j + 1]});
+        for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) {
+            int32_t u[3] = {(int32_t)(s.u_upd.size() / 2), 0, 0};
+            for (int k = 0; k < 2; ++k) {
+                for (int v = s.Up[q]; v < s.Up[q + 1]; ++v)
+                    if (part(owner[s.Ub[v]]) == k) {
+                        s.u_upd.push_back(s.Ua[v]);
+                        s.u_upd.push_back(s.Ub[v]);
+                    }
+                u[k + 1] = (int32_t)(s.u_upd.size() / 2);
+            }
+            s.u_slot.insert(s.u_slot.end(), {q, s.perm[j], s.perm[s.Li[q]], s.ylo[q], s.yup[q],
+                                             u[0], u[1], u[2]});
+        }
+    }
+    LevelTerms lt((int32_t)s.Li.size(), s.nn);
+    for (int l = M; l < s.tail_level && l < nlev; ++l) {
+        lt.start();
+        for (int x = s.level_ptr[l]; x < s.level_ptr[l + 1]; ++x) {
+            const int j = s.level_nodes[x];
+            lt.add_node(j, s.Lp[j], s.Lp[j + 1], [&](int32_t t) { return s.Li[t]; },
+                        [&](int32_t k) { return s.Lp[k]; });
+        }
+        const int32_t op0 = (int32_t)s.g_next.size();
+        // room for the padding; the destination -1 marks it
+        s.g_op.resize(4 * ((size_t)op0 + lt.terms.size() + 63), -1);
+        s.g_next.resize((size_t)op0 + lt.terms.size() + 63, 0);
+        lt.place(64, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
+            int32_t* r = &s.g_op[4 * ((size_t)op0 + i)];
+            r[0] = d;
+            r[1] = q.a;
+            r[2] = q.b;
+            r[3] = q.j;
+            s.g_next[(size_t)op0 + i] = next;
+        });
+        s.g_op.resize(4 * ((size_t)op0 + lt.total));
+        s.g_next.resize((size_t)op0 + lt.total);
+        s.g_lev.insert(s.g_lev.end(), {op0, lt.ns, lt.nd, 0, lt.ns2, lt.nd2, 0, 0});
+    }
+    // stands in for the first operation of an empty last level
+    s.g_op.insert(s.g_op.end(), 4, -1);
+    s.g_next.push_back(0);
 }
 
 // The tail's operations by level (layouts documented with DevSym).
@@ -577,7 +645,7 @@ void build_tail_ops(HostSym& s)
     const int x0 = s.level_ptr[s.tail_level];
     auto slot0 = [&](int jl) { return s.t_node[12 * (size_t)jl + 3]; };
     auto slot1 = [&](int jl) { return s.t_node[12 * (size_t)jl + 4]; };
-    auto high = [&](int t) { return s.t_slot[12 * (size_t)t + 1]; };
+    auto high = [&](int t) { return s.t_slot[4 * (size_t)t + 1]; };
     std::vector<int32_t> own(TS);
     for (int jl = 0; jl < K; ++jl)
         for (int t = slot0(jl); t < slot1(jl); ++t) own[t] = jl;
@@ -593,7 +661,7 @@ void build_tail_ops(HostSym& s)
             lt.add_node(x - x0, slot0(x - x0), slot1(x - x0), high, slot0);
         const size_t op0 = s.t_op.size() / 2;
         s.t_op.resize(s.t_op.size() + 2 * lt.terms.size());
-        lt.place([&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
+        lt.place(1, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
             put(op0 + i, d, q.a, q.b, q.j, next);
         });
         int32_t* r = &s.t_lev[8 * (size_t)tl];

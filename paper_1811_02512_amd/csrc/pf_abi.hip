@@ -305,9 +305,17 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     d.t_node = reinterpret_cast<const int4*>(put(h.t_node));
     d.t_slot = reinterpret_cast<const int4*>(put(h.t_slot));
     d.t_rl = reinterpret_cast<const int2*>(put(h.t_rl));
-    d.t_upd = reinterpret_cast<const int2*>(put(h.t_upd));
     d.t_lev = reinterpret_cast<const int4*>(put(h.t_lev));
     d.t_op = reinterpret_cast<const uint2*>(put(h.t_op));
+    d.mid_level = h.mid_level;
+    d.u_slots = (int32_t)(h.u_slot.size() / 8);
+    d.u_node = reinterpret_cast<const int4*>(put(h.u_node));
+    d.u_slot = reinterpret_cast<const int4*>(put(h.u_slot));
+    d.u_rl = reinterpret_cast<const int2*>(put(h.u_rl));
+    d.u_upd = reinterpret_cast<const int2*>(put(h.u_upd));
+    d.g_lev = reinterpret_cast<const int4*>(put(h.g_lev));
+    d.g_op = reinterpret_cast<const int4*>(put(h.g_op));
+    d.g_next = put(h.g_next);
     d.sub_cut = h.sub_cut;
     d.sub_roots = h.sub_roots;
     d.sub_idx = put(h.sub_idx);

@@ -444,6 +444,7 @@ struct SrcState {
         lo = jac_off(o.yl.x, o.yl.y, o.rk.a, o.rk.b, dj.r.a, dj.r.b, vm_of(dj.r), o.pk, dj.pv);
         up = jac_off(o.yu.x, o.yu.y, dj.r.a, dj.r.b, o.rk.a, o.rk.b, vk, dj.pv, o.pk);
     }
+    // the same straight from the bus records (the LDS copy may be gone)
     __device__ __forceinline__ Blk diag(int, int bus, int yd) const
     {
         const double2 y = reinterpret_cast<const double2*>(yv)[yd];
@@ -1179,9 +1180,170 @@ __device__ __forceinline__ int clique_slot(int c0, int KC, int a, int b)
     return c0 + a * (KC - 1) - (a * (a - 1)) / 2 + (b - a - 1);
 }
 
-// The LDS tail of the factorisation.
-// Phase A (all threads, no ordering): every tail diagonal, rhs entry and
-//   slot takes the updates of descendants outside the tail (global memory).
+// Right-looking factorisation of the upper levels below the tail in global
+// memory, on values that have taken every update from below (W, V per slot, D
+// and, with FWD, z): one thread per destination of a level's operation list
+// (g_op), over the threads of every workgroup of the split, one barrier of the
+// split per level.  Leaves the pivots and V as they are (not inverted, not
+// normalised).  A thread's first two terms come from known places of the
+// list: their indices are requested before the barrier that starts the level,
+// then all their values together.
+template <bool FWD, class P>
+__device__ __forceinline__ void factor_ops(const P& par, const DevSym& S, const View& w,
+                                           int64_t lu, const View& wr, int64_t rhs)
+{
+    const int T = wg_size();
+    const int me = par.rank() * T + (int)threadIdx.x, all = par.size() * T;
+    const int nl = S.tail_level - S.mid_level;
+    struct Head {
+        int op0, ns, nd, ns2, nd2;
+        // position of destination index t's second operation
+        __device__ __forceinline__ int two(int t) const
+        {
+            const bool slot = t < ns;
+            const int k = slot ? t : t - ns;
+            return k < (slot ? ns2 : nd2) ? op0 + nd + (slot ? 0 : ns2) + k : op0;
+        }
+    };
+    struct Ops {
+        int4 o, p;
+        int no, np;  // offsets of the term after each, 0 = none
+    };
+    struct Val {
+        Blk Wa, Va, Wb, Vb, D;
+        double2 z;
+    };
+    auto fetch = [&](const Head& h, int t) {
+        const int a = h.op0 + (t < h.nd ? t : 0), b = h.two(t);
+        return Ops{S.g_op[a], S.g_op[b], S.g_next[a], S.g_next[b]};
+    };
+    auto load = [&](const int4& o, bool slot) {
+        Val v;
+        const int64_t ra = lu + 8 * (int64_t)o.y, rb = lu + 8 * (int64_t)o.z;
+        v.D = w.blk(4 * (int64_t)o.w);
+        v.Wa = w.blk(ra);
+        v.Va = w.blk(ra + 4);
+        if (slot) {
+            v.Wb = w.blk(rb);
+            v.Vb = w.blk(rb + 4);
+        } else if (FWD) {
+            v.z = wr.v2(rhs + 2 * (int64_t)o.w);
+        }
+        return v;
+    };
+    // all terms of a destination, the first two's values requested together
+    auto terms = [&](const Ops& e, const Head& h, int t, bool slot, auto&& add) {
+        const Val v = load(e.o, slot);
+        if (!e.no) {
+            add(v);
+            return;
+        }
+        const Val u = load(e.p, slot);
+        add(v);
+        add(u);
+        int at = h.two(t), nx = e.np;
+        while (nx) {
+            at += nx;
+            const int4 o = S.g_op[at];
+            nx = S.g_next[at];
+            add(load(o, slot));
+        }
+    };
+    for (int l0 = 0; l0 < nl; l0 += kWave) {
+        const int m = nl - l0 < kWave ? nl - l0 : kWave;
+        const int hl = (int)(threadIdx.x & (kWave - 1));
+        const int4 ha = S.g_lev[2 * (l0 + (hl < m ? hl : m - 1))];
+        const int4 hb = S.g_lev[2 * (l0 + (hl < m ? hl : m - 1)) + 1];
+        // the table entry of a level, read where all lanes are active
+        auto head = [&](int i) {
+            const int k = i < m ? i : m - 1;
+            return Head{__builtin_amdgcn_readlane(ha.x, k), __builtin_amdgcn_readlane(ha.y, k),
+                        __builtin_amdgcn_readlane(ha.z, k), __builtin_amdgcn_readlane(hb.x, k),
+                        __builtin_amdgcn_readlane(hb.y, k)};
+        };
+        Head h = head(0);
+        Ops cur = fetch(h, me);
+        for (int i = 0; i < m; ++i) {
+            const Head hn = head(i + 1);
+            for (int t = me; t < h.nd; t += all) {
+                const Ops e = cur;
+                if (t + all < h.nd) cur = fetch(h, t + all);
+                if (e.o.x < 0) continue;
+                bool ok;
+                if (t < h.ns) {
+                    const int64_t rd = lu + 8 * (int64_t)e.o.x;
+                    Blk A = w.blk(rd), B = w.blk(rd + 4);
+                    terms(e, h, t, true, [&](const Val& v) {
+                        const Blk Di = binv(v.D, ok);
+                        bmsub(A, v.Wa, bmul(Di, v.Vb));
+                        bmsub(B, v.Wb, bmul(Di, v.Va));
+                    });
+                    w.put(rd, A);
+                    w.put(rd + 4, B);
+                } else {
+                    const int64_t rd = 4 * (int64_t)e.o.x, zd = rhs + 2 * (int64_t)e.o.x;
+                    Blk A = w.blk(rd);
+                    double2 z = make_double2(0.0, 0.0);
+                    if (FWD) z = wr.v2(zd);
+                    terms(e, h, t, false, [&](const Val& v) {
+                        const Blk Di = binv(v.D, ok);
+                        bmsub(A, v.Wa, bmul(Di, v.Va));
+                        if (FWD) {
+                            double y0 = 0.0, y1 = 0.0;
+                            mvadd(y0, y1, Di, v.z.x, v.z.y);
+                            z.x = fma(-v.Wa.a, y0, fma(-v.Wa.b, y1, z.x));
+                            z.y = fma(-v.Wa.c, y0, fma(-v.Wa.d, y1, z.y));
+                        }
+                    });
+                    w.put(rd, A);
+                    if (FWD) wr.put2(zd, z);
+                }
+            }
+            h = hn;
+            cur = fetch(h, me);
+            par.sync();
+        }
+    }
+}
+
+// The rows of the upper levels below the tail normalised, after factor_ops:
+// U_jk = D_j^-1 V_jk, y_j = D_j^-1 z_j and, with STORE_D, D_j^-1; kRowLanes
+// lanes per node (of one wavefront, so that the pivot is read by all of them
+// before it is replaced), nodes first, first + step, ....
+constexpr int kRowLanes = 4;
+template <bool FWD, bool STORE_D>
+__device__ __forceinline__ void upper_rows(const DevSym& S, const View& w, int64_t lu,
+                                           const View& wr, int64_t rhs, int* s_bad, int first,
+                                           int step)
+{
+    const int x1 = S.level_ptr[S.mid_level];
+    const int n = S.level_ptr[S.tail_level] - x1;
+    const int lane = (int)threadIdx.x & (kRowLanes - 1);
+    for (int i = first; i < n; i += step) {
+        const int j = S.u_node[2 * i].x;
+        const int4 b = S.u_node[2 * i + 1];
+        bool ok;
+        const Blk Di = binv(w.blk(4 * (int64_t)j), ok);
+        double2 z = make_double2(0.0, 0.0);
+        if (FWD) z = wr.v2(rhs + 2 * (int64_t)j);
+        for (int t = b.z + lane; t < b.w; t += kRowLanes)
+            w.put(lu + 8 * (int64_t)t + 4, bmul(Di, w.blk(lu + 8 * (int64_t)t + 4)));
+        if (lane == 0) {
+            if (!ok) mark_pivot(s_bad, x1 + i);
+            if (STORE_D) w.put(4 * (int64_t)j, Di);
+            if (FWD) {
+                double y0 = 0.0, y1 = 0.0;
+                mvadd(y0, y1, Di, z.x, z.y);
+                wr.put2(rhs + 2 * (int64_t)j, make_double2(y0, y1));
+            }
+        }
+    }
+}
+
+// The tail of the factorisation and, in a spread launch, the upper levels
+// below it (from mid_level on).
+// Phase A (all threads, no ordering): every diagonal, rhs entry and slot
+//   there takes the updates of descendants below (global memory).
 // Phase B: the levels upward, right-looking: once a level's pivots are
 //   final, every block above that one of its nodes j updates (A_kl -= W_kj
 //   D_j^-1 V_jl, the rhs with the diagonal) is one destination of the level's
@@ -1200,25 +1362,36 @@ __device__ __forceinline__ int clique_slot(int c0, int KC, int a, int b)
 // Phase C: all rows normalised at once (U_jk = D_j^-1 V_jk, y_j); the pivots
 //   stay as they are in LDS.
 // WRITE stores the tail's factors to global memory.
-// With a Spread split, every workgroup of the launch takes a share of phase
-// A and leaves its results in the tail's own places in global memory (the
-// D blocks, rhs entries and slot records of the tail nodes, which nothing
-// else reads until the tail writes them); after a grid barrier workgroup 0
-// loads them into LDS and runs the rest, and the other workgroups return.
+// With a Spread split, all workgroups share phase A for all upper levels, and
+// then factorise those below the tail right-looking in global memory
+// (factor_ops); the values lie in their own places there (D blocks, rhs
+// entries, slot records), where workgroup 0 loads the tail from to run the
+// rest, while the others normalise the rows below it and return.  A level
+// costs one grid barrier and one short chain (an operation's values, the
+// products) where the left-looking sweep walks a node's record, lists, blocks
+// and update pairs: 4.5 against 8-14 us a level (one 10,000-bus case over 32
+// workgroups, 19 levels).  One workgroup alone keeps the left-looking levels:
+// there an operation's 19 scattered 16-byte accesses bound it, and a 2,000-bus
+// batch of 1,024 took 2.41 instead of 1.72 ms.
 template <class SRC, bool FWD, bool WRITE, class P = OneGroup>
-__device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, const View& w,
-                                            int64_t lu, const View& wr, int64_t rhs, int* s_bad,
-                                            const P& par = P{})
+__device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, const View& w,
+                                             int64_t lu, const View& wr, int64_t rhs, int* s_bad,
+                                             const P& par = P{})
 {
     const int K = S.tail_nodes, TS = S.tail_slots;
     const int nT = S.nlev - S.tail_level;
     const TailLds L(S);
-    const int a0 = P::kSpread ? par.rank() * (int)blockDim.x + (int)threadIdx.x : threadIdx.x;
-    const int as = P::kSpread ? par.size() * (int)blockDim.x : blockDim.x;
-    for (int it = a0; it < K + TS; it += as) {
-        if (it < K) {
-            const int4 t0 = S.t_node[3 * it];
-            const int4 t1 = S.t_node[3 * it + 1];
+    const int T = wg_size();
+    // the items: all of the upper levels, or the tail's alone
+    const int x0 = P::kSpread ? 0 : S.level_ptr[S.tail_level] - S.level_ptr[S.mid_level];
+    const int y0 = P::kSpread ? 0 : S.u_slots - TS;
+    const int UN = S.nn - S.level_ptr[S.mid_level] - x0, US = S.u_slots - y0;
+    const int a0 = par.rank() * T + (int)threadIdx.x, as = par.size() * T;
+    for (int it = a0; it < UN + US; it += as) {
+        if (it < UN) {
+            const int4 t0 = S.u_node[2 * (x0 + it)];
+            const int4 t1 = S.u_node[2 * (x0 + it) + 1];
+            const int r1 = P::kSpread ? t1.y : t0.w;
             Blk acc = src.diag(t0.x, t0.y, t0.z);
             double z0 = 0.0, z1 = 0.0;
             if constexpr (FWD) {
@@ -1228,17 +1401,17 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                 z0 = b.x;
                 z1 = b.y;
             }
-            // lower neighbours outside the tail: four per step, their blocks
-            // and y requested together, the next four indices in flight
-            // (entries past the list's end are not loaded)
-            if (t1.y < t1.z) {
+            // lower neighbours below the upper levels: four per step, their
+            // blocks and y requested together, the next four indices in
+            // flight (entries past the list's end are not loaded)
+            if (t1.x < r1) {
                 int2 e[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) e[k] = upd_at(S.t_rl, t1.y + k, t1.z);
-                for (int r = t1.y; r < t1.z; r += 4) {
+                for (int k = 0; k < 4; ++k) e[k] = upd_at(S.u_rl, t1.x + k, r1);
+                for (int r = t1.x; r < r1; r += 4) {
                     int2 nx[4];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) nx[k] = upd_at(S.t_rl, r + 4 + k, t1.z);
+                    for (int k = 0; k < 4; ++k) nx[k] = upd_at(S.u_rl, r + 4 + k, r1);
                     Blk wv[4], uv[4];
                     double2 yi[4];
 #pragma unroll
@@ -1246,7 +1419,7 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                         wv[k] = bzero();
                         uv[k] = bzero();
                         yi[k] = make_double2(0.0, 0.0);
-                        if (r + k < t1.z) {
+                        if (r + k < r1) {
                             wv[k] = w.blk(lu + 8 * (int64_t)e[k].y);
                             uv[k] = w.blk(lu + 8 * (int64_t)e[k].y + 4);
                             if (FWD) yi[k] = wr.v2(rhs + 2 * (int64_t)e[k].x);
@@ -1254,7 +1427,7 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                     }
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        if (r + k < t1.z) {
+                        if (r + k < r1) {
                             bmsub(acc, wv[k], uv[k]);
                             if (FWD) {
                                 z0 = fma(-wv[k].a, yi[k].x, fma(-wv[k].b, yi[k].y, z0));
@@ -1266,34 +1439,39 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                     for (int k = 0; k < 4; ++k) e[k] = nx[k];
                 }
             }
-            if constexpr (P::kSpread) {
-                w.put(4 * (int64_t)t0.x, acc);
-                if (FWD) wr.put2(rhs + 2 * (int64_t)t0.x, make_double2(z0, z1));
-            } else {
+            if constexpr (!P::kSpread) {
                 L.setD(it, acc);
                 L.sety(it, z0, z1);
+            } else {
+                w.put(4 * (int64_t)t0.x, acc);
+                if (FWD) wr.put2(rhs + 2 * (int64_t)t0.x, make_double2(z0, z1));
             }
         } else {
-            const int t = it - K;
-            const int4 a = S.t_slot[3 * t];
-            const int4 b = S.t_slot[3 * t + 1];
-            const int4 c = S.t_slot[3 * t + 2];
+            const int t = it - UN;
+            const int4 a = S.u_slot[2 * (y0 + t)];
+            const int4 b = S.u_slot[2 * (y0 + t) + 1];
             Blk Wk, Vk;
-            src.off(a.x, c.x, a.z, a.w, b.x, Wk, Vk);
-            apply_updates(S.t_upd, b.y, b.z, w, lu, Wk, Vk);
-            if constexpr (P::kSpread) {
-                w.put(lu + 8 * (int64_t)a.x, Wk);
-                w.put(lu + 8 * (int64_t)a.x + 4, Vk);
-            } else {
+            src.off(a.x, a.y, a.z, a.w, b.x, Wk, Vk);
+            apply_updates(S.u_upd, b.y, P::kSpread ? b.z : b.w, w, lu, Wk, Vk);
+            if constexpr (!P::kSpread) {
                 L.setW(t, Wk);
                 L.setU(t, Vk);
+            } else {
+                w.put(lu + 8 * (int64_t)a.x, Wk);
+                w.put(lu + 8 * (int64_t)a.x + 4, Vk);
             }
         }
     }
     if constexpr (P::kSpread) {
         par.sync();
+        factor_ops<FWD>(par, S, w, lu, wr, rhs);
+        const int g0 = K > 0 ? 1 : 0;  // workgroup 0 has the tail to do
+        if (par.rank() >= g0)
+            upper_rows<FWD, WRITE>(S, w, lu, wr, rhs, s_bad,
+                                   ((par.rank() - g0) * T + (int)threadIdx.x) / kRowLanes,
+                                   (par.size() - g0) * T / kRowLanes);
         if (par.rank() != 0) return;
-        for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
+        for (int it = threadIdx.x; it < K + TS; it += T) {
             if (it < K) {
                 const int j = S.t_node[3 * it].x;
                 L.setD(it, w.blk(4 * (int64_t)j));
@@ -1301,13 +1479,14 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
                 L.sety(it, z.x, z.y);
             } else {
                 const int t = it - K;
-                const int64_t sg = lu + 8 * (int64_t)S.t_slot[3 * t].x;
+                const int64_t sg = lu + 8 * (int64_t)S.t_slot[t].x;
                 L.setW(t, w.blk(sg));
                 L.setU(t, w.blk(sg + 4));
             }
         }
     }
     __syncthreads();
+    if (K == 0) return;
     // The terms of a destination from its first operation on.
     auto terms = [&](const uint2& q, const uint2& second, auto&& at2, auto&& term) {
         TailOp e = tail_op(q);
@@ -1405,13 +1584,13 @@ __device__ __forceinline__ void tail_factor(const DevSym& S, const SRC& src, con
             }
         } else {
             const int t = it - K;
-            L.setU(t, bmul(L.Dinv(S.t_slot[3 * t + 2].y), L.U(t)));
+            L.setU(t, bmul(L.Dinv(S.t_slot[t].z), L.U(t)));
         }
     }
     __syncthreads();
     if (WRITE) {
         for (int t = threadIdx.x; t < TS; t += blockDim.x) {
-            const int s = S.t_slot[3 * t].x;
+            const int s = S.t_slot[t].x;
             w.put(lu + 8 * (int64_t)s, L.W(t));
             w.put(lu + 8 * (int64_t)s + 4, L.U(t));
         }
@@ -1485,7 +1664,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
             const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
             double2 y = L.yv(jl);
             for (int t = t1 - 1; t >= t0; --t) {  // the clique's are the last ones
-                const int k = S.t_slot[3 * t].y;
+                const int k = S.t_slot[t].y;
                 if (k < kf) break;
                 const Blk U = L.U(t);
                 const double2 x = L.yv(k);

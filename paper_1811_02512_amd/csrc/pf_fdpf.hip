@@ -167,7 +167,7 @@ struct FdTail {
 __device__ __forceinline__ void fd_tail_load(const DevSym& S, const double* m, const FdTail& t)
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
-    for (int i = threadIdx.x; i < S.tail_slots; i += blockDim.x) t.wu[i] = sl[S.t_slot[3 * i].x];
+    for (int i = threadIdx.x; i < S.tail_slots; i += blockDim.x) t.wu[i] = sl[S.t_slot[i].x];
     for (int i = threadIdx.x; i < S.tail_nodes; i += blockDim.x) t.d[i] = m[S.t_node[3 * i].x];
 }
 
@@ -271,7 +271,7 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
             const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
             double y = sy[jl];
             for (int q = t1 - 1; q >= t0; --q) {
-                const int k = S.t_slot[3 * q].y;
+                const int k = S.t_slot[q].y;
                 if (k < kf) break;
                 y = fma(-t.wu[q].y, sy[k], y);
             }

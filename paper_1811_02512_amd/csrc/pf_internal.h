@@ -35,10 +35,8 @@ namespace pf {
 //     as (i, slot) global pairs in t_rl, [rn1, rt1) lower neighbours inside
 //     the tail as (local i, local slot) pairs in t_rl, those below the
 //     clique first: [rn1, rmid) below, [rmid, rt1) in the clique
-//   t_slot[t] (3 x int4): {s, kl, bus_k, ylo}, {yup, un0, un1, 0},
-//                         {bus_j, jl, 0, 0}
-//     s = global slot, kl = local node of k, [un0, un1) update pairs from
-//     outside the tail (global slots); jl = local node owning the slot
+//   t_slot[t] (int4): {s, kl, jl, 0}
+//     s = global slot, kl = local node of k, jl = local node owning the slot
 //   The clique is the last tail_clique local nodes: a chain of single-node
 //   levels, each adjacent to every node above it (local slot of clique pair
 //   (a, b), a < b, is t_node[a].sl0 + b - a - 1).
@@ -54,6 +52,22 @@ namespace pf {
 //   t_lev[2 l + 1] = {op0, nb, 0, 0}: the backward operations of level l
 //     below the clique: x_d -= U_a x_b for every slot a whose higher
 //     neighbour b is on the level (d owns the slot)
+// Upper levels [mid_level, nlev) of a launch spread over several workgroups:
+// all nodes' diagonals, rhs entries and slots there take the updates of lower
+// levels in one pass; then the levels below the tail (the narrow ones) are
+// factorised right-looking in global memory.  One workgroup alone pulls the
+// tail's updates only, from all levels below it.
+//   u_node[x] (2 x int4, x = level-ordered node - level_ptr[mid_level]):
+//     {j, bus, ydiag, r2}, {r0, r1, s0, s1}: its lower neighbours as (i, slot)
+//     pairs in u_rl, [r0, r1) those below mid_level, [r1, r2) those from there
+//     to the tail; [s0, s1) = its slots
+//   u_slot[t] (2 x int4, slots in the order of their nodes): {s, bus_j, bus_k,
+//     ylo}, {yup, u0, u1, u2}: its update pairs in u_upd, as upd's, [u0, u1)
+//     from below mid_level, [u1, u2) from there to the tail
+//   g_lev[2 i], g_lev[2 i + 1] (level mid_level + i): {op0, ns, nd, 0}, {ns2,
+//     nd2, 0, 0}: its operations g_op = {d, a, b, j}, as t_lev's with global
+//     slots and positions, the slots padded to a wavefront with d = -1 where
+//     diagonals follow; g_next: the offset of a destination's next operation
 struct DevSym {
     int32_t n, m, nn, slack;
     int32_t nnz_y, nnz_l, nlev, pad0;
@@ -93,11 +107,19 @@ struct DevSym {
     int32_t tail_clique;
     int32_t ef_lds;  // bytes of the LDS copy of (e, f) per bus the Newton mismatch reads, 0 = none
     const int4* t_node;      // 3 K
-    const int4* t_slot;      // 3 TS
+    const int4* t_slot;      // TS
     const int2* t_rl;
-    const int2* t_upd;
     const int4* t_lev;       // 2 (nlev - tail_level)
     const uint2* t_op;
+    // upper levels
+    int32_t mid_level, u_slots;  // u_slots: entries of u_slot
+    const int4* u_node;
+    const int4* u_slot;
+    const int2* u_rl;
+    const int2* u_upd;
+    const int4* g_lev;
+    const int4* g_op;
+    const int32_t* g_next;
     // Subtrees below a cut level (the group of workgroups that a spread
     // batch of grids gives a case hands each workgroup whole subtrees there,
     // so those levels need workgroup barriers only; a one-case spread launch
@@ -129,7 +151,10 @@ struct HostSym {
     // tail
     int32_t tail_level = 0, tail_nodes = 0, tail_slots = 0, tail_lds = 0, tail_clique = 0;
     int64_t tail_budget = 64 * 1024;
-    std::vector<int32_t> t_node, t_slot, t_rl, t_upd, t_lev, t_op;
+    std::vector<int32_t> t_node, t_slot, t_rl, t_lev, t_op;
+    // upper levels (DevSym); rebuilt with the tail
+    int32_t mid_level = 0;
+    std::vector<int32_t> u_node, u_slot, u_rl, u_upd, g_lev, g_op, g_next;
     // subtrees below a cut level (DevSym); rebuilt with the tail
     int32_t sub_cut = 0, sub_roots = 0;
     std::vector<int32_t> sub_idx, sub_ptr, sub_cum;
@@ -193,6 +218,10 @@ void default_mapping(HostSym& s);
 // the subtrees below the cut level under it.
 void build_tail(HostSym& s, int64_t budget);
 void build_tail_ops(HostSym& s);
+// The upper levels' lists: in a spread launch, the highest levels below the
+// tail of at most kMidWidth nodes are factorised right-looking.
+constexpr int kMidWidth = 600;
+void build_upper(HostSym& s);
 // Subtrees of the levels below the tail for spread launches: the highest cut
 // at or below the tail level with at least kSubMinRoots roots (none if no
 // such level).

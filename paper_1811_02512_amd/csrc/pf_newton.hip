@@ -92,6 +92,12 @@ __device__ __forceinline__ void newton_case(const P& par, const DevSym& S, const
                             : nullptr;
     const EFView ef{wb, o.BUS};
     const bool tail = S.tail_nodes > 0;
+    // the left-looking levels; above them upper_factor
+    const int ltop = P::kSpread ? S.mid_level : S.tail_level;
+    const bool upper = ltop < S.nlev;
+    // levels that a workgroup of a group in a batch of grids factorises on its
+    // own subtrees
+    const int subs = S.sub_cut < S.mid_level ? S.sub_cut : S.mid_level;
     int it = 0, st = ST_NOT_CONVERGED;
     double nrm = 0.0;
     for (;;) {
@@ -161,15 +167,15 @@ __device__ __forceinline__ void newton_case(const P& par, const DevSym& S, const
         };
         int lc = 0;  // first level shared among the workgroups
         if constexpr (P::kSub) {
-            if (S.sub_cut > 0) {
-                for_sub_levels(S, k0, k1, 0, S.sub_cut, true, fwd);
+            if (subs > 0) {
+                for_sub_levels(S, k0, k1, 0, subs, true, fwd);
                 par.sync();
-                lc = S.sub_cut;
+                lc = subs;
             }
         }
-        for_nodes(par, S, lc, S.tail_level, true, fwd);
-        if (tail) {
-            tail_factor<SrcState, true, false>(S, src, w, o.LU, wb, o.RHS, bad, par);
+        for_nodes(par, S, lc, ltop, true, fwd);
+        if (upper) {
+            upper_factor<SrcState, true, false>(S, src, w, o.LU, wb, o.RHS, bad, par);
             tail_done();
         }
         if (marker() != kNoPivot) {
@@ -206,15 +212,15 @@ __device__ __forceinline__ void newton_case(const P& par, const DevSym& S, const
         };
         int lc = 0;
         if constexpr (P::kSub) {
-            if (S.sub_cut > 0) {
-                for_sub_levels(S, k0, k1, 0, S.sub_cut, true, keep);
+            if (subs > 0) {
+                for_sub_levels(S, k0, k1, 0, subs, true, keep);
                 par.sync();
-                lc = S.sub_cut;
+                lc = subs;
             }
         }
-        for_nodes(par, S, lc, S.tail_level, true, keep);
-        if (tail) {
-            tail_factor<SrcState, false, true>(S, src, w, o.LU, wb, o.RHS, bad, par);
+        for_nodes(par, S, lc, ltop, true, keep);
+        if (upper) {
+            upper_factor<SrcState, false, true>(S, src, w, o.LU, wb, o.RHS, bad, par);
             tail_done();
         }
         if (marker() != kNoPivot) st = ST_ZERO_PIVOT;
@@ -418,7 +424,7 @@ __global__ __launch_bounds__(kLevelThreads) void k_factor(DevSym S, double* vals
     for_nodes(S, 0, S.tail_level, true, [&](int x, const NodeRec& r, int lane, int g) {
         factor_node<SrcLoadT<SYM>, false, true, SYM>(S, src, x, r, lane, g, w, lu, w, 0, &s_bad);
     });
-    if (S.tail_nodes > 0) tail_factor<SrcLoadT<SYM>, false, true>(S, src, w, lu, w, 0, &s_bad);
+    if (S.tail_nodes > 0) upper_factor<SrcLoadT<SYM>, false, true>(S, src, w, lu, w, 0, &s_bad);
     __syncthreads();
     if (threadIdx.x == 0) {
         if (status) status[c] = s_bad != kNoPivot ? ST_ZERO_PIVOT : ST_OK;
@@ -598,7 +604,7 @@ __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
                 for (int r = t1.z + lane; r < rmid; r += g) {  // the tail below the clique
                     const int2 e = S.t_rl[r];
                     const int i = S.t_node[3 * e.x].x;
-                    const int sl = S.t_slot[3 * e.y].x;
+                    const int sl = S.t_slot[e.y].x;
                     const double2 p = x2[i];
                     madd(z0, z1, w.blk(lu + 8 * (int64_t)sl + kUp), p.x, p.y);
                 }
