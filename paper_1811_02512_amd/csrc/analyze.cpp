@@ -10,6 +10,7 @@
 // position <-> bus maps, Y entry of every filled block, lower-neighbour lists
 // and the per-destination update pairs of the left-looking factorisation.
 #include <algorithm>
+#include <cstdint>
 #include <cstring>
 #include <queue>
 #include <utility>
@@ -58,6 +59,7 @@ struct LevelTerms {
     };
     std::vector<Term> terms;
     std::vector<int32_t> dst, third, count, at, seq;
+    std::vector<uint64_t> keys;
     int32_t slots = 0;
     // ns: slots (padded), nd: slots and diagonals, total: all positions
     int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0, total = 0;
@@ -98,12 +100,14 @@ struct LevelTerms {
     template <class F>
     void place(int32_t pad, F&& fn)
     {
-        std::sort(dst.begin(), dst.end(), [&](int32_t u, int32_t v) {
-            if ((u < slots) != (v < slots)) return u < slots;
-            if (count[u] != count[v]) return count[u] > count[v];
-            return u < v;
-        });
+        // slots first, then many terms first, then by destination, as one key
         const int32_t n = (int32_t)dst.size();
+        keys.resize(n);
+        for (int32_t i = 0; i < n; ++i)
+            keys[i] = (uint64_t)(dst[i] >= slots) << 63 |
+                      (uint64_t)(INT32_MAX - count[dst[i]]) << 32 | (uint32_t)dst[i];
+        std::sort(keys.begin(), keys.end());
+        for (int32_t i = 0; i < n; ++i) dst[i] = (int32_t)(uint32_t)keys[i];
         int32_t real = 0;
         ns2 = nd2 = 0;
         for (int32_t d : dst) {
@@ -184,13 +188,23 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
     s.from.assign(from, from + m);
     s.to.assign(to, to + m);
 
-    // incidence: (other bus, branch) per bus, sorted
-    std::vector<std::vector<std::pair<int32_t, int32_t>>> inc(n);
+    // incidence: (other bus, branch) per bus, sorted: inc[ip[i] .. ip[i + 1])
+    using Inc = std::pair<int32_t, int32_t>;
+    std::vector<int32_t> ip(n + 1, 0);
     for (int e = 0; e < m; ++e) {
-        inc[from[e]].push_back({to[e], e});
-        inc[to[e]].push_back({from[e], e});
+        ++ip[from[e] + 1];
+        ++ip[to[e] + 1];
     }
-    for (auto& v : inc) std::sort(v.begin(), v.end());
+    for (int i = 0; i < n; ++i) ip[i + 1] += ip[i];
+    std::vector<Inc> inc(2 * (size_t)m);
+    {
+        std::vector<int32_t> cur(ip.begin(), ip.end() - 1);
+        for (int e = 0; e < m; ++e) {
+            inc[cur[from[e]]++] = {to[e], e};
+            inc[cur[to[e]]++] = {from[e], e};
+        }
+    }
+    for (int i = 0; i < n; ++i) std::sort(inc.begin() + ip[i], inc.begin() + ip[i + 1]);
 
     // every bus must reach the slack
     {
@@ -201,11 +215,11 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
         while (!stack.empty()) {
             int v = stack.back();
             stack.pop_back();
-            for (auto& pe : inc[v])
-                if (!seen[pe.first]) {
-                    seen[pe.first] = 1;
+            for (int q = ip[v]; q < ip[v + 1]; ++q)
+                if (!seen[inc[q].first]) {
+                    seen[inc[q].first] = 1;
                     ++cnt;
-                    stack.push_back(pe.first);
+                    stack.push_back(inc[q].first);
                 }
         }
         if (cnt != n) {
@@ -214,36 +228,35 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
         }
     }
 
-    // admittance CSR (diagonal always present) and contributing branches
+    // admittance CSR (diagonal always present) and contributing branches, both
+    // ascending
     s.yptr.assign(n + 1, 0);
+    s.ycol.reserve(n + 2 * (size_t)m);
+    s.ybr.reserve(4 * (size_t)m);
+    s.ybr_ptr.reserve(n + 2 * (size_t)m + 1);
     s.ybr_ptr.push_back(0);
     for (int i = 0; i < n; ++i) {
-        std::vector<int32_t> cols;
-        cols.push_back(i);
-        for (auto& pe : inc[i]) cols.push_back(pe.first);
-        std::sort(cols.begin(), cols.end());
-        cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
-        for (int32_t c : cols) {
-            s.ycol.push_back(c);
-            if (c == i) {
-                std::vector<int32_t> br;
-                for (auto& pe : inc[i]) br.push_back(pe.second);
-                std::sort(br.begin(), br.end());
-                s.ybr.insert(s.ybr.end(), br.begin(), br.end());
-            } else {
-                for (auto& pe : inc[i])
-                    if (pe.first == c) s.ybr.push_back(pe.second);  // ascending branch id
+        auto diagonal = [&]() {
+            s.ycol.push_back(i);
+            const size_t b0 = s.ybr.size();
+            for (int q = ip[i]; q < ip[i + 1]; ++q) s.ybr.push_back(inc[q].second);
+            std::sort(s.ybr.begin() + b0, s.ybr.end());
+            s.ybr_ptr.push_back((int32_t)s.ybr.size());
+        };
+        bool done = false;
+        for (int q = ip[i]; q < ip[i + 1];) {
+            const int32_t c = inc[q].first;
+            if (c > i && !done) {
+                diagonal();
+                done = true;
             }
+            s.ycol.push_back(c);
+            for (; q < ip[i + 1] && inc[q].first == c; ++q) s.ybr.push_back(inc[q].second);
             s.ybr_ptr.push_back((int32_t)s.ybr.size());
         }
+        if (!done) diagonal();
         s.yptr[i + 1] = (int32_t)s.ycol.size();
     }
-    auto yfind = [&](int32_t row, int32_t col) -> int32_t {
-        auto b = s.ycol.begin() + s.yptr[row], e = s.ycol.begin() + s.yptr[row + 1];
-        auto it = std::lower_bound(b, e, col);
-        return (it != e && *it == col) ? (int32_t)(it - s.ycol.begin()) : -1;
-    };
-
     // reduced graph: node v <-> bus, ascending bus order without the slack
     const int nn = s.nn;
     std::vector<int32_t> bus_of(nn), node_of(n, -1);
@@ -254,13 +267,12 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
         }
     std::vector<std::vector<int32_t>> adj(nn);
     for (int v = 0; v < nn; ++v) {
-        int i = bus_of[v];
-        for (auto& pe : inc[i]) {
-            int w = node_of[pe.first];
-            if (w >= 0) adj[v].push_back(w);
+        const int i = bus_of[v];  // its row's columns ascend, and so do their nodes
+        adj[v].reserve(s.yptr[i + 1] - s.yptr[i]);
+        for (int q = s.yptr[i]; q < s.yptr[i + 1]; ++q) {
+            const int w = node_of[s.ycol[q]];
+            if (w >= 0 && w != v) adj[v].push_back(w);
         }
-        std::sort(adj[v].begin(), adj[v].end());
-        adj[v].erase(std::unique(adj[v].begin(), adj[v].end()), adj[v].end());
     }
 
     // symbolic elimination: minimum degree (ties to the lowest node, i.e.
@@ -290,14 +302,13 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
             }
             order[step] = p;
             gone[p] = 1;
-            hi[p] = adj[p];
+            hi[p] = std::move(adj[p]);
+            adj[p].clear();
             for (int32_t a : hi[p]) {
                 merge_without(adj[a], hi[p], a, p, tmp);
                 adj[a].swap(tmp);
                 if (ordering == PF_ORDER_MINDEG) heap.push({(int32_t)adj[a].size(), a});
             }
-            adj[p].clear();
-            adj[p].shrink_to_fit();
         }
     }
 
@@ -312,14 +323,16 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
     }
     s.Lp.assign(nn + 1, 0);
     for (int p = 0; p < nn; ++p) {
-        std::vector<int32_t> sp;
-        for (int32_t v : hi[order[p]]) sp.push_back(pos_of_node[v]);
-        std::sort(sp.begin(), sp.end());
-        s.Li.insert(s.Li.end(), sp.begin(), sp.end());
+        const size_t b0 = s.Li.size();
+        for (int32_t v : hi[order[p]]) s.Li.push_back(pos_of_node[v]);
+        std::sort(s.Li.begin() + b0, s.Li.end());
         s.Lp[p + 1] = (int32_t)s.Li.size();
     }
     hi.clear();
     const int64_t nnzl = (int64_t)s.Li.size();
+    s.owner.resize(nnzl);
+    for (int p = 0; p < nn; ++p)
+        for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) s.owner[q] = p;
 
     // elimination tree and levels (level = 1 + highest child level)
     s.parent.assign(nn, -1);
@@ -343,17 +356,26 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
     for (int l = 0; l < nlev; ++l)
         s.max_width = std::max(s.max_width, s.level_ptr[l + 1] - s.level_ptr[l]);
 
-    // admittance entries of every block
+    // admittance entries of every block: at[] marks where the columns of p's
+    // row stand; rows ascend, so the entries of a column come in its own
+    // row's order and cur[] finds the transposed entry
     s.ydiag.resize(nn);
     s.ylo.resize(nnzl);
     s.yup.resize(nnzl);
-    for (int p = 0; p < nn; ++p) {
-        int bp = s.perm[p];
-        s.ydiag[p] = yfind(bp, bp);
-        for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) {
-            int bk = s.perm[s.Li[q]];
-            s.ylo[q] = yfind(bk, bp);
-            s.yup[q] = yfind(bp, bk);
+    {
+        std::vector<int32_t> cur(s.yptr.begin(), s.yptr.end() - 1), transposed(s.ycol.size()), at(n, -1);
+        for (int i = 0; i < n; ++i)
+            for (int q = s.yptr[i]; q < s.yptr[i + 1]; ++q) transposed[q] = cur[s.ycol[q]]++;
+        for (int p = 0; p < nn; ++p) {
+            const int bp = s.perm[p];
+            for (int q = s.yptr[bp]; q < s.yptr[bp + 1]; ++q) at[s.ycol[q]] = q;
+            s.ydiag[p] = at[bp];
+            for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) {
+                const int32_t u = at[s.perm[s.Li[q]]];
+                s.yup[q] = u;
+                s.ylo[q] = u < 0 ? -1 : transposed[u];
+            }
+            for (int q = s.yptr[bp]; q < s.yptr[bp + 1]; ++q) at[s.ycol[q]] = -1;
         }
     }
 
@@ -379,35 +401,34 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
     // neighbours of a node form a clique in the filled graph); the block
     // pair at a = slot(i;k) updates destination slot(j;k).
     s.Up.assign(nnzl + 1, 0);
-    for (int pass = 0; pass < 2; ++pass) {
-        std::vector<int32_t> cur;
-        if (pass == 1) {
-            for (int64_t q = 0; q < nnzl; ++q) s.Up[q + 1] += s.Up[q];
-            s.Ua.resize(s.Up[nnzl]);
-            s.Ub.resize(s.Up[nnzl]);
-            cur.assign(s.Up.begin(), s.Up.end() - 1);
-        }
-        for (int j = 0; j < nn; ++j) {
+    {
+        std::vector<int32_t> dst;  // destination slots, in the walk's order
+        dst.reserve(8 * (size_t)nnzl);
+        for (int j = 0; j < nn; ++j)
             for (int r = s.Rp[j]; r < s.Rp[j + 1]; ++r) {
-                int i = s.Ri[r], b = s.Rs[r];
                 int d = s.Lp[j];
-                for (int a = b + 1; a < s.Lp[i + 1]; ++a) {
-                    int k = s.Li[a];
+                for (int a = s.Rs[r] + 1; a < s.Lp[s.Ri[r] + 1]; ++a) {
+                    const int k = s.Li[a];
                     while (d < s.Lp[j + 1] && s.Li[d] < k) ++d;
                     if (d >= s.Lp[j + 1] || s.Li[d] != k) {
                         msg = "pf_analyze: internal error, filled pattern is not closed";
                         return PF_E_INVALID;
                     }
-                    if (pass == 0) {
-                        s.Up[d + 1]++;
-                    } else {
-                        s.Ua[cur[d]] = a;
-                        s.Ub[cur[d]] = b;
-                        cur[d]++;
-                    }
+                    s.Up[d + 1]++;
+                    dst.push_back(d);
                 }
             }
-        }
+        for (int64_t q = 0; q < nnzl; ++q) s.Up[q + 1] += s.Up[q];
+        s.Ua.resize(s.Up[nnzl]);
+        s.Ub.resize(s.Up[nnzl]);
+        std::vector<int32_t> cur(s.Up.begin(), s.Up.end() - 1);
+        size_t u = 0;
+        for (int64_t r = 0; r < nnzl; ++r)
+            for (int a = s.Rs[r] + 1; a < s.Lp[s.Ri[r] + 1]; ++a) {
+                const int32_t x = cur[dst[u++]]++;
+                s.Ua[x] = a;
+                s.Ub[x] = s.Rs[r];
+            }
     }
 
     // packed records (layouts documented with DevSym)
@@ -576,37 +597,50 @@ void build_upper(HostSym& s)
     for (auto* v : {&s.u_node, &s.u_slot, &s.u_rl, &s.u_upd, &s.g_lev, &s.g_op, &s.g_next})
         v->clear();
     const int x1 = s.level_ptr[M];  // first node (level order) of the upper levels
-    std::vector<int32_t> owner(s.Li.size());
-    for (int p = 0; p < s.nn; ++p)
-        for (int q = s.Lp[p]; q < s.Lp[p + 1]; ++q) owner[q] = p;
     // part 0: below the upper levels; part 1: the upper levels below the tail
     auto part = [&](int p) { return s.level[p] <= M ? 0 : s.level[p] <= s.tail_level ? 1 : 2; };
+    s.u_node.reserve(8 * (size_t)(s.nn - x1));
+    s.u_slot.reserve(8 * s.Li.size());
+    s.u_rl.reserve(2 * s.Li.size());
+    s.u_upd.reserve(2 * s.Ua.size());
+    std::vector<int32_t> rest;  // part 1 of a list, appended to its part 0
+    auto close = [&](std::vector<int32_t>& list) {
+        const int32_t mid = (int32_t)(list.size() / 2);
+        list.insert(list.end(), rest.begin(), rest.end());
+        rest.clear();
+        return mid;
+    };
     for (int x = x1; x < s.nn; ++x) {
         const int j = s.level_nodes[x];
-        int32_t r[3] = {(int32_t)(s.u_rl.size() / 2), 0, 0};
-        for (int k = 0; k < 2; ++k) {
-            for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q)
-                if (part(s.Ri[q]) == k) {
-                    s.u_rl.push_back(s.Ri[q]);
-                    s.u_rl.push_back(s.Rs[q]);
-                }
-            r[k + 1] = (int32_t)(s.u_rl.size() / 2);
+        const int32_t r0 = (int32_t)(s.u_rl.size() / 2);
+        for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q) {
+            const int k = part(s.Ri[q]);
+            if (k > 1) continue;
+            auto& list = k ? rest : s.u_rl;
+            list.push_back(s.Ri[q]);
+            list.push_back(s.Rs[q]);
         }
-        s.u_node.insert(s.u_node.end(),
-                        {j, s.perm[j], s.ydiag[j], r[2], r[0], r[1], s.Lp[j], s.Lp[j + 1]});
+        const int32_t r1 = close(s.u_rl);
+        s.u_node.insert(s.u_node.end(), {j, s.perm[j], s.ydiag[j], (int32_t)(s.u_rl.size() / 2),
+                                         r0, r1, s.Lp[j], s.Lp[j + 1]});
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) {
-            int32_t u[3] = {(int32_t)(s.u_upd.size() / 2), 0, 0};
-            for (int k = 0; k < 2; ++k) {
-                for (int v = s.Up[q]; v < s.Up[q + 1]; ++v)
-                    if (part(owner[s.Ub[v]]) == k) {
-                        s.u_upd.push_back(s.Ua[v]);
-                        s.u_upd.push_back(s.Ub[v]);
-                    }
-                u[k + 1] = (int32_t)(s.u_upd.size() / 2);
+            const int32_t u0 = (int32_t)(s.u_upd.size() / 2);
+            for (int v = s.Up[q]; v < s.Up[q + 1]; ++v) {
+                const int k = part(s.owner[s.Ub[v]]);
+                if (k > 1) continue;
+                auto& list = k ? rest : s.u_upd;
+                list.push_back(s.Ua[v]);
+                list.push_back(s.Ub[v]);
             }
+            const int32_t u1 = close(s.u_upd);
             s.u_slot.insert(s.u_slot.end(), {q, s.perm[j], s.perm[s.Li[q]], s.ylo[q], s.yup[q],
-                                             u[0], u[1], u[2]});
+                                             u0, u1, (int32_t)(s.u_upd.size() / 2)});
         }
+    }
+    if (M >= s.tail_level) {  // no level between
+        s.g_op.assign(4, -1);
+        s.g_next.assign(1, 0);
+        return;
     }
     LevelTerms lt((int32_t)s.Li.size(), s.nn);
     for (int l = M; l < s.tail_level && l < nlev; ++l) {

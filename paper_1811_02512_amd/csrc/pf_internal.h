@@ -144,6 +144,7 @@ struct HostSym {
     std::vector<int32_t> yptr, ycol, ybr_ptr, ybr;
     std::vector<int32_t> perm, pos, parent, level;
     std::vector<int32_t> Lp, Li, ylo, yup, ydiag;
+    std::vector<int32_t> owner;  // position that owns each slot
     std::vector<int32_t> Rp, Ri, Rs;
     std::vector<int32_t> Up, Ua, Ub;
     std::vector<int32_t> level_ptr, level_nodes, level_g;
