@@ -87,6 +87,23 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// threadIdx.x as a value the compiler takes for a new one at each call: what
+// it derives from it (the addresses of a pass) is computed in that pass and
+// not kept in registers through the whole iteration.
+__device__ __forceinline__ int fresh_thread()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The value of lane q of the wavefront, whose lanes all run here.
+__device__ __forceinline__ double lane_value(double v, int q)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), q),
+                            __builtin_amdgcn_readlane(__double2loint(v), q));
+}
+
 // One case's doubles inside an interleaved group of C cases: element d
 // lives at base + (d / K) * K C + K (case % C) + d % K, i.e. chunks of K
 // doubles of the C cases alternate.  The filled values use K = 8 (a slot
@@ -1644,7 +1661,27 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
     const int kf = K - KC;
     if (KC > 0) {
         const int c0 = S.t_node[3 * kf].w;
-        if (threadIdx.x < kWave) {
+        if (KC <= kWave) {
+            if (threadIdx.x < kWave) {
+                const int k = threadIdx.x;
+                double2 y = make_double2(0.0, 0.0);
+                if (k < KC) y = L.yv(kf + k);
+                auto column = [&](int a) {
+                    return k < a ? L.U(clique_slot(c0, KC, k, a)) : bzero();
+                };
+                Blk U = column(KC - 1);
+                for (int a = KC - 1; a > 0; --a) {
+                    const Blk next = column(a - 1);
+                    const double x0 = lane_value(y.x, a), x1 = lane_value(y.y, a);
+                    if (k < a) {
+                        y.x = fma(-U.a, x0, fma(-U.b, x1, y.x));
+                        y.y = fma(-U.c, x0, fma(-U.d, x1, y.y));
+                    }
+                    U = next;
+                }
+                if (k < KC) L.sety(kf + k, y.x, y.y);
+            }
+        } else if (threadIdx.x < kWave) {
             for (int a = KC - 1; a > 0; --a) {
                 const int ja = kf + a;
                 const double2 x = L.yv(ja);
@@ -1663,13 +1700,21 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
             const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
             double2 y = L.yv(jl);
-            for (int t = t1 - 1; t >= t0; --t) {  // the clique's are the last ones
-                const int k = S.t_slot[t].y;
-                if (k < kf) break;
-                const Blk U = L.U(t);
-                const double2 x = L.yv(k);
-                y.x = fma(-U.a, x.x, fma(-U.b, x.y, y.x));
-                y.y = fma(-U.c, x.x, fma(-U.d, x.y, y.y));
+            bool more = true;
+            for (int t = t1 - 1; more && t >= t0; t -= 4) {  // the clique's are the last ones
+                int kk[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kk[i] = S.t_slot[t - i >= t0 ? t - i : t0].y;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    more = more && t - i >= t0 && kk[i] >= kf;
+                    if (more) {
+                        const Blk U = L.U(t - i);
+                        const double2 x = L.yv(kk[i]);
+                        y.x = fma(-U.a, x.x, fma(-U.b, x.y, y.x));
+                        y.y = fma(-U.c, x.x, fma(-U.d, x.y, y.y));
+                    }
+                }
             }
             L.sety(jl, y.x, y.y);
         }
@@ -1865,19 +1910,43 @@ struct CaseDesc {
     int32_t spread, back_lo;
 };
 
+// What the mismatch pass does with a bus's P, Q, F_P, F_Q: Newton stores all
+// four in the second half of the bus record, in one store ...
+struct MisNewton {
+    const View& wb;
+    int64_t bus_off;
+    __device__ __forceinline__ double scale(int) const { return 1.0; }
+    __device__ __forceinline__ void put(int i, int, double, double p, double q, double fp,
+                                        double fq) const
+    {
+        wb.put(bus_off + 8 * (int64_t)i + 4, {p, q, fp, fq});
+    }
+};
+// ... the fast decoupled iteration the right-hand side of its next half step,
+// F_P / |V| or (second) F_Q / |V|, by position.
+struct MisHalf {
+    const double* vm;
+    double* b;
+    bool second;
+    __device__ __forceinline__ double scale(int i) const { return vm[i]; }
+    __device__ __forceinline__ void put(int, int pos, double v, double, double, double fp,
+                                        double fq) const
+    {
+        b[pos] = (second ? fq : fp) / v;
+    }
+};
+
 // Mismatch pass of one case: F = calculated - scheduled (F_Q = 0 at PV buses)
-// and P + jQ.  Without SCALE (Newton) P, Q, F_P, F_Q go into the second half
-// of the bus record in one store; with SCALE (the fast decoupled right-hand
-// sides) P, Q into the record and F / |V| into the rhs in position order.  The thread's max
-// |F| and NaN flag accumulate into mx and nan.  Buses are taken in bus
+// and P + jQ, into out.  The thread's max |F| and NaN flag accumulate into mx
+// and nan.  Buses are taken in bus
 // order, NB per thread per step (blockDim apart), so that the admittance
 // rows, row pointers, positions and scheduled injections of a wavefront are
 // adjacent in memory; all loads of a step's buses are issued before any of
 // them is summed.  The buses are first, first + stride, ... (the thread's
 // index and count over the workgroups that share the case).
-template <bool SCALE, class EF, int NB = 2>
+template <int NB, class EF, class OUT>
 __device__ __forceinline__ void mismatch_pass(const DevSym& S, const double* yv, const EF& ef,
-                                              const View& wb, const Off& o, const PvMask& pvm,
+                                              const OUT& out, const PvMask& pvm,
                                               const double* Psp, const double* Qsp, double& mx,
                                               int& nan, int first, int stride)
 {
@@ -1885,7 +1954,7 @@ __device__ __forceinline__ void mismatch_pass(const DevSym& S, const double* yv,
     for (int i0 = first; i0 < S.n; i0 += NB * bd) {
         int ib[NB], pc[NB], q0[NB], q1[NB];
         bool has[NB], pv[NB];
-        double sp[NB], sq[NB];
+        double sp[NB], sq[NB], sc[NB];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             has[k] = i0 + k * bd < S.n;
@@ -1895,16 +1964,12 @@ __device__ __forceinline__ void mismatch_pass(const DevSym& S, const double* yv,
             q1[k] = S.yptr[ib[k] + 1];
             sp[k] = Psp[ib[k]];
             sq[k] = Qsp[ib[k]];
+            sc[k] = out.scale(ib[k]);
         }
-        Blk v[NB];  // e, f, |V| (|V| only with SCALE)
+        double ve[NB], vf[NB];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-            if (SCALE) {
-                v[k] = wb.blk(o.BUS + 8 * (int64_t)ib[k]);
-            } else {
-                ef.get(ib[k], v[k].a, v[k].b);
-                v[k].c = 1.0;
-            }
+            ef.get(ib[k], ve[k], vf[k]);
             pv[k] = pvm(ib[k]);
         }
         int kk[NB][4];
@@ -1916,31 +1981,15 @@ __device__ __forceinline__ void mismatch_pass(const DevSym& S, const double* yv,
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             double p, q;
-            row_finish(S, yv, ef, q0[k], q1[k], h[k], v[k].a, v[k].b, p, q);
+            row_finish(S, yv, ef, q0[k], q1[k], h[k], ve[k], vf[k], p, q);
             if (has[k] && pc[k] >= 0) {  // the slack is not a position
-                const int64_t rc = o.BUS + 8 * (int64_t)ib[k];
                 const double fp = p - sp[k], fq = pv[k] ? 0.0 : q - sq[k];
-                if (SCALE) {
-                    wb.put2(rc + 4, make_double2(p, q));
-                    wb.put2(o.RHS + 2 * (int64_t)pc[k], make_double2(fp / v[k].c, fq / v[k].c));
-                } else {  // P, Q and the Newton rhs F in one store of the bus record
-                    wb.put(rc + 4, {p, q, fp, fq});
-                }
+                out.put(ib[k], pc[k], sc[k], p, q, fp, fq);
                 nan |= (fp != fp) | (fq != fq);
                 mx = fmax(mx, fmax(fabs(fp), fabs(fq)));
             }
         }
     }
-}
-
-template <bool SCALE, class EF, int NB = 2>
-__device__ __forceinline__ void mismatch_pass(const DevSym& S, const double* yv, const EF& ef,
-                                              const View& wb, const Off& o, const PvMask& pvm,
-                                              const double* Psp, const double* Qsp, double& mx,
-                                              int& nan)
-{
-    mismatch_pass<SCALE, EF, NB>(S, yv, ef, wb, o, pvm, Psp, Qsp, mx, nan, (int)threadIdx.x,
-                                 (int)blockDim.x);
 }
 
 }  // namespace

@@ -85,23 +85,15 @@ __device__ __forceinline__ void fd_factor_node(const DevSym& S, const NodeRec& r
 //   y_j = (1/d_j) (b_j - sum_{i in R(j)} w_ji y_i), levels [0, l1) upward.
 // Four entries per lane per batch with the next batch's indices in flight;
 // the node's own b_j and 1/d_j are requested first.
-// The work vector of a half step: with VL in LDS by position (xv), else the
-// rhs component comp in the bus view.  The right-hand side b itself always
-// comes from the rhs (the mismatch pass writes it there).
-template <bool VL>
-__device__ __forceinline__ double& fd_x(double* xv, const View& wb, int64_t rhs, int comp, int p)
-{
-    return VL ? xv[p] : *wb.at(rhs + 2 * (int64_t)p + comp);
-}
-
-template <bool VL>
-__device__ __forceinline__ void fd_forward(const DevSym& S, const double* m, const View& wb,
-                                           int64_t rhs, int comp, int l1, double* xv)
+// b holds the right-hand side and x the half step's work vector, both by
+// position.
+__device__ __forceinline__ void fd_forward(const DevSym& S, const double* m, const double* b,
+                                           double* x, int l1)
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
     for_nodes(S, 0, l1, true, [&](int, const NodeRec& rec, int lane, int g) {
         const int j = rec.a.x, r1 = rec.a.w;
-        const double bj = *wb.at(rhs + 2 * (int64_t)j + comp);
+        const double bj = b[j];
         const double dj = m[j];
         int r = rec.a.z + lane;
         // absent entries are not loaded (skipped when no lane needs them)
@@ -120,7 +112,7 @@ __device__ __forceinline__ void fd_forward(const DevSym& S, const double* m, con
                 y[k] = 0.0;
                 if (r + k * g < r1) {
                     w[k] = sl[e[k].y].x;
-                    y[k] = fd_x<VL>(xv, wb, rhs, comp, e[k].x);
+                    y[k] = x[e[k].x];
                 }
             }
             const int rn = r + 4 * g;
@@ -132,29 +124,73 @@ __device__ __forceinline__ void fd_forward(const DevSym& S, const double* m, con
                 if (r + k * g < r1) z = fma(w[k], y[k], z);
         }
         if (g > 1) z = gsum(z, g);
-        if (lane == 0) fd_x<VL>(xv, wb, rhs, comp, j) = dj * (bj - z);
+        if (lane == 0) x[j] = dj * (bj - z);
     });
 }
 
-// The half step at a bus: ANGLE: theta -= x; else |V| -= x at PQ buses.
-template <bool ANGLE>
-__device__ __forceinline__ void fd_half_step_to(const View& wb, int64_t br, const Blk& v, int bus,
-                                                const PvMask& pv, double x)
-{
-    double vm = v.c, va = v.d;
-    if (ANGLE) va -= x;
-    else if (!pv(bus)) vm -= x;
-    double sn, cs;
-    sincos(va, &sn, &cs);
-    wb.put(br, {vm * cs, vm * sn, vm, va});
-}
+// State of one case.  |V| and theta are updated in the caller's arrays; the
+// workspace keeps (cos, sin) of theta per bus (the magnitude half step leaves
+// them as they are) and (e, f) for the mismatch pass, which is copied to or
+// made in LDS when it has room there.
+struct FdState {
+    double* Vm;
+    double* Va;
+    double2* cs;
+    double2* ef;
+};
 
-template <bool ANGLE>
-__device__ __forceinline__ void fd_half_step(const View& wb, int64_t bus_off, int bus,
-                                             const PvMask& pv, double x)
+// The half step of every bus from the solution x by position: theta -= x
+// (ANGLE), else |V| -= x at PQ buses.  In bus order, as every array but x is
+// then read and written contiguously (done with each node's substitution
+// instead it put a bus record's load, the sine and the store at the end of
+// every level).  The next bus's loads are in flight under the sine: taking
+// several buses at once instead needs more registers than two workgroups per
+// compute unit leave.
+template <bool ANGLE, class E>
+__device__ __forceinline__ void fd_half_step(const DevSym& S, const FdState& st,
+                                             const PvMask& pv, const double* x, E&& put_ef)
 {
-    const int64_t br = bus_off + 8 * (int64_t)bus;
-    fd_half_step_to<ANGLE>(wb, br, wb.blk(br), bus, pv, x);
+    struct Bus {
+        double vm, x;
+        double2 t;  // theta, or (cos, sin)
+    };
+    const int T = wg_size(), n = S.n;
+    auto load = [&](int i, int p) {
+        Bus b{0.0, 0.0, make_double2(0.0, 0.0)};
+        if (i < n) {
+            b.vm = st.Vm[i];
+            if (ANGLE) b.t.x = st.Va[i];
+            else b.t = st.cs[i];
+            if (p >= 0) b.x = x[p];
+        }
+        return b;
+    };
+    int i = fresh_thread();
+    int p = i < n ? S.pos[i] : -1, pn = i + T < n ? S.pos[i + T] : -1;
+    Bus b = load(i, p);
+    while (i < n) {
+        const int p2 = i + 2 * T < n ? S.pos[i + 2 * T] : -1;
+        const Bus next = load(i + T, pn);
+        double vm = b.vm;
+        double2 cs = b.t;
+        if (ANGLE) {
+            double va = b.t.x;
+            if (p >= 0) {  // the slack keeps its voltage
+                va -= b.x;
+                st.Va[i] = va;
+            }
+            sincos(va, &cs.y, &cs.x);
+            st.cs[i] = cs;
+        } else if (p >= 0 && !pv(i)) {
+            vm -= b.x;
+            st.Vm[i] = vm;
+        }
+        put_ef(i, make_double2(vm * cs.x, vm * cs.y));
+        i += T;
+        p = pn;
+        pn = p2;
+        b = next;
+    }
 }
 
 // The top of the tree (the LDS tail's levels) of a factored matrix, copied
@@ -171,19 +207,17 @@ __device__ __forceinline__ void fd_tail_load(const DevSym& S, const double* m, c
     for (int i = threadIdx.x; i < S.tail_nodes; i += blockDim.x) t.d[i] = m[S.t_node[3 * i].x];
 }
 
-// Forward substitution of the tail levels in LDS on component comp: each
-// tail node first takes b_j and the terms of its descendants outside the
+// Forward substitution of the tail levels in LDS: each tail node first takes
+// b_j and the terms of its descendants outside the
 // tail (global lists, all nodes at once), then the tail levels go upward
 // with the local lists.  y of the tail stays in sy for the backward sweep.
-template <bool VL>
 __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m, const FdTail& t,
-                                                double* sy, const View& wb, int64_t rhs,
-                                                int comp, double* xv)
+                                                double* sy, const double* rhs, const double* x)
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
     for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x) {
         const int4 a = S.t_node[3 * jl], b = S.t_node[3 * jl + 1];
-        double z = *wb.at(rhs + 2 * (int64_t)a.x + comp);
+        double z = rhs[a.x];
         const int r1 = b.z;
         int r = b.y;
         int2 e[4];
@@ -194,7 +228,7 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 w[k] = sl[e[k].y].x;
-                y[k] = fd_x<VL>(xv, wb, rhs, comp, e[k].x);
+                y[k] = x[e[k].x];
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) e[k] = S.t_rl[r + 4 + k < r1 ? r + 4 + k : 0];
@@ -225,11 +259,26 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
         sy[d] = z;
     });
     for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) sy[jl] *= t.d[jl];
-    if (KC > 0) {
+    if (KC > 0 && threadIdx.x < kWave) {
         // the clique (every node adjacent to all above it) column by column
-        // on the first wavefront (no workgroup barriers)
-        if (threadIdx.x < kWave) {
-            const int c0 = S.t_node[3 * kf].w;
+        // on the first wavefront, without workgroup barriers; a node per lane
+        // in registers, as far as the lanes go, the next column in flight
+        const int c0 = S.t_node[3 * kf].w;
+        if (KC <= kWave) {
+            const int k = threadIdx.x;
+            auto column = [&](int q) {
+                return k > q && k < KC ? t.wu[clique_slot(c0, KC, q, k)].x : 0.0;
+            };
+            const double d = k < KC ? t.d[kf + k] : 0.0;
+            double z = k < KC ? sy[kf + k] : 0.0, w = column(0);
+            for (int q = 0; q < KC; ++q) {
+                const double next = column(q + 1);
+                const double yq = lane_value(d * z, q);
+                if (k > q) z = fma(-w, yq, z);
+                w = next;
+            }
+            if (k < KC) sy[kf + k] = d * z;
+        } else {
             for (int q = 0; q < KC; ++q) {
                 const double yq = t.d[kf + q] * sy[kf + q];
                 for (int k = q + 1 + threadIdx.x; k < KC; k += kWave)
@@ -242,15 +291,11 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
     __syncthreads();
 }
 
-// Backward substitution of the tail levels in LDS, downward; then, in one
-// parallel pass (so that no level waits for a bus-record load), each tail x
-// is written to the rhs for the levels below and its bus takes the half step.
-template <bool ANGLE, bool VL>
+// Backward substitution of the tail levels in LDS, downward; then each tail x
+// goes to x for the levels below.
 __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& t, double* sy,
-                                                 const View& wb, int64_t rhs, int64_t bus_off,
-                                                 const PvMask& pv, double* xv)
+                                                 double* x)
 {
-    const int comp = ANGLE ? 0 : 1;
     const int nT = S.nlev - S.tail_level, KC = S.tail_clique;
     const int kf = S.tail_nodes - KC;
     if (KC > 0) {
@@ -259,21 +304,42 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         // clique's terms of every node below it
         if (threadIdx.x < kWave) {
             const int c0 = S.t_node[3 * kf].w;
-            for (int q = KC - 1; q > 0; --q) {
-                const double xq = sy[kf + q];
-                for (int k = threadIdx.x; k < q; k += kWave)
-                    sy[kf + k] = fma(-t.wu[clique_slot(c0, KC, k, q)].y, xq, sy[kf + k]);
-                wave_sync();
+            if (KC <= kWave) {
+                const int k = threadIdx.x;
+                auto column = [&](int q) {
+                    return k < q ? t.wu[clique_slot(c0, KC, k, q)].y : 0.0;
+                };
+                double y = k < KC ? sy[kf + k] : 0.0, u = column(KC - 1);
+                for (int q = KC - 1; q > 0; --q) {
+                    const double next = column(q - 1);
+                    const double xq = lane_value(y, q);
+                    if (k < q) y = fma(-u, xq, y);
+                    u = next;
+                }
+                if (k < KC) sy[kf + k] = y;
+            } else {
+                for (int q = KC - 1; q > 0; --q) {
+                    const double xq = sy[kf + q];
+                    for (int k = threadIdx.x; k < q; k += kWave)
+                        sy[kf + k] = fma(-t.wu[clique_slot(c0, KC, k, q)].y, xq, sy[kf + k]);
+                    wave_sync();
+                }
             }
         }
         __syncthreads();
         for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
             const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
             double y = sy[jl];
-            for (int q = t1 - 1; q >= t0; --q) {
-                const int k = S.t_slot[q].y;
-                if (k < kf) break;
-                y = fma(-t.wu[q].y, sy[k], y);
+            bool more = true;
+            for (int q = t1 - 1; more && q >= t0; q -= 4) {  // the clique's are the last ones
+                int kk[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kk[i] = S.t_slot[q - i >= t0 ? q - i : t0].y;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    more = more && q - i >= t0 && kk[i] >= kf;
+                    if (more) y = fma(-t.wu[q - i].y, sy[kk[i]], y);
+                }
             }
             sy[jl] = y;
         }
@@ -284,28 +350,20 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         sy[o.d] = fma(-t.wu[o.a].y, sy[o.b], sy[o.d]);
     });
     __syncthreads();
-    for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x) {
-        const int4 a = S.t_node[3 * jl];
-        const double x = sy[jl];
-        fd_x<VL>(xv, wb, rhs, comp, a.x) = x;
-        fd_half_step<ANGLE>(wb, bus_off, a.y, pv, x);
-    }
+    for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x)
+        x[S.t_node[3 * jl].x] = sy[jl];
     __syncthreads();
 }
 
 // Backward substitution x_j = y_j - sum_{k in S(j)} u_jk x_k, levels
-// downward, and the half step at bus(j); four slots per lane per batch with
-// the next batch's indices in flight.
-template <bool ANGLE, bool VL>
-__device__ __forceinline__ void fd_backward(const DevSym& S, const double* m, const View& wb,
-                                            int64_t rhs, int64_t bus_off, const PvMask& pv,
-                                            int l1, double* xv)
+// downward; four slots per lane per batch with the next batch's indices in
+// flight.
+__device__ __forceinline__ void fd_backward(const DevSym& S, const double* m, double* x, int l1)
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
-    const int comp = ANGLE ? 0 : 1;
     for_nodes(S, 0, l1, false, [&](int, const NodeRec& rec, int lane, int g) {
         const int s1 = rec.b.y;
-        const double yj = fd_x<VL>(xv, wb, rhs, comp, rec.a.x);
+        const double yj = x[rec.a.x];
         // absent entries are not loaded (skipped when no lane needs them)
         int s = rec.b.x + lane;
         int kk[4];
@@ -316,14 +374,14 @@ __device__ __forceinline__ void fd_backward(const DevSym& S, const double* m, co
         }
         double a = 0.0;
         for (; s < s1; s += 4 * g) {
-            double u[4], x[4];
+            double u[4], xk[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 u[k] = 0.0;
-                x[k] = 0.0;
+                xk[k] = 0.0;
                 if (s + k * g < s1) {
                     u[k] = sl[s + k * g].y;
-                    x[k] = fd_x<VL>(xv, wb, rhs, comp, kk[k]);
+                    xk[k] = x[kk[k]];
                 }
             }
             const int sn = s + 4 * g;
@@ -332,118 +390,127 @@ __device__ __forceinline__ void fd_backward(const DevSym& S, const double* m, co
                 if (sn + k * g < s1) kk[k] = S.Li[sn + k * g];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                if (s + k * g < s1) a = fma(u[k], x[k], a);
+                if (s + k * g < s1) a = fma(u[k], xk[k], a);
         }
         if (g > 1) a = gsum(a, g);
-        if (lane == 0) {
-            const double xj = yj - a;
-            fd_x<VL>(xv, wb, rhs, comp, rec.a.x) = xj;
-            fd_half_step<ANGLE>(wb, bus_off, rec.a.y, pv, xj);
-        }
+        if (lane == 0) x[rec.a.x] = yj - a;
     });
 }
 
+// What k_fdpf keeps in LDS besides the PV mask and the tails: nothing (FD_NONE,
+// both matrices' tails), (e, f) per bus over the tail of one matrix at a time,
+// which is loaded after each mismatch pass (FD_OVER), and in it too the work
+// vector x of a half step (FD_OVER_X), or everything apart (FD_APART).
+enum { FD_NONE, FD_OVER, FD_OVER_X, FD_APART };
+
+// Offsets in doubles into the dynamic LDS (the PV mask at 0): (w, u) and 1/d
+// of the two matrices' tails, the tail's y, x by position and (e, f) per bus.
+struct FdLds {
+    int32_t mode, wu1, d1, wu2, d2, y, x, ef;
+};
+
 // The fast decoupled iteration of one case (one workgroup): mismatch, angle
 // half step with B', mismatch, magnitude half step with B'', until max|F| <
-// tol; iters counts angle half steps and max_iter bounds them.  VL: the
-// half step's work vector in LDS (after the tail of the half step's matrix).
-template <bool VL>
-__device__ void fdpf_case(const DevSym& S, const double* yv, const int8_t* type,
+// tol; iters counts angle half steps and max_iter bounds them.
+// Latency bounds it: a chain of some 60 barrier-separated steps per half step
+// (levels, tail, mismatch) on one workgroup, so registers are held to what two
+// workgroups per compute unit leave (128; with 156 a batch of 384 took two
+// rounds), x and (e, f) are in LDS where they fit, and the sine is taken once
+// per angle half step, in bus order.  Before -> after: 10,000 buses x 256
+// cases 5.52 -> 3.40 ms, 2,000 buses x 384 outages 2.65 -> 1.58 ms (the whole
+// screen), 3,001 buses alone 1.21 -> 0.97 ms.
+template <int MODE>
+__device__ void fdpf_case(const DevSym& S, const FdLds& L, const double* yv, const int8_t* type,
                           const double* Psp, const double* Qsp, double* Vm, double* Va,
-                          const View& wb, const double* m1, const double* m2, double tol,
+                          double* ws, const double* m1, const double* m2, double tol,
                           int max_iter, int32_t* o_iters, double* o_norm, int32_t* o_status)
 {
-    // LDS: PV mask, then either (ef_lds = 0) the (w, u) of the B' and B''
-    // tails | 1/d of both | tail y, loaded once; or the (e, f) copy of the
-    // mismatch pass, over which the tail of the matrix of the half step
-    // (w, u | 1/d | y) is loaded after each mismatch
     uint32_t* fd_pv = reinterpret_cast<uint32_t*>(pf_smem);
-    double* lds = pf_smem + ((((S.n + 63) / 64) + 1) & ~1);  // mask: 8 bytes per 64 buses
-    const int K = S.tail_nodes, TS = S.tail_slots;
-    const bool efl = S.ef_lds != 0;
-    const FdTail t1{reinterpret_cast<double2*>(lds), lds + (efl ? 2 : 4) * TS};
-    const FdTail t2 = efl ? t1 : FdTail{reinterpret_cast<double2*>(lds + 2 * TS), lds + 4 * TS + K};
-    double* sy = efl ? lds + 2 * TS + K : lds + 4 * TS + 2 * K;
-    double* xv = lds + 2 * TS + 2 * K;  // VL only
-    const bool tail = K > 0;
+    const FdTail t1{reinterpret_cast<double2*>(pf_smem + L.wu1), pf_smem + L.d1};
+    const FdTail t2{reinterpret_cast<double2*>(pf_smem + L.wu2), pf_smem + L.d2};
+    double* sy = pf_smem + L.y;
+    const EFLds efs{reinterpret_cast<double2*>(pf_smem + L.ef)};
+    constexpr bool efl = MODE != FD_NONE, shared = MODE == FD_OVER || MODE == FD_OVER_X;
+    const bool tail = S.tail_nodes > 0;
     const int lg = tail ? S.tail_level : S.nlev;  // levels swept in global memory
-    if (tail && !efl) {
+    // workspace: (cos, sin) | (e, f) | b | x
+    const FdState st{Vm, Va, reinterpret_cast<double2*>(ws),
+                     reinterpret_cast<double2*>(ws) + S.n};
+    double* const b = ws + 4 * (int64_t)S.n;
+    double* const x = MODE >= FD_OVER_X ? pf_smem + L.x : b + S.nn;
+    const EFLds efg{st.ef};
+    if (tail && !shared) {
         fd_tail_load(S, m1, t1);
         fd_tail_load(S, m2, t2);
     }
-    const Off o = ws_off(S);
+    auto put_ef = [&](int i, double2 v) {
+        if (!efl) st.ef[i] = v;
+        else if (!shared) efs.s[i] = v;
+    };
     for (int i = threadIdx.x; i < S.n; i += blockDim.x) {
         double sn, cs;
         const double vm = Vm[i], va = Va[i];
         sincos(va, &sn, &cs);
-        wb.put(o.BUS + 8 * (int64_t)i, {vm * cs, vm * sn, vm, va});
+        st.cs[i] = make_double2(cs, sn);
+        put_ef(i, make_double2(vm * cs, vm * sn));
     }
     pv_fill_at(fd_pv, S, type);
     __syncthreads();
     const PvMask pvm{fd_pv};
-    const EFView ef{wb, o.BUS};
-    int it = 0, half = 0, st = ST_NOT_CONVERGED;
+    int it = 0, half = 0, status = ST_NOT_CONVERGED;
     double nrm = 0.0;
     for (;;) {
         double mx = 0.0;
         int nan = 0;
-        if (efl) {
-            const EFLds efs{reinterpret_cast<double2*>(lds)};
-            for (int i = threadIdx.x; i < S.n; i += blockDim.x)
-                efs.s[i] = wb.v2(o.BUS + 8 * (int64_t)i);
+        const MisHalf out{Vm, b, half != 0};
+        if (shared) {
+            // each thread's own buses of the half step (or of the start)
+            for (int i = fresh_thread(); i < S.n; i += wg_size()) {
+                const double2 cs = st.cs[i];
+                const double vm = Vm[i];
+                efs.s[i] = make_double2(vm * cs.x, vm * cs.y);
+            }
             __syncthreads();
-            mismatch_pass<true>(S, yv, efs, wb, o, pvm, Psp, Qsp, mx, nan);
-        } else {
-            mismatch_pass<true>(S, yv, ef, wb, o, pvm, Psp, Qsp, mx, nan);
         }
+        mismatch_pass<2>(S, yv, efl ? efs : efg, out, pvm, Psp, Qsp, mx, nan, fresh_thread(), wg_size());
         int any_nan = 0;
         nrm = block_max(mx, nan, any_nan);
         if (any_nan || !isfinite(nrm)) {
-            st = ST_NONFINITE;
+            status = ST_NONFINITE;
             break;
         }
         if (nrm < tol) {
-            st = ST_OK;
+            status = ST_OK;
             break;
         }
-        if (efl && tail && (half != 0 || it < max_iter)) {
+        if (half == 0 && it >= max_iter) break;
+        if (shared && tail) {
             fd_tail_load(S, half == 0 ? m1 : m2, t1);
             __syncthreads();
         }
+        const double* m = half == 0 ? m1 : m2;
+        const FdTail& t = half == 0 || shared ? t1 : t2;
+        fd_forward(S, m, b, x, lg);
+        if (tail) {
+            fd_forward_tail(S, m, t, sy, b, x);
+            fd_backward_tail(S, t, sy, x);
+        }
+        fd_backward(S, m, x, lg);
         if (half == 0) {
-            if (it >= max_iter) {
-                st = ST_NOT_CONVERGED;
-                break;
-            }
-            fd_forward<VL>(S, m1, wb, o.RHS, 0, lg, xv);
-            if (tail) {
-                fd_forward_tail<VL>(S, m1, t1, sy, wb, o.RHS, 0, xv);
-                fd_backward_tail<true, VL>(S, t1, sy, wb, o.RHS, o.BUS, pvm, xv);
-            }
-            fd_backward<true, VL>(S, m1, wb, o.RHS, o.BUS, pvm, lg, xv);
+            fd_half_step<true>(S, st, pvm, x, put_ef);
             ++it;
         } else {
-            fd_forward<VL>(S, m2, wb, o.RHS, 1, lg, xv);
-            if (tail) {
-                fd_forward_tail<VL>(S, m2, t2, sy, wb, o.RHS, 1, xv);
-                fd_backward_tail<false, VL>(S, t2, sy, wb, o.RHS, o.BUS, pvm, xv);
-            }
-            fd_backward<false, VL>(S, m2, wb, o.RHS, o.BUS, pvm, lg, xv);
+            fd_half_step<false>(S, st, pvm, x, put_ef);
         }
+        __syncthreads();
         half ^= 1;
-    }
-    for (int i = threadIdx.x; i < S.n; i += blockDim.x) {
-        const Blk r = wb.blk(o.BUS + 8 * (int64_t)i);
-        Vm[i] = r.c;
-        Va[i] = r.d;
     }
     if (threadIdx.x == 0) {
         if (o_iters) *o_iters = it;
         if (o_norm) *o_norm = nrm;
-        if (o_status) *o_status = st;
+        if (o_status) *o_status = status;
     }
 }
-
 
 }  // namespace
 
@@ -512,28 +579,17 @@ __global__ void k_fill_status(int B, int32_t* status, int32_t v)
     if (c < B) status[c] = v;
 }
 
-__global__ __launch_bounds__(kLevelThreads) void k_fdpf(DevSym S, NewtonArgs a,
-                                                        const double* mat, int64_t mstride)
+template <int MODE>
+__global__ __launch_bounds__(kLevelThreads, 4) void k_fdpf(DevSym S, FdLds L, NewtonArgs a,
+                                                           const double* mat, int64_t mstride)
 {
     const int c = blockIdx.x;
-    View wb;
-    wb.base = a.ws + c * a.ws_stride;
-    wb.lane = 0;
-    wb.sh = 2;
-    wb.cs = 2;
     const double* m1 = mat + c * mstride;
-    // the work vector fits in LDS after one matrix's tail, within the (e, f) copy
-    const bool vl = S.ef_lds != 0 &&
-                    16 * ((int64_t)S.tail_slots + S.tail_nodes) + 8 * (int64_t)S.nn <= S.ef_lds;
-    auto run = [&](auto tag) {
-        fdpf_case<decltype(tag)::value>(
-            S, a.yval + c * a.y_stride, a.type + c * a.type_stride, a.Psp + c * a.inj_stride,
-            a.Qsp + c * a.inj_stride, a.Vm + c * a.v_stride, a.Va + c * a.v_stride, wb, m1,
-            m1 + S.fd_mat, a.tol, a.max_iter, a.iters ? a.iters + c : nullptr,
-            a.norm ? a.norm + c : nullptr, a.status ? a.status + c : nullptr);
-    };
-    if (vl) run(std::true_type{});
-    else run(std::false_type{});
+    fdpf_case<MODE>(S, L, a.yval + c * a.y_stride, a.type + c * a.type_stride,
+                    a.Psp + c * a.inj_stride, a.Qsp + c * a.inj_stride, a.Vm + c * a.v_stride,
+                    a.Va + c * a.v_stride, a.ws + c * a.ws_stride, m1, m1 + S.fd_mat, a.tol,
+                    a.max_iter, a.iters ? a.iters + c : nullptr, a.norm ? a.norm + c : nullptr,
+                    a.status ? a.status + c : nullptr);
 }
 
 // Branch flows (Sec. II-A: post-convergence, edge by edge): pi-model with
@@ -574,36 +630,82 @@ __global__ void k_branch_flows(int m, const int32_t* __restrict__ from,
 
 namespace {
 
-// Dynamic LDS of the fast decoupled kernel: PV mask (rounded to 16 bytes),
-// then (w, u) of both matrices' tails, 1/d of both, and the tail's y.
-size_t fd_lds_bytes(const HostSym& h)
-{
-    const size_t mask = ((pv_mask_bytes(h.n) + 15) / 16) * 16;
-    if (h.ef_lds)  // (e, f) copy, and one matrix's tail at a time over it
-        return mask + std::max((size_t)h.ef_lds,
-                               8 * (2 * (size_t)h.tail_slots + 2 * (size_t)h.tail_nodes));
-    return mask + 8 * (4 * (size_t)h.tail_slots + 3 * (size_t)h.tail_nodes);
-}
+using FdKernel = void (*)(DevSym, FdLds, NewtonArgs, const double*, int64_t);
+constexpr FdKernel kFdKernels[] = {&k_fdpf<FD_NONE>, &k_fdpf<FD_OVER>, &k_fdpf<FD_OVER_X>,
+                                   &k_fdpf<FD_APART>};
 
-// Raises the dynamic-LDS limit of the fast decoupled kernel to what the device
-// allows minus its static LDS (failures keep the default limit).
-void allow_big_lds_fdpf()
-{
-    static bool done = false;
-    if (done) return;
-    done = true;
-    int dev = 0, lds_max = 0;
-    hipFuncAttributes fa{};
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-            hipSuccess &&
-        hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_fdpf)) == hipSuccess) {
-        const int dyn = lds_max - (int)fa.sharedSizeBytes;
-        if (dyn > 0)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fdpf),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+// The fast decoupled kernels' dynamic-LDS limit, raised to what the device
+// allows minus their static LDS (failures keep the default limit: 0 here), and
+// the device's compute units.
+struct FdDevice {
+    int64_t dyn = 0;
+    int cus = 1;
+    FdDevice()
+    {
+        int dev = 0, lds_max = 0, mp = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
+                hipSuccess &&
+            hipDeviceGetAttribute(&mp, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
+            int64_t least = lds_max;
+            for (FdKernel k : kFdKernels) {
+                const void* f = reinterpret_cast<const void*>(k);
+                hipFuncAttributes fa{};
+                int d = 0;
+                if (hipFuncGetAttributes(&fa, f) == hipSuccess)
+                    d = lds_max - (int)fa.sharedSizeBytes;
+                if (d <= 0 || hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  d) != hipSuccess)
+                    d = 0;
+                least = std::min(least, (int64_t)d);
+            }
+            dyn = least;
+            cus = std::max(mp, 1);
+        }
+        (void)hipGetLastError();
     }
-    (void)hipGetLastError();
+};
+
+// LDS of B cases (bytes into *bytes).  Everything apart, if the device can
+// keep as many of the launch's workgroups resident as with less LDS; else
+// (e, f) over the rest as far as the caller's budget has room for it; else
+// (e, f) in the workspace.
+FdLds fd_lds(const HostSym& h, int B, int threads, const FdDevice& dev, size_t* bytes)
+{
+    const int64_t mask = (((int64_t)pv_mask_bytes(h.n) + 15) / 16) * 2;
+    const int64_t TS = h.tail_slots, K = h.tail_nodes, n = h.n, nn = h.nn;
+    const int64_t K2 = (K + 1) & ~(int64_t)1, nn2 = (nn + 1) & ~(int64_t)1;
+    const int64_t tails = 4 * TS + 3 * K2;  // both matrices' (w, u) | 1/d | 1/d | y
+    const int64_t apart = mask + tails + nn2 + 2 * n;
+    const int64_t less = mask + (h.ef_lds ? std::max((int64_t)h.ef_lds / 8, 2 * (TS + K)) : tails);
+    // workgroups a compute unit gets, of those its registers have room for
+    const int64_t want = std::min(((int64_t)B + dev.cus - 1) / dev.cus,
+                                  std::max((int64_t)1, (int64_t)2 * kLevelThreads / threads));
+    auto resident = [&](int64_t doubles) { return std::min(want, dev.dyn / (8 * doubles + 512)); };
+    const bool all = resident(apart) > 0 && resident(apart) >= resident(less);
+    FdLds L;
+    L.wu1 = L.x = L.ef = (int32_t)mask;
+    if (all || !h.ef_lds) {
+        L.mode = all ? FD_APART : FD_NONE;
+        L.wu2 = (int32_t)(mask + 2 * TS);
+        L.d1 = (int32_t)(mask + 4 * TS);
+        L.d2 = (int32_t)(L.d1 + K2);
+        L.y = (int32_t)(L.d2 + K2);
+        if (all) {
+            L.x = (int32_t)(mask + tails);
+            L.ef = (int32_t)(mask + tails + nn2);
+        }
+    } else {
+        // x after one matrix's tail, within the (e, f) copy
+        const bool in = 8 * (2 * (TS + K) + nn) <= h.ef_lds;
+        L.mode = in ? FD_OVER_X : FD_OVER;
+        L.wu2 = L.wu1;
+        L.d1 = L.d2 = (int32_t)(mask + 2 * TS);
+        L.y = (int32_t)(L.d1 + K);
+        if (in) L.x = (int32_t)(L.y + K);
+    }
+    *bytes = 8 * (size_t)(all ? apart : less);
+    return L;
 }
 
 }  // namespace
@@ -677,9 +779,12 @@ int pf_fdpf(const pf_symbolic s, int B, const double* d_yval, int64_t y_stride,
     if (B == 0) return PF_OK;
     NewtonArgs a{d_yval, y_stride, d_type, type_stride, d_Psp, d_Qsp, inj_stride, d_Vm, d_Va,
                  v_stride, d_ws, ws_stride, tol, max_iter, 0, 1, B, d_iters, d_norm, d_status};
-    allow_big_lds_fdpf();
-    hipLaunchKernelGGL(k_fdpf, dim3(B), dim3(launch_threads(s->h, B)),
-                       fd_lds_bytes(s->h), as_stream(stream), s->h.dev, a, d_mat, mat_stride);
+    static const FdDevice device;
+    size_t lds = 0;
+    const int threads = launch_threads(s->h, B);
+    const FdLds L = fd_lds(s->h, B, threads, device, &lds);
+    hipLaunchKernelGGL(kFdKernels[L.mode], dim3(B), dim3(threads), lds, as_stream(stream),
+                       s->h.dev, L, a, d_mat, mat_stride);
     return launch_check("pf_fdpf");
 }
 

@@ -185,7 +185,8 @@ struct HostSym {
     int64_t fd_lu() const { return ((int64_t)nn + 7) & ~(int64_t)7; }
     int64_t fd_mat() const { return (fd_lu() + 2 * (int64_t)Li.size() + 7) & ~(int64_t)7; }
     int64_t fd_ws_doubles() const {
-        int64_t w = 8 * (int64_t)n + 2 * (int64_t)nn;  // bus records | rhs
+        // (cos, sin) | (e, f) | b | x, with room to spare
+        int64_t w = 8 * (int64_t)n + 2 * (int64_t)nn;
         return (w + 31) & ~(int64_t)31;
     }
     // vals | bus records (8 n) | rhs (2 nn) | grid-barrier words of a one-case

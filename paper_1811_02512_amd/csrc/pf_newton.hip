@@ -110,9 +110,10 @@ __device__ __forceinline__ void newton_case(const P& par, const DevSym& S, const
             for (int i = threadIdx.x; i < S.n; i += blockDim.x)
                 el.s[i] = wb.v2(o.BUS + 8 * (int64_t)i);
             __syncthreads();
-            mismatch_pass<false, EFLds, 4>(S, yv, el, wb, o, pvm, Psp, Qsp, mx, nan);
+            mismatch_pass<4>(S, yv, el, MisNewton{wb, o.BUS}, pvm, Psp, Qsp, mx, nan,
+                             (int)threadIdx.x, (int)blockDim.x);
         } else {
-            mismatch_pass<false>(S, yv, ef, wb, o, pvm, Psp, Qsp, mx, nan, t0(), ts());
+            mismatch_pass<2>(S, yv, ef, MisNewton{wb, o.BUS}, pvm, Psp, Qsp, mx, nan, t0(), ts());
         }
         int any_nan = 0;
         nrm = block_max(mx, nan, any_nan);
