@@ -455,6 +455,8 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
         r[3] = s.yup[q];
         r[4] = s.Up[q];
         r[5] = s.Up[q + 1];
+        r[6] = s.owner[q];
+        r[7] = s.perm[s.owner[q]];
     }
     s.rl.resize(2 * (size_t)nnzl);
     for (int64_t q = 0; q < nnzl; ++q) {

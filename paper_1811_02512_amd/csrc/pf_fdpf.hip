@@ -26,16 +26,17 @@ namespace {
 // B'' of a PV bus is the identity row and column, so its |V| never moves.
 // ---------------------------------------------------------------------------
 
-// Entry of B' (XB = false) or B'' from the branches of admittance entry q.
+// Entry of B' (XB = false) or B'' from the branches [t0, t1) of an admittance
+// entry's list, the first of them e0.
 template <bool XB>
-__device__ __forceinline__ double fd_entry(const DevSym& S, int q, bool diag,
+__device__ __forceinline__ double fd_entry(const DevSym& S, int t0, int t1, int e0, bool diag,
                                            const double* __restrict__ r,
                                            const double* __restrict__ x,
                                            const double* __restrict__ b)
 {
     double v = 0.0;
-    for (int t = S.ybr_ptr[q]; t < S.ybr_ptr[q + 1]; ++t) {
-        const int e = S.ybr[t];
+    for (int t = t0; t < t1; ++t) {
+        const int e = t == t0 ? e0 : S.ybr[t];
         if (!XB) {
             const double bx = 1.0 / x[e];
             v += diag ? bx : -bx;
@@ -52,15 +53,26 @@ __device__ __forceinline__ double fd_entry(const DevSym& S, int q, bool diag,
 // blocks and U = L^T):
 //   d_j = a_jj - sum_{i in R(j)} w_ji u_ij,
 //   w_kj = a_kj - sum_i w_ki u_ij (k in S(j)),  u_jk = w_kj / d_j.
+// Bound by its chains of loads (list, then factor entries), so four terms are
+// requested at a time, the next four's indices under them: both matrices of
+// 384 cases of 2,000 buses 183 -> 155 us.
 __device__ __forceinline__ void fd_factor_node(const DevSym& S, const NodeRec& rec, int lane,
                                                int g, double* m, int* s_bad)
 {
     const int j = rec.a.x;
     double2* sl = reinterpret_cast<double2*>(m + S.fd_lu);
     double ds = 0.0;
-    for (int r = rec.a.z + lane; r < rec.a.w; r += g) {
-        const double2 wu = sl[S.rl[r].y];
-        ds = fma(wu.x, wu.y, ds);
+    const int r1 = rec.a.w;
+    for (int r = rec.a.z + lane; r < r1; r += 4 * g) {
+        int at[4];
+        double2 wu[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[k] = S.rl[r + k * g < r1 ? r + k * g : r].y;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) wu[k] = sl[at[k]];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (r + k * g < r1) ds = fma(wu[k].x, wu[k].y, ds);
     }
     if (g > 1) ds = gsum(ds, g);
     const double D = m[j] - ds;
@@ -69,9 +81,24 @@ __device__ __forceinline__ void fd_factor_node(const DevSym& S, const NodeRec& r
     for (int s = rec.b.x + lane; s < rec.b.y; s += g) {
         const int4 b = S.slot_info[2 * s + 1];
         double W = sl[s].x;
-        for (int u = b.x; u < b.y; ++u) {
-            const int2 p = S.upd[u];
-            W = fma(-sl[p.x].x, sl[p.y].y, W);
+        int2 p[4];
+        if (b.x < b.y) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = S.upd[b.x + k < b.y ? b.x + k : b.x];
+        }
+        for (int u = b.x; u < b.y; u += 4) {
+            double w[4], v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w[k] = sl[p[k].x].x;
+                v[k] = sl[p[k].y].y;
+            }
+            const int un = u + 4 < b.y ? u + 4 : u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = S.upd[un + k < b.y ? un + k : un];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (u + k < b.y) W = fma(-w[k], v[k], W);
         }
         sl[s] = make_double2(W, W * Dinv);
     }
@@ -516,41 +543,51 @@ __device__ void fdpf_case(const DevSym& S, const FdLds& L, const double* yv, con
 
 
 // Fast decoupled matrices of B cases: B' then B'' (fd_mat doubles each) in
-// the scalar filled layout, lower and upper values equal.
-__global__ void k_fd_matrices(DevSym S, const double* __restrict__ r,
+// the scalar filled layout, lower and upper values equal.  A thread per
+// diagonal entry, then one per slot: the chain of loads from the slot to its
+// branches bounds it (a thread per node, slot after slot: 2,000 buses x 384
+// cases 116 us, now 61).
+__global__ void k_fd_matrices(DevSym S, int B, int per_case, int slots, const double* __restrict__ r,
                               const double* __restrict__ x, const double* __restrict__ b,
                               int64_t bstride, const double* __restrict__ ysh,
                               int64_t sh_stride, const int8_t* __restrict__ type,
                               int64_t type_stride, double* __restrict__ mat, int64_t mstride)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (p >= S.fd_lu) return;
+    const int2 at = item_block(per_case, B);
+    const int c = at.x, p = at.y + threadIdx.x;
+    const int s = p - S.fd_lu;
+    if (c < 0 || s >= slots) return;
+    const bool diag = s < 0, pad = diag && p >= S.nn;  // padding of the d sections
+    int q = -1, bj = 0, bk = 0;
+    if (!diag) {
+        const int4 a = S.slot_info[2 * s];
+        q = a.z;
+        bk = a.y;
+        bj = S.slot_info[2 * s + 1].w;
+    } else if (!pad) {
+        q = S.ydiag[p];
+        bj = S.perm[p];
+    }
+    const int t0 = q < 0 ? 0 : S.ybr_ptr[q], t1 = q < 0 ? 0 : S.ybr_ptr[q + 1];
+    const int e0 = t0 < t1 ? S.ybr[t0] : 0;
     const double* rc = r + c * bstride;
     const double* xc = x + c * bstride;
     const double* bc = b + c * bstride;
     const int8_t* tc = type + c * type_stride;
     double* m1 = mat + c * mstride;
     double* m2 = m1 + S.fd_mat;
-    if (p >= S.nn) {  // padding of the d sections
-        m1[p] = 0.0;
-        m2[p] = 0.0;
-        return;
-    }
-    const bool pvj = tc[S.perm[p]] == T_PV;
-    // B'' = -Im(Y): the bus shunt's susceptance comes off the diagonal
-    const double bsh = ysh ? ysh[c * sh_stride + 2 * (int64_t)S.perm[p] + 1] : 0.0;
-    m1[p] = fd_entry<false>(S, S.ydiag[p], true, rc, xc, bc);
-    m2[p] = pvj ? 1.0 : fd_entry<true>(S, S.ydiag[p], true, rc, xc, bc) - bsh;
-    double2* s1 = reinterpret_cast<double2*>(m1 + S.fd_lu);
-    double2* s2 = reinterpret_cast<double2*>(m2 + S.fd_lu);
-    for (int s = S.Lp[p]; s < S.Lp[p + 1]; ++s) {
-        const int q = S.ylo[s];
-        const bool pvk = tc[S.perm[S.Li[s]]] == T_PV;
-        const double v1 = q < 0 ? 0.0 : fd_entry<false>(S, q, false, rc, xc, bc);
-        const double v2 = (q < 0 || pvj || pvk) ? 0.0 : fd_entry<true>(S, q, false, rc, xc, bc);
-        s1[s] = make_double2(v1, v1);
-        s2[s] = make_double2(v2, v2);
+    const double v1 = fd_entry<false>(S, t0, t1, e0, diag, rc, xc, bc);
+    const double v2 = fd_entry<true>(S, t0, t1, e0, diag, rc, xc, bc);
+    const bool pvj = tc[bj] == T_PV;
+    if (diag) {
+        // B'' = -Im(Y): the bus shunt's susceptance comes off the diagonal
+        const double bsh = ysh && !pad ? ysh[c * sh_stride + 2 * (int64_t)bj + 1] : 0.0;
+        m1[p] = pad ? 0.0 : v1;
+        m2[p] = pad ? 0.0 : pvj ? 1.0 : v2 - bsh;
+    } else {
+        const double w2 = pvj || tc[bk] == T_PV ? 0.0 : v2;
+        reinterpret_cast<double2*>(m1 + S.fd_lu)[s] = make_double2(v1, v1);
+        reinterpret_cast<double2*>(m2 + S.fd_lu)[s] = make_double2(w2, w2);
     }
 }
 
@@ -593,38 +630,40 @@ __global__ __launch_bounds__(kLevelThreads, 4) void k_fdpf(DevSym S, FdLds L, Ne
 }
 
 // Branch flows (Sec. II-A: post-convergence, edge by edge): pi-model with
-// series y = 1/(r + jx) and charging b, I_ft = (y + jb/2) V_f - y V_t,
-// S_ft = V_f conj(I_ft), and the same from the other end.
-__global__ void k_branch_flows(int m, const int32_t* __restrict__ from,
+// series y = g + jb' = 1/(r + jx) and charging b,
+//   S_ft = V_f conj((y + jb/2) V_f - y V_t)
+//        = |V_f|^2 (g - j(b' + b/2)) - |V_f||V_t| e^{j d} (g - jb'),
+// d = theta_f - theta_t, and the same from the other end with -d: one sine for
+// both ends.  The outputs are not read here: stored past the caches.  The
+// gathered voltages bound it, not the sines (one or two: the same 119 us at
+// 10,000 buses x 512 cases; several cases per thread: 141 and more): with a
+// case's workgroups on one XCD 81 us; 63 us for the bytes.
+__global__ void k_branch_flows(int m, int B, int per_case, const int32_t* __restrict__ from,
                                const int32_t* __restrict__ to, const double* __restrict__ r,
                                const double* __restrict__ x, const double* __restrict__ b,
                                int64_t bstride, const double* __restrict__ Vm,
                                const double* __restrict__ Va, int64_t vstride, double* Pft,
                                double* Qft, double* Ptf, double* Qtf, int64_t ostride)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (e >= m) return;
+    const int2 at = item_block(per_case, B);
+    const int c = at.x, e = at.y + threadIdx.x;
+    if (c < 0 || e >= m) return;
     const int fb = from[e], tb = to[e];
     const double rr = r[c * bstride + e], xx = x[c * bstride + e], hb = b[c * bstride + e] / 2.0;
-    const double den = rr * rr + xx * xx;
-    const double yg = rr / den, yb = -xx / den;
     const double* vm = Vm + c * vstride;
     const double* va = Va + c * vstride;
-    double sf, cf, st, ct;
-    sincos(va[fb], &sf, &cf);
-    sincos(va[tb], &st, &ct);
-    const double ef = vm[fb] * cf, ff = vm[fb] * sf, et = vm[tb] * ct, ft = vm[tb] * st;
-    // I_ft = (yg + j(yb + hb)) V_f - (yg + j yb) V_t, and symmetrically
-    const double ifr = yg * ef - (yb + hb) * ff - (yg * et - yb * ft);
-    const double ifi = yg * ff + (yb + hb) * ef - (yg * ft + yb * et);
-    const double itr = yg * et - (yb + hb) * ft - (yg * ef - yb * ff);
-    const double iti = yg * ft + (yb + hb) * et - (yg * ff + yb * ef);
+    const double vf = vm[fb], vt = vm[tb];
+    double sn, cs;
+    sincos(va[fb] - va[tb], &sn, &cs);
+    const double den = rr * rr + xx * xx;
+    const double g = rr / den, yb = -xx / den, bs = yb + hb;
+    const double ff = vf * vf, tt = vt * vt, ft = vf * vt;
+    const double gc = g * cs, gs = g * sn, bc = yb * cs, bn = yb * sn;
     const int64_t o = c * ostride + e;
-    Pft[o] = ef * ifr + ff * ifi;  // V conj(I)
-    Qft[o] = ff * ifr - ef * ifi;
-    Ptf[o] = et * itr + ft * iti;
-    Qtf[o] = ft * itr - et * iti;
+    __builtin_nontemporal_store(ff * g - ft * (gc + bn), &Pft[o]);
+    __builtin_nontemporal_store(-ff * bs - ft * (gs - bc), &Qft[o]);
+    __builtin_nontemporal_store(tt * g - ft * (gc - bn), &Ptf[o]);
+    __builtin_nontemporal_store(-tt * bs + ft * (gs + bc), &Qtf[o]);
 }
 
 
@@ -729,10 +768,12 @@ int pf_fdpf_matrices(const pf_symbolic s, int B, const double* d_r, const double
     if (!shared_stride_ok(B, branch_stride, s->h.m) || !shared_stride_ok(B, type_stride, s->h.n))
         return fail(PF_E_WORKSPACE, "pf_fdpf_matrices: a stride is too small or negative");
     if (B == 0) return PF_OK;
-    dim3 grid((unsigned)((s->h.fd_lu() + 255) / 256), B);
-    hipLaunchKernelGGL(k_fd_matrices, grid, dim3(256), 0, as_stream(stream), s->h.dev, d_r, d_x,
-                       d_b, branch_stride, d_ysh, ysh_stride, d_type, type_stride, d_mat,
-                       mat_stride);
+    const int64_t slots = (int64_t)s->h.Li.size();
+    int per_case = 0;
+    const dim3 grid = item_grid(s->h.fd_lu() + slots, B, &per_case);
+    hipLaunchKernelGGL(k_fd_matrices, grid, dim3(256), 0, as_stream(stream), s->h.dev, B, per_case,
+                       (int)slots, d_r, d_x, d_b, branch_stride, d_ysh, ysh_stride, d_type,
+                       type_stride, d_mat, mat_stride);
     return launch_check("pf_fdpf_matrices");
 }
 
@@ -802,8 +843,10 @@ int pf_branch_flows(const pf_symbolic s, int B, const double* d_r, const double*
     if (!shared_stride_ok(B, branch_stride, s->h.m))
         return fail(PF_E_WORKSPACE, "pf_branch_flows: branch_stride too small or negative");
     if (B == 0 || s->h.m == 0) return PF_OK;
-    dim3 grid((s->h.m + 255) / 256, B);
-    hipLaunchKernelGGL(k_branch_flows, grid, dim3(256), 0, as_stream(stream), s->h.m, s->d_from,
+    int per_case = 0;
+    const dim3 grid = item_grid(s->h.m, B, &per_case);
+    hipLaunchKernelGGL(k_branch_flows, grid, dim3(256), 0, as_stream(stream), s->h.m, B, per_case,
+                       s->d_from,
                        s->d_to, d_r, d_x, d_b, branch_stride, d_Vm, d_Va, v_stride, d_Pft, d_Qft,
                        d_Ptf, d_Qtf, out_stride);
     return launch_check("pf_branch_flows");

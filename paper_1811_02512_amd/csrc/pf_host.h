@@ -29,6 +29,17 @@ int launch_check(const char* what);
 // Workgroup size of the level-scheduled kernels: the symbolic's setting, or
 // by batch size.
 int launch_threads(const pf::HostSym& h, int B);
+// Grid of a per-item kernel (an item: a bus, a branch, a slot; 256 threads per
+// workgroup) over B cases, and the workgroups per case it hands to the kernel
+// (item_block): one dimension, a case on one XCD, where that leaves at most
+// one in nine of the XCDs' turns empty.
+inline dim3 item_grid(int64_t items, int B, int* per_case)
+{
+    const int64_t nb = (items + 255) / 256, full = ((int64_t)B + 7) / 8 * 8, lin = nb * full;
+    const bool xcd = 8 * full <= 9 * (int64_t)B && lin < (int64_t)1 << 23;  // under 2^32 threads
+    *per_case = xcd ? (int)nb : 0;
+    return xcd ? dim3((unsigned)lin) : dim3((unsigned)nb, B);
+}
 // Blocks for B cases in groups of C placed one XCD round apart.
 int grid_blocks(int B, int C);
 bool valid_interleave(int C);

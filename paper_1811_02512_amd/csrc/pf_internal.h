@@ -21,8 +21,8 @@ namespace pf {
 //     j = position, [r0, r1) = its lower-neighbour range in rl,
 //     [s0, s1) = its slots (higher neighbours), ydiag = Y entry (bus, bus),
 //     [q0, q1) = the bus's admittance row
-//   slot_info[s] (2 x int4): {k, bus_k, ylo, yup}, {u0, u1, 0, 0}
-//     k = higher neighbour, ylo/yup = Y entries (bus_k, bus_j) / (bus_j,
+//   slot_info[s] (2 x int4): {k, bus_k, ylo, yup}, {u0, u1, j, bus_j}
+//     k = higher neighbour, j = the owner, ylo/yup = Y entries (bus_k, bus_j) / (bus_j,
 //     bus_k) or -1 for fill, [u0, u1) = its update pairs in upd
 //   rl[r] = (i, slot(i;j))      upd[u] = (slot(i;k), slot(i;j))
 //

@@ -258,21 +258,22 @@ struct AsmPolar {
         injection(*S, yv, ef, bus, p, q);
         return jac_diag(y.x, y.y, p, q, Vm[bus], type[bus] == T_PV);
     }
-    __device__ __forceinline__ void off(int j, int s, Blk& lo, Blk& up) const
+    __device__ __forceinline__ void off(int s, Blk& lo, Blk& up) const
     {
-        const int ylo = S->ylo[s];
+        const int4 a = S->slot_info[2 * s], b = S->slot_info[2 * s + 1];
+        const int ylo = a.z;
         if (ylo < 0) {
             lo = bzero();
             up = bzero();
             return;
         }
-        const int bj = S->perm[j], bk = S->perm[S->Li[s]];
+        const int bj = b.w, bk = a.y;
         double ej, fj, ek, fk;
         ef.get(bj, ej, fj);
         ef.get(bk, ek, fk);
         const bool pj = type[bj] == T_PV, pk = type[bk] == T_PV;
         const double2 yl = reinterpret_cast<const double2*>(yv)[ylo];
-        const double2 yu = reinterpret_cast<const double2*>(yv)[S->yup[s]];
+        const double2 yu = reinterpret_cast<const double2*>(yv)[a.w];
         lo = jac_off(yl.x, yl.y, ek, fk, ej, fj, Vm[bj], pk, pj);
         up = jac_off(yu.x, yu.y, ej, fj, ek, fk, Vm[bk], pj, pk);
     }
@@ -323,15 +324,17 @@ __device__ __forceinline__ void ybus_row(const DevSym& S, int i, int sub, int ns
     }
 }
 
-__global__ void k_ybus(DevSym S, const double* __restrict__ r, const double* __restrict__ x,
+// A case's rows on one XCD (item_block): 2,000 buses x 384 cases 98 -> 59 us.
+__global__ void k_ybus(DevSym S, int B, int per_case, const double* __restrict__ r, const double* __restrict__ x,
                        const double* __restrict__ bc, int64_t bstride,
                        const double* __restrict__ ysh, int64_t sh_stride,
                        double* __restrict__ yval, int64_t ystride)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int2 at = item_block(per_case, B);
+    const int t = at.y + threadIdx.x;
     const int i = t / kYbusLanes;
-    const int c = blockIdx.y;
-    if (i >= S.n) return;
+    const int c = at.x;
+    if (c < 0 || i >= S.n) return;
     const double2* sh = ysh ? reinterpret_cast<const double2*>(ysh + c * sh_stride) : nullptr;
     ybus_row(S, i, t % kYbusLanes, kYbusLanes, r + c * bstride, x + c * bstride,
              bc + c * bstride, sh, yval + c * ystride);
@@ -353,14 +356,28 @@ __global__ void k_ybus_multi(const CaseDesc* __restrict__ descs, const double* _
                  x + cd.br_off, bc + cd.br_off, sh, yval + cd.y_off);
 }
 
+// Mismatch and injections of one case per workgroup.  LDS: (e, f) of every bus
+// there, one sine per bus instead of one per admittance entry, which bound the
+// pass: 5,003 buses x 48 cases 82 -> 23 us.  Without room for it (above 10,176
+// buses) the entries' voltages come from their polar values.
+template <bool LDS>
 __global__ __launch_bounds__(kMaxThreads) void k_mismatch(
     DevSym S, const double* yval, int64_t y_stride, const int8_t* type, int64_t type_stride,
     const double* Psp, const double* Qsp, int64_t inj_stride, const double* Vm,
     const double* Va, int64_t v_stride, double* rhs, int64_t rhs_stride, double* norm,
     double* PQ)
 {
-    const int c = blockIdx.x;
-    const EFPolar ef{Vm + c * v_stride, Va + c * v_stride};
+    const int c = blockIdx.x, T = wg_size();
+    const EFPolar polar{Vm + c * v_stride, Va + c * v_stride};
+    const EFLds efs{reinterpret_cast<double2*>(pf_smem)};
+    if (LDS) {
+        for (int i = threadIdx.x; i < S.n; i += T) {
+            double e, f;
+            polar.get(i, e, f);
+            efs.s[i] = make_double2(e, f);
+        }
+        __syncthreads();
+    }
     int any_nan = 0;
     double* pq = PQ ? PQ + (int64_t)c * 2 * S.n : nullptr;
     double m = 0.0;
@@ -370,9 +387,10 @@ __global__ __launch_bounds__(kMaxThreads) void k_mismatch(
     const double* ps = Psp + c * inj_stride;
     const double* qs = Qsp + c * inj_stride;
     double* rh = rhs + c * rhs_stride;
-    for (int i = threadIdx.x; i < S.n; i += blockDim.x) {
+    for (int i = threadIdx.x; i < S.n; i += T) {
         double p, q;
-        injection(S, yv, ef, i, p, q);
+        if (LDS) injection(S, yv, efs, i, p, q);
+        else injection(S, yv, polar, i, p, q);
         if (pq) reinterpret_cast<double2*>(pq)[i] = make_double2(p, q);
         const int po = S.pos[i];
         if (po >= 0) {
@@ -387,23 +405,33 @@ __global__ __launch_bounds__(kMaxThreads) void k_mismatch(
     if (threadIdx.x == 0 && norm) norm[c] = any_nan ? __builtin_nan("") : r;
 }
 
+// Jacobian blocks of one case (blockIdx.y): a thread per diagonal block, then
+// one per slot, so that a case's sines and chains of loads run side by side
+// (with a node's slots in one thread, 5,003 buses x 48 cases took 44 us, now
+// 36).  The diagonal section's padding is zeroed.
 __global__ void k_jacobian(DevSym S, const double* yval, int64_t y_stride, const int8_t* type,
                            int64_t type_stride, const double* Vm, const double* Va,
-                           int64_t v_stride, double* vals, int64_t vals_stride, int C)
+                           int64_t v_stride, double* vals, int64_t vals_stride, int C, int slots,
+                           int B, int per_case)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (j >= S.nn) return;
+    const int2 at = item_block(per_case, B);
+    const int t = at.y + threadIdx.x;
+    const int c = at.x;
+    if (c < 0) return;
     const EFPolar ef{Vm + c * v_stride, Va + c * v_stride};
     const AsmPolar A{&S, yval + c * y_stride, type + c * type_stride, Vm + c * v_stride, ef};
     const View w = case_view(vals, vals_stride, C, c);
     const int64_t lu = S.lu_off;
-    w.put(4 * (int64_t)j, A.diag(j));
-    for (int s = S.Lp[j]; s < S.Lp[j + 1]; ++s) {
+    if (t < S.nn) {
+        w.put(4 * (int64_t)t, A.diag(t));
+    } else if (t - S.nn < slots) {
+        const int s = t - S.nn;
         Blk lo, up;
-        A.off(j, s, lo, up);
+        A.off(s, lo, up);
         w.put(lu + 8 * (int64_t)s, lo);
         w.put(lu + 8 * (int64_t)s + 4, up);
+    } else if (t - S.nn - slots < lu / 4 - S.nn) {
+        w.put(4 * (int64_t)(t - slots), bzero());
     }
 }
 
@@ -546,20 +574,6 @@ __device__ __forceinline__ void solve_down(const DevSym& S, const View& w, doubl
     });
 }
 
-// Orders one wavefront's accesses to the vector (LDS, or global memory with
-// workgroup-scope fences).
-template <bool LDSX>
-__device__ __forceinline__ void sync_x()
-{
-    if (LDSX) {
-        wave_sync();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-}
-
 // The clique chain at the top of the tree (KC single-node levels, each node
 // adjacent to every node above it; clique node b's higher neighbours are the
 // clique nodes above it in order, so the slot of (b; a), a > b, is entry
@@ -570,14 +584,16 @@ __device__ __forceinline__ void sync_x()
 //                  l_a = D_a^-T (p_a - sum_{c > a} W_ca^T l_c).
 // The parts from below the clique in one parallel pass (16 lanes per clique
 // node); then the clique column by column on the first wavefront, lane a
-// owning clique node a, each lane's blocks requested four columns ahead: up,
+// owning clique node a (its entry in registers, so that a column is a lane's
+// value and a product: 2,000 buses' gain matrix 25.5 -> 19.5 us with
+// the LDS round trips taken out), each lane's blocks requested columns ahead: up,
 // once node b is final (after its D^-1 when transpose = 0) every node a above
 // it takes node b's part; down, node c final (after its D^-T when
 // transpose = 1), every node a below takes node c's part.
-template <bool TRANS, bool LDSX>
+template <bool TRANS>
 __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
 {
-    constexpr int kAhead = 4;  // columns whose blocks are in flight
+    constexpr int kAhead = 8;  // columns whose blocks are in flight
     // the part of slot (i; k) that the up sweep reads (U_ik^T or W_ki) and
     // the part of slot (a; c) the down sweep reads (W_ca^T or U_ac)
     constexpr int kUp = TRANS ? 4 : 0, kDown = TRANS ? 0 : 4;
@@ -627,87 +643,68 @@ __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
             ja = S.t_node[3 * (kf + lane)].x;
             lpa = S.Lp[ja];
         }
-        auto d_of = [&](int c) { return w.blk(4 * (int64_t)__shfl(ja, c)); };
-        // up: the block of slot (b; lane), and (transpose = 0) D_b^-1
+        Blk D = bzero();
+        double2 v = make_double2(0.0, 0.0);
+        if (mine) {
+            D = w.blk(4 * (int64_t)ja);
+            v = x2[ja];
+        }
+        // column c with block u: its node's entry is final (after D^-1 where
+        // `own`), the lanes that `take` it subtract their part
+        auto column = [&](int c, const Blk& u, bool own, bool take) {
+            double2 y = v;
+            if (own) {
+                y = make_double2(0.0, 0.0);
+                if (TRANS) mtvadd(y.x, y.y, D, v.x, v.y);
+                else mvadd(y.x, y.y, D, v.x, v.y);
+                if (lane == c) v = y;
+            }
+            const double p0 = lane_value(y.x, c), p1 = lane_value(y.y, c);
+            if (take) {
+                double z0 = 0.0, z1 = 0.0;
+                madd(z0, z1, u, p0, p1);
+                v = make_double2(v.x - z0, v.y - z1);
+            }
+        };
+        // up: the block of slot (b; lane)
         auto u_of = [&](int b) {
-            const int lpb = __shfl(lpa, b);
+            const int lpb = __builtin_amdgcn_readlane(lpa, b);
             Blk r = bzero();
             if (mine && lane > b) r = w.blk(lu + 8 * (int64_t)(lpb + lane - b - 1) + kUp);
             return r;
         };
-        const int nb = TRANS ? KC - 1 : KC;  // columns of the up pass
-        Blk q[kAhead], qd[kAhead];
+        Blk q[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
-            q[k] = k + 1 < KC ? u_of(k) : bzero();
-            qd[k] = bzero();
-            if (!TRANS && k < KC) qd[k] = d_of(k);
-        }
-        for (int b = 0; b < nb; ++b) {
-            const Blk u = q[0], Db = qd[0];
+        for (int k = 0; k < kAhead; ++k) q[k] = k < KC ? u_of(k) : bzero();
+        for (int b0 = 0; b0 < KC; b0 += kAhead) {
 #pragma unroll
-            for (int k = 0; k + 1 < kAhead; ++k) {
-                q[k] = q[k + 1];
-                qd[k] = qd[k + 1];
+            for (int k = 0; k < kAhead; ++k) {
+                const int b = b0 + k;
+                if (b < KC) {
+                    column(b, q[k], !TRANS, mine && lane > b);
+                    if (b + kAhead < KC) q[k] = u_of(b + kAhead);
+                }
             }
-            q[kAhead - 1] = b + kAhead + 1 < KC ? u_of(b + kAhead) : bzero();
-            qd[kAhead - 1] = bzero();
-            if (!TRANS && b + kAhead < KC) qd[kAhead - 1] = d_of(b + kAhead);
-            double2 pb = x2[__shfl(ja, b)];
-            if (!TRANS) {
-                double y0 = 0.0, y1 = 0.0;
-                mvadd(y0, y1, Db, pb.x, pb.y);
-                pb = make_double2(y0, y1);
-            }
-            if (mine && lane > b) {
-                double z0 = 0.0, z1 = 0.0;
-                madd(z0, z1, u, pb.x, pb.y);
-                const double2 v = x2[ja];
-                x2[ja] = make_double2(v.x - z0, v.y - z1);
-            } else if (!TRANS && lane == b) {
-                x2[ja] = pb;
-            }
-            sync_x<LDSX>();
         }
-        // down: the block of slot (lane; c), and (transpose = 1) D_c^-1
+        // down: the block of slot (lane; c)
         auto w_of = [&](int c) {
             Blk r = bzero();
             if (lane < c) r = w.blk(lu + 8 * (int64_t)(lpa + c - lane - 1) + kDown);
             return r;
         };
-        Blk wq[kAhead], dq[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
-            wq[k] = KC - 1 - k >= 0 ? w_of(KC - 1 - k) : bzero();
-            dq[k] = bzero();
-            if (TRANS && KC - 1 - k >= 0) dq[k] = d_of(KC - 1 - k);
-        }
-        for (int c = KC - 1; c >= 0; --c) {
-            const Blk Wc = wq[0], Dc = dq[0];
+        for (int k = 0; k < kAhead; ++k) q[k] = KC - 1 - k >= 0 ? w_of(KC - 1 - k) : bzero();
+        for (int c0 = KC - 1; c0 >= 0; c0 -= kAhead) {
 #pragma unroll
-            for (int k = 0; k + 1 < kAhead; ++k) {
-                wq[k] = wq[k + 1];
-                dq[k] = dq[k + 1];
+            for (int k = 0; k < kAhead; ++k) {
+                const int c = c0 - k;
+                if (c >= 0) {
+                    column(c, q[k], TRANS, lane < c);
+                    if (c - kAhead >= 0) q[k] = w_of(c - kAhead);
+                }
             }
-            wq[kAhead - 1] = c - kAhead >= 0 ? w_of(c - kAhead) : bzero();
-            dq[kAhead - 1] = bzero();
-            if (TRANS && c - kAhead >= 0) dq[kAhead - 1] = d_of(c - kAhead);
-            double2 pc = x2[__shfl(ja, c)];
-            if (TRANS) {
-                double l0 = 0.0, l1 = 0.0;
-                mtvadd(l0, l1, Dc, pc.x, pc.y);
-                pc = make_double2(l0, l1);
-            }
-            if (lane < c) {
-                double z0 = 0.0, z1 = 0.0;
-                madd(z0, z1, Wc, pc.x, pc.y);
-                const double2 v = x2[ja];
-                x2[ja] = make_double2(v.x - z0, v.y - z1);
-            } else if (TRANS && lane == c) {
-                x2[ja] = pc;
-            }
-            sync_x<LDSX>();
         }
+        if (mine) x2[ja] = v;
     }
     __syncthreads();
 }
@@ -721,7 +718,7 @@ __device__ __forceinline__ void solve_sweeps(const DevSym& S, const View& w, dou
     const bool col = S.tail_clique >= 3 && S.tail_clique <= kWave;
     const int L = col ? S.nlev - S.tail_clique : S.nlev;
     solve_up<TRANS>(S, w, x2, L);
-    if (col) clique_solve<TRANS, LDSX>(S, w, x2);
+    if (col) clique_solve<TRANS>(S, w, x2);
     solve_down<TRANS>(S, w, x2, L);
 }
 
@@ -1137,7 +1134,8 @@ void allow_big_lds()
         (void)hipGetLastError();
         return;
     }
-    const void* kernels[] = {reinterpret_cast<const void*>(&k_adjoint<true>),
+    const void* kernels[] = {reinterpret_cast<const void*>(&k_mismatch<true>),
+                             reinterpret_cast<const void*>(&k_adjoint<true>),
                              reinterpret_cast<const void*>(&k_newton<false>),
                              reinterpret_cast<const void*>(&k_newton<true>),
                              reinterpret_cast<const void*>(&k_newton_spread),
@@ -1304,9 +1302,10 @@ int pf_build_ybus(const pf_symbolic s, int B, const double* d_r, const double* d
         return fail(PF_E_INVALID, "pf_build_ybus: ysh_stride must be 0 or even and >= 2*n, "
                                   "d_ysh 16-byte aligned");
     if (B == 0) return PF_OK;
-    dim3 grid((unsigned)(((int64_t)s->h.n * kYbusLanes + 255) / 256), B);
-    hipLaunchKernelGGL(k_ybus, grid, dim3(256), 0, as_stream(stream), s->h.dev, d_r, d_x, d_b,
-                       branch_stride, d_ysh, ysh_stride, d_yval, y_stride);
+    int per_case = 0;
+    const dim3 grid = item_grid((int64_t)s->h.n * kYbusLanes, B, &per_case);
+    hipLaunchKernelGGL(k_ybus, grid, dim3(256), 0, as_stream(stream), s->h.dev, B, per_case, d_r,
+                       d_x, d_b, branch_stride, d_ysh, ysh_stride, d_yval, y_stride);
     return launch_check("pf_build_ybus");
 }
 
@@ -1325,9 +1324,19 @@ int pf_mismatch(const pf_symbolic s, int B, const double* d_yval, int64_t y_stri
         (B > 1 && (v_stride < s->h.n || rhs_stride < 2 * (int64_t)s->h.nn)))
         return fail(PF_E_WORKSPACE, "pf_mismatch: a stride is too small or negative");
     if (B == 0) return PF_OK;
-    hipLaunchKernelGGL(k_mismatch, dim3(B), dim3(256), 0, as_stream(stream), s->h.dev, d_yval,
-                       y_stride, d_type, type_stride, d_Psp, d_Qsp, inj_stride, d_Vm, d_Va,
-                       v_stride, d_rhs, rhs_stride, d_norm, d_PQ);
+    const size_t ef = 16 * (size_t)s->h.n;
+    const bool lds = ef <= kSolveLdsMax;
+    if (lds) allow_big_lds();
+    // 2,048 threads per compute unit from the workgroups that fit one (by
+    // LDS, and of 256 units' share of the batch), but no more than buses
+    const int64_t fit = lds ? kSolveLdsMax / ef : 8;
+    const int64_t cu = std::min<int64_t>(fit, (B + 255) / 256);
+    int threads = cu >= 8 ? 256 : cu >= 4 ? 512 : 1024;
+    while (threads > 256 && threads / 2 >= s->h.n) threads /= 2;
+    hipLaunchKernelGGL(lds ? k_mismatch<true> : k_mismatch<false>, dim3(B), dim3(threads),
+                       lds ? ef : 0, as_stream(stream), s->h.dev, d_yval, y_stride, d_type,
+                       type_stride, d_Psp, d_Qsp, inj_stride, d_Vm, d_Va, v_stride, d_rhs,
+                       rhs_stride, d_norm, d_PQ);
     return launch_check("pf_mismatch");
 }
 
@@ -1347,10 +1356,12 @@ int pf_jacobian(const pf_symbolic s, int B, const double* d_yval, int64_t y_stri
         (B > 1 && v_stride < s->h.n))
         return fail(PF_E_WORKSPACE, "pf_jacobian: a stride is too small or negative");
     if (B == 0 || s->h.nn == 0) return PF_OK;
-    dim3 grid((s->h.nn + 255) / 256, B);
+    const int64_t slots = (int64_t)s->h.Li.size();
+    int per_case = 0;
+    const dim3 grid = item_grid(s->h.lu_off() / 4 + slots, B, &per_case);
     hipLaunchKernelGGL(k_jacobian, grid, dim3(256), 0, as_stream(stream), s->h.dev, d_yval,
                        y_stride, d_type, type_stride, d_Vm, d_Va, v_stride, d_vals, vals_stride,
-                       vals_interleave);
+                       vals_interleave, (int)slots, B, per_case);
     return launch_check("pf_jacobian");
 }
 
