@@ -114,8 +114,8 @@ typedef struct {
     int32_t tail_nodes;
     int32_t tail_lds_bytes;  /* dynamic LDS per workgroup for the tail      */
     int32_t threads;         /* workgroup size, 0 = chosen per launch       */
-    int32_t tail_clique;     /* top nodes of the tail handled as a dense     */
-                             /* clique (right-looking, one barrier a pivot) */
+    int32_t tail_clique;     /* top nodes of the tail that form a dense      */
+                             /* chain, substituted column by column          */
     int32_t ws_interleave;   /* cases per interleaved group in pf_newton's   */
                              /* workspace (1, 2, 4 or 8)                   */
     int64_t lu_offset;       /* doubles before the LU section (8*ceil(nn/2)) */

@@ -21,8 +21,9 @@
 // node gets a group of g lanes (g from the symbolic's per-level mapping);
 // the lanes of a group split the node's destinations and its descendant
 // list, and combine partial sums with a butterfly over the group.  The top
-// levels whose values fit (the "tail") run in LDS, the top clique of the
-// elimination tree as a dense block.  Outside the tail the Newton and fast
+// levels whose values fit (the "tail") run in LDS, right-looking by operation
+// lists; substitutions take the top clique of the elimination tree column by
+// column in one wavefront's registers.  Outside the tail the Newton and fast
 // decoupled kernels reuse the same LDS for a copy of every bus's (e, f)
 // (mismatch, Jacobian) and for the sweeps' solution vector.
 //
@@ -1654,7 +1655,8 @@ __device__ __forceinline__ void apply_step(const View& w, int64_t rec, bool pv, 
 }
 
 // Backward substitution of the tail from LDS: x_j = y_j - sum U_jk x_k.  The
-// clique goes first, on the first wavefront alone, column-oriented: once x_a
+// clique goes first, on the first wavefront alone, column-oriented (a node per
+// lane in registers as far as the lanes go: 200 buses 136 -> 122 us): once x_a
 // is final, y_k -= U_ka x_a for every clique node k below a.  Every node
 // below the clique then takes the clique's terms, and the levels follow
 // downward, column-oriented too: one thread per slot whose higher neighbour
