@@ -41,7 +41,7 @@ KERNEL_SOURCES = tuple("paper_1811_02512_amd/csrc/" + f for f in (
     "pf_kernels.h", "pf_internal.h", "analyze.cpp"))
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_newton_10k_x256_hbm_traffic.md")
 ALL_LEGS = ("c5", "c1", "c2", "c3", "c4", "fdpf", "graph", "screen", "se")
-HOST_THREADS = 16  # the GPU machine's CPU share; also the oracle's thread pool
+HOST_THREADS = 16  # also the oracle's thread pool
 
 
 def log(*a):
