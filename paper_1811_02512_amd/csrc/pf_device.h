@@ -1030,7 +1030,14 @@ struct TailLds {
     __device__ __forceinline__ void setD(int j, const Blk& v) const
     {
         bstore(d + 4 * j, v);
-        q[j] = 1.0 / (v.a * v.d - v.b * v.c);
+        q[j] = 1.0 / bdet(v);
+    }
+    // the row x of a block times D_j^-1
+    __device__ __forceinline__ double2 over(const double2& x, int j) const
+    {
+        const Blk v = bload(d + 4 * j);
+        const double i = q[j];
+        return make_double2(fma(x.x, v.d, -(x.y * v.c)) * i, fma(x.y, v.a, -(x.x * v.b)) * i);
     }
     __device__ __forceinline__ Blk Dinv(int j) const
     {
@@ -1041,6 +1048,12 @@ struct TailLds {
     __device__ __forceinline__ Blk get(int row, int t) const
     {
         const double2 u = r[row * TS + t], v = r[(row + 1) * TS + t];
+        return {u.x, u.y, v.x, v.y};
+    }
+    // W_t D_j^-1
+    __device__ __forceinline__ Blk W_over(int t, int j) const
+    {
+        const double2 u = over(r[t], j), v = over(r[TS + t], j);
         return {u.x, u.y, v.x, v.y};
     }
     __device__ __forceinline__ void put(int row, int t, const Blk& v) const
@@ -1554,25 +1567,24 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
                 zrow ? reinterpret_cast<const double2*>(L.y) + e.j
                      : L.r + 2 * TS + (hi ? e.a : e.b);
             const double2 u = right[0], v = right[zrow ? 0 : TS];
-            const Blk D = bload(L.d + 4 * e.j);
-            const double i = L.q[e.j];
-            const double t0 = (l.x * D.d - l.y * D.c) * i;
-            const double t1 = (l.y * D.a - l.x * D.b) * i;
-            a0 = fma(-t0, u.x, fma(-t1, zrow ? v.y : v.x, a0));
-            a1 = fma(-t0, u.y, fma(-t1, v.y, a1));
+            const double2 t = L.over(l, e.j);
+            a0 = fma(-t.x, u.x, fma(-t.y, zrow ? v.y : v.x, a0));
+            a1 = fma(-t.x, u.y, fma(-t.y, v.y, a1));
         });
         dst[0] = a0;
         if (!zrow) dst[1] = a1;
         if (!slot) {
             // the pivot's determinant from its two rows
             const double b0 = dpp_peer<0xB1>(a0), b1 = dpp_peer<0xB1>(a1);
-            if (!hi && row == 0) L.q[d] = 1.0 / (a0 * b1 - a1 * b0);
+            if (!hi && row == 0) L.q[d] = 1.0 / bdet({a0, a1, b0, b1});
         }
     };
     // One thread per destination, one form for both kinds, so that a wavefront
     // holding both runs one path: A -= W_a D_j^-1 V_b with A = W_d or the
     // diagonal D_d, and B -= W_b D_j^-1 X with B = V_d, X = V_a, or (a = b)
-    // B = z_d, X = z_j as the first column of a block.
+    // B = z_d, X = z_j as the first column of a block.  The same operations in
+    // the same order as a quad's: which of them a level takes depends on the
+    // workgroup's size, the results (and a zero pivot's verdict) do not.
     auto lane = [&](const uint2& q, const uint2& second, auto&& at2, bool slot) {
         const int d = tail_op(q).d;
         double2* const a0 = slot ? L.r + d : reinterpret_cast<double2*>(L.d) + 2 * d;
@@ -1589,17 +1601,15 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
             const double2* const x0 =
                 slot ? L.r + 2 * TS + e.a : reinterpret_cast<const double2*>(L.y) + e.j;
             const double2* const x1 = slot ? L.r + 3 * TS + e.a : x0;
-            const Blk Wa = L.W(e.a), Wb = L.W(e.b), Vb = L.U(e.b);
-            const Blk X = as_block(*x0, *x1);
-            const Blk Di = L.Dinv(e.j);
-            bmsub(A, Wa, bmul(Di, Vb));
-            bmsub(B, Wb, bmul(Di, X));
+            const Blk Vb = L.U(e.b), X = as_block(*x0, *x1);
+            bmsub(A, L.W_over(e.a, e.j), Vb);
+            bmsub(B, L.W_over(e.b, e.j), X);
         });
         *a0 = make_double2(A.a, A.b);
         *a1 = make_double2(A.c, A.d);
         *b0 = make_double2(B.a, slot ? B.b : B.c);
         if (slot) *b1 = make_double2(B.c, B.d);
-        else L.q[d] = 1.0 / (A.a * A.d - A.b * A.c);
+        else L.q[d] = 1.0 / bdet(A);
     };
     for_tail_updates(S, nT, quad, lane);
     for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {

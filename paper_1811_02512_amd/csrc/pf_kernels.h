@@ -72,10 +72,14 @@ __device__ __forceinline__ void mtvadd(double& y0, double& y1, const Blk& A, dou
     y1 = fma(A.b, x0, fma(A.d, x1, y1));
 }
 
+// Determinant of a 2x2 block, the fused product spelled out: every kernel that
+// takes it gets the same bits, and so the same verdict on a pivot.
+__device__ __forceinline__ double bdet(const Blk& x) { return fma(x.a, x.d, -(x.b * x.c)); }
+
 // Inverse of a 2x2 block; ok = false when the determinant is zero or not finite.
 __device__ __forceinline__ Blk binv(const Blk& x, bool& ok)
 {
-    double det = x.a * x.d - x.b * x.c;
+    double det = bdet(x);
     ok = (det != 0.0) && isfinite(det);
     double r = 1.0 / det;
     return {x.d * r, -x.b * r, -x.c * r, x.a * r};
