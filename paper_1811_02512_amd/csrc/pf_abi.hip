@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <type_traits>
@@ -35,6 +36,61 @@ int hip_check(hipError_t e, const char* what)
 }
 
 int launch_check(const char* what) { return hip_check(hipGetLastError(), what); }
+
+namespace {
+constexpr int64_t kDefaultLds = 64 * 1024;  // static and dynamic, without asking for more
+
+struct LdsLimit {
+    int dev;
+    const void* kernel;
+    int64_t bytes;
+};
+std::mutex g_limits_mu;
+std::vector<LdsLimit> g_limits;  // one entry per device and kernel asked for
+
+int64_t raise_lds(int dev, const void* kernel)
+{
+    int max = 0;
+    hipFuncAttributes fa{};
+    int64_t bytes = 0;
+    if (hipFuncGetAttributes(&fa, kernel) == hipSuccess) {
+        bytes = kDefaultLds - (int64_t)fa.sharedSizeBytes;
+        if (hipDeviceGetAttribute(&max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
+            hipSuccess) {
+            const int64_t dyn = max - (int64_t)fa.sharedSizeBytes;
+            if (dyn > bytes &&
+                hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)dyn) == hipSuccess)
+                bytes = dyn;
+        }
+    }
+    (void)hipGetLastError();
+    return std::max<int64_t>(bytes, 0);
+}
+}  // namespace
+
+int64_t lds_limit(const void* kernel)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    std::lock_guard<std::mutex> lock(g_limits_mu);
+    for (const LdsLimit& l : g_limits)
+        if (l.dev == dev && l.kernel == kernel) return l.bytes;
+    g_limits.push_back({dev, kernel, raise_lds(dev, kernel)});
+    return g_limits.back().bytes;
+}
+
+int compute_units()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        (void)hipGetLastError();
+    return std::max(cus, 1);
+}
 
 int launch_threads(const HostSym& h, int B)
 {

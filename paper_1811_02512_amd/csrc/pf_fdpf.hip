@@ -673,37 +673,18 @@ using FdKernel = void (*)(DevSym, FdLds, NewtonArgs, const double*, int64_t);
 constexpr FdKernel kFdKernels[] = {&k_fdpf<FD_NONE>, &k_fdpf<FD_OVER>, &k_fdpf<FD_OVER_X>,
                                    &k_fdpf<FD_APART>};
 
-// The fast decoupled kernels' dynamic-LDS limit, raised to what the device
-// allows minus their static LDS (failures keep the default limit: 0 here), and
-// the device's compute units.
+// What the current device offers a launch: the dynamic LDS that any of the
+// fast decoupled kernels may ask for, and its compute units.
 struct FdDevice {
-    int64_t dyn = 0;
-    int cus = 1;
-    FdDevice()
-    {
-        int dev = 0, lds_max = 0, mp = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-                hipSuccess &&
-            hipDeviceGetAttribute(&mp, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) {
-            int64_t least = lds_max;
-            for (FdKernel k : kFdKernels) {
-                const void* f = reinterpret_cast<const void*>(k);
-                hipFuncAttributes fa{};
-                int d = 0;
-                if (hipFuncGetAttributes(&fa, f) == hipSuccess)
-                    d = lds_max - (int)fa.sharedSizeBytes;
-                if (d <= 0 || hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  d) != hipSuccess)
-                    d = 0;
-                least = std::min(least, (int64_t)d);
-            }
-            dyn = least;
-            cus = std::max(mp, 1);
-        }
-        (void)hipGetLastError();
-    }
+    int64_t dyn;
+    int cus;
 };
+FdDevice fd_device()
+{
+    FdDevice d{lds_limit(kFdKernels[0]), compute_units()};
+    for (FdKernel k : kFdKernels) d.dyn = std::min(d.dyn, lds_limit(k));
+    return d;
+}
 
 // LDS of B cases (bytes into *bytes).  Everything apart, if the device can
 // keep as many of the launch's workgroups resident as with less LDS; else
@@ -820,10 +801,9 @@ int pf_fdpf(const pf_symbolic s, int B, const double* d_yval, int64_t y_stride,
     if (B == 0) return PF_OK;
     NewtonArgs a{d_yval, y_stride, d_type, type_stride, d_Psp, d_Qsp, inj_stride, d_Vm, d_Va,
                  v_stride, d_ws, ws_stride, tol, max_iter, 0, 1, B, d_iters, d_norm, d_status};
-    static const FdDevice device;
     size_t lds = 0;
     const int threads = launch_threads(s->h, B);
-    const FdLds L = fd_lds(s->h, B, threads, device, &lds);
+    const FdLds L = fd_lds(s->h, B, threads, fd_device(), &lds);
     hipLaunchKernelGGL(kFdKernels[L.mode], dim3(B), dim3(threads), lds, as_stream(stream),
                        s->h.dev, L, a, d_mat, mat_stride);
     return launch_check("pf_fdpf");

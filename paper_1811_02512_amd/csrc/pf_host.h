@@ -26,6 +26,18 @@ extern thread_local std::string g_err;
 int fail(int code, const std::string& msg);
 int hip_check(hipError_t e, const char* what);
 int launch_check(const char* what);
+// The current device: compute units (1 if unknown) and the dynamic LDS a launch
+// of `kernel` may ask for there, raised at the first question to what the
+// device has beside the kernel's static LDS; the default limit where that is
+// refused.  Kept per device and kernel, safe from several threads; errors of
+// the queries are cleared, so that no launch check reports them.
+int compute_units();
+int64_t lds_limit(const void* kernel);
+template <class K>
+int64_t lds_limit(K* kernel)
+{
+    return lds_limit(reinterpret_cast<const void*>(kernel));
+}
 // Workgroup size of the level-scheduled kernels: the symbolic's setting, or
 // by batch size.
 int launch_threads(const pf::HostSym& h, int B);

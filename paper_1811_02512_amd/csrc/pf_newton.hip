@@ -1118,43 +1118,6 @@ int newton_lds(const HostSym& h)
     return std::max(h.tail_lds, h.ef_lds) + (int)pv_mask_bytes(h.n);
 }
 
-// Raises the dynamic-LDS limit of the level-scheduled kernels to what the
-// device allows (160 KB per workgroup on gfx950) minus their static LDS.
-// Failures only keep the default limit; the sticky error is cleared so that
-// it is not reported by the next launch check.
-void allow_big_lds()
-{
-    static bool done = false;
-    if (done) return;
-    done = true;
-    int dev = 0, lds_max = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
-            hipSuccess) {
-        (void)hipGetLastError();
-        return;
-    }
-    const void* kernels[] = {reinterpret_cast<const void*>(&k_mismatch<true>),
-                             reinterpret_cast<const void*>(&k_adjoint<true>),
-                             reinterpret_cast<const void*>(&k_newton<false>),
-                             reinterpret_cast<const void*>(&k_newton<true>),
-                             reinterpret_cast<const void*>(&k_newton_spread),
-                             reinterpret_cast<const void*>(&k_newton_multi_spread),
-                             reinterpret_cast<const void*>(&k_factor<false>),
-                             reinterpret_cast<const void*>(&k_factor<true>),
-                             reinterpret_cast<const void*>(&k_solve<false, true>),
-                             reinterpret_cast<const void*>(&k_solve<true, true>)};
-    for (const void* k : kernels) {
-        hipFuncAttributes fa{};
-        if (hipFuncGetAttributes(&fa, k) == hipSuccess) {
-            const int dyn = lds_max - (int)fa.sharedSizeBytes;
-            if (dyn > 0)
-                (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
-        }
-    }
-    (void)hipGetLastError();
-}
-
 // Workgroups of a one-case Newton launch spread over the device: the
 // symbolic's setting, capped by the workgroups the device keeps resident at
 // once (a cooperative launch needs every one of them at the same time); 0
@@ -1165,6 +1128,7 @@ int spread_blocks(const HostSym& h, int B, int threads, int lds, hipStream_t st)
     if (B != 1 || h.spread <= 1) return 0;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     int dev = 0, cus = 0, per = 0;
+    (void)lds_limit(&k_newton_spread);
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone ||
         hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1180,7 +1144,6 @@ int spread_blocks(const HostSym& h, int B, int threads, int lds, hipStream_t st)
 // The Newton launch of pf_newton and pf_newton_noalloc (arguments checked).
 int newton_launch(const HostSym& h, int B, int C, NewtonArgs a, hipStream_t st, const char* fn)
 {
-    allow_big_lds();
     const int threads = launch_threads(h, B);
     const int lds = newton_lds(h);
     const int G = spread_blocks(h, B, threads, lds, st);
@@ -1201,6 +1164,7 @@ int newton_launch(const HostSym& h, int B, int C, NewtonArgs a, hipStream_t st, 
                                                     (unsigned)lds, st),
                          fn);
     }
+    (void)lds_limit(&k_newton<false>);
     hipLaunchKernelGGL(k_newton<false>, dim3(grid_blocks(B, C)), dim3(threads), lds, st, h.dev,
                        (const CaseDesc*)nullptr, (const int32_t*)nullptr, a);
     return launch_check(fn);
@@ -1272,7 +1236,7 @@ namespace abi {
 void factor_launch(const HostSym& h, int B, double* vals, int64_t stride, int C,
                    int32_t* status, int32_t* pivot, hipStream_t st, bool sym)
 {
-    allow_big_lds();
+    (void)lds_limit(sym ? &k_factor<true> : &k_factor<false>);
     if (sym)
         hipLaunchKernelGGL(k_factor<true>, dim3(grid_blocks(B, C)), dim3(launch_threads(h, B)),
                            h.tail_lds, st, h.dev, vals, stride, C, B, status, pivot);
@@ -1325,8 +1289,7 @@ int pf_mismatch(const pf_symbolic s, int B, const double* d_yval, int64_t y_stri
         return fail(PF_E_WORKSPACE, "pf_mismatch: a stride is too small or negative");
     if (B == 0) return PF_OK;
     const size_t ef = 16 * (size_t)s->h.n;
-    const bool lds = ef <= kSolveLdsMax;
-    if (lds) allow_big_lds();
+    const bool lds = ef <= kSolveLdsMax && (int64_t)ef <= lds_limit(&k_mismatch<true>);
     // 2,048 threads per compute unit from the workgroups that fit one (by
     // LDS, and of 256 units' share of the batch), but no more than buses
     const int64_t fit = lds ? kSolveLdsMax / ef : 8;
@@ -1392,8 +1355,9 @@ int pf_solve(const pf_symbolic s, int B, const double* d_vals, int64_t vals_stri
     const dim3 grid(grid_blocks(B, vals_interleave)), block(launch_threads(s->h, B));
     // the case's vector in LDS when it fits beside nothing else (nn x 16 bytes)
     const size_t xbytes = 16 * (size_t)s->h.nn;
-    const bool lds = xbytes <= kSolveLdsMax;
-    if (lds) allow_big_lds();
+    const bool lds = xbytes <= kSolveLdsMax &&
+                     (int64_t)xbytes <= (transpose ? lds_limit(&k_solve<true, true>)
+                                                   : lds_limit(&k_solve<false, true>));
     auto go = [&](auto kern, size_t shm) {
         hipLaunchKernelGGL(kern, grid, block, shm, as_stream(stream), s->h.dev, d_vals,
                            vals_stride, vals_interleave, B, d_rhs, rhs_stride);
@@ -1551,8 +1515,7 @@ int pf_adjoint(const pf_symbolic s, int B, double* d_ws, int64_t ws_stride,
               d_r, d_x, branch_stride, gx_mode == 0 ? d_gx : nullptr, fuse ? gx_mode : -1};
     const size_t xbytes = 16 * (size_t)h.nn;
     const dim3 grid(grid_blocks(B, C)), block(launch_threads(h, B));
-    if (xbytes <= kSolveLdsMax) {
-        allow_big_lds();
+    if (xbytes <= kSolveLdsMax && (int64_t)xbytes <= lds_limit(&k_adjoint<true>)) {
         hipLaunchKernelGGL(k_adjoint<true>, grid, block, xbytes, as_stream(stream), h.dev, a);
     } else {
         hipLaunchKernelGGL(k_adjoint<false>, grid, block, 0, as_stream(stream), h.dev, a);
@@ -1803,7 +1766,6 @@ int pf_newton_multi(const pf_multi p, const double* d_yval, const int8_t* d_type
         wait = std::max<uint64_t>(wait, sy->h.spread_wait);
     }
     const int threads = multi_threads(p);
-    allow_big_lds();
     const int G = (int)p->syms.size();
     const int nb = (int)p->blocks.size() / 4;
     hipStream_t st = as_stream(stream);
@@ -1812,6 +1774,7 @@ int pf_newton_multi(const pf_multi p, const double* d_yval, const int8_t* d_type
         // keeps them all resident and the stream is not being captured
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         int dev = 0, cus = 0, per = 0;
+        (void)lds_limit(&k_newton_multi_spread);
         const bool queried =
             hipStreamIsCapturing(st, &cs) == hipSuccess && hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) ==
@@ -1832,6 +1795,7 @@ int pf_newton_multi(const pf_multi p, const double* d_yval, const int8_t* d_type
                 "pf_newton_multi");
         }
     }
+    (void)lds_limit(&k_newton<true>);
     hipLaunchKernelGGL(k_newton<true>, dim3(G), dim3(threads), lds, st, none, p->d_desc,
                        p->d_order, a);
     return launch_check("pf_newton_multi");
