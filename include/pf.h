@@ -168,7 +168,12 @@ int pf_symbolic_set_mapping(pf_symbolic sym, const int32_t* lanes_per_level);
  * (0 = none, at most 161792 so that 2 KB of LDS stay for reductions;
  * default 65536).  The Newton kernel's LDS copy of every bus's (e, f)
  * (16 n bytes) is used only when it fits this budget too, so a budget of
- * at most half the LDS lets two workgroups share a CU.  A new budget rebuilds the
+ * at most half the LDS lets two workgroups share a CU.  pf_fdpf keeps its
+ * tails, vectors and (e, f) within a budget below the default; with the
+ * default or more it takes LDS beyond the budget, up to the device's, where
+ * that leaves as many of the launch's own workgroups on a CU.  pf_mismatch,
+ * pf_solve and pf_adjoint hold one vector of 16 bytes a bus in LDS whatever
+ * the budget.  A new budget rebuilds the
  * tail and requires pf_symbolic_upload again.  interleave (1, 2, 4, 8;
  * default 4) is the case grouping of pf_newton's workspace.               */
 int pf_symbolic_set_launch(pf_symbolic sym, int threads, int64_t tail_lds_budget,

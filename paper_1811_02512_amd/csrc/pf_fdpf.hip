@@ -687,9 +687,10 @@ FdDevice fd_device()
 }
 
 // LDS of B cases (bytes into *bytes).  Everything apart, if the device can
-// keep as many of the launch's workgroups resident as with less LDS; else
-// (e, f) over the rest as far as the caller's budget has room for it; else
-// (e, f) in the workspace.
+// keep as many of the launch's workgroups resident as with less LDS (and it
+// fits a budget that the caller set below the default, to leave room for
+// other launches' workgroups); else (e, f) over the rest as far as the
+// caller's budget has room for it; else (e, f) in the workspace.
 FdLds fd_lds(const HostSym& h, int B, int threads, const FdDevice& dev, size_t* bytes)
 {
     const int64_t mask = (((int64_t)pv_mask_bytes(h.n) + 15) / 16) * 2;
@@ -702,7 +703,9 @@ FdLds fd_lds(const HostSym& h, int B, int threads, const FdDevice& dev, size_t* 
     const int64_t want = std::min(((int64_t)B + dev.cus - 1) / dev.cus,
                                   std::max((int64_t)1, (int64_t)2 * kLevelThreads / threads));
     auto resident = [&](int64_t doubles) { return std::min(want, dev.dyn / (8 * doubles + 512)); };
-    const bool all = resident(apart) > 0 && resident(apart) >= resident(less);
+    const bool fits =
+        h.tail_budget >= kDefaultTailBudget || 8 * (apart - mask) <= h.tail_budget;
+    const bool all = fits && resident(apart) > 0 && resident(apart) >= resident(less);
     FdLds L;
     L.wu1 = L.x = L.ef = (int32_t)mask;
     if (all || !h.ef_lds) {

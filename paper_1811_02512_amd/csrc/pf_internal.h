@@ -138,6 +138,9 @@ struct DevSym {
     const int32_t* sub_cum;
 };
 
+// LDS budget of the tail until the caller sets one.
+constexpr int64_t kDefaultTailBudget = 64 * 1024;
+
 struct HostSym {
     int32_t n = 0, m = 0, nn = 0, slack = 0, ordering = 0;
     std::vector<int32_t> from, to;
@@ -151,7 +154,7 @@ struct HostSym {
     std::vector<int32_t> node_info, slot_info, rl, upd;  // packed (int32 view)
     // tail
     int32_t tail_level = 0, tail_nodes = 0, tail_slots = 0, tail_lds = 0, tail_clique = 0;
-    int64_t tail_budget = 64 * 1024;
+    int64_t tail_budget = kDefaultTailBudget;
     std::vector<int32_t> t_node, t_slot, t_rl, t_lev, t_op;
     // upper levels (DevSym); rebuilt with the tail
     int32_t mid_level = 0;
