@@ -25,6 +25,8 @@ class Symbolic:
         self.t = np.ascontiguousarray(t, np.int32)
         self.buf = None
         self.device = None
+        self.plans = 0  # MultiPlans that hold a copy of its device addresses
+        self.kept = []  # replaced device copies: launches or graphs may read them
 
     def __del__(self):
         h = getattr(self, "h", None)
@@ -60,7 +62,18 @@ class Symbolic:
 
     def set_spread(self, workgroups):
         """Workgroups of a one-case Newton launch (0: one workgroup)."""
+        before = self.info.dev_bytes
         B.pf_symbolic_set_spread(self.h, workgroups)
+        if not self.plans:
+            self.renew(before)
+
+    def renew(self, before):
+        """Uploads again, to a new buffer, if the lists that a spread launch
+        reads have grown from `before` bytes (a grid with much fill)."""
+        if self.buf is not None and self.info.dev_bytes != before:
+            self.kept.append(self.buf)
+            self.buf = None
+            self.upload(self.device)
 
     def upload(self, device=None):
         dev = _dev(device)
@@ -164,6 +177,8 @@ class MultiPlan:
     def __init__(self, syms, device=None):
         self.syms = list(syms)
         self.p = B.pf_multi_create([s.h for s in self.syms])
+        for s in set(self.syms):
+            s.plans += 1
         nbytes, self.offs = B.pf_multi_info(self.p, len(self.syms))
         self.buf = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=_dev(device))
         B.pf_multi_upload(self.p, self.buf)
@@ -173,6 +188,8 @@ class MultiPlan:
         if p is not None and B is not None and getattr(B, "lib", None) is not None:
             try:
                 B.pf_multi_destroy(p)
+                for s in set(self.syms):
+                    s.plans -= 1
             except Exception:  # interpreter shutdown
                 pass
             self.p = None
@@ -180,7 +197,10 @@ class MultiPlan:
     def set_spread(self, workgroups):
         """Workgroups of the batch's Newton launch (0: one per case); the
         plan's device table is rebuilt and uploaded again."""
+        own = {s: s.info.dev_bytes for s in self.syms if s.plans == 1}
         B.pf_multi_set_spread(self.p, workgroups)
+        for s, before in own.items():
+            s.renew(before)
         nbytes, _ = B.pf_multi_info(self.p, len(self.syms))
         if self.buf.numel() < nbytes:
             self.buf = torch.empty(nbytes, dtype=torch.uint8, device=self.buf.device)

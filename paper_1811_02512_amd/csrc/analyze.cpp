@@ -151,8 +151,8 @@ size_t HostSym::dev_bytes() const
                                           &level_nodes, &level_g, &node_info, &slot_info, &rl,
                                           &upd,       &t_node,    &t_slot,  &t_rl,
                                           &t_lev,     &t_op,      &from,    &to,     &sub_idx,
-                                          &sub_ptr,   &sub_cum,   &u_node,  &u_slot,  &u_rl,
-                                          &u_upd,     &g_lev,     &g_op,    &g_next};
+                                          &sub_ptr,   &sub_cum,   &up.node, &up.slot, &up.rl,
+                                          &up.upd,    &up.lev,    &up.op,   &up.next};
     size_t total = 0;
     for (auto* a : arrs) total += align256(std::max<size_t>(a->size(), 1) * sizeof(int32_t));
     return total;
@@ -512,7 +512,7 @@ void build_tail(HostSym& s, int64_t budget)
     s.t_lev.clear();
     s.t_op.clear();
     build_subtrees(s);
-    build_upper(s);
+    s.up = build_upper(s, s.want_whole);
     if (K == 0) return;
 
     // clique chain at the top of the tail: level nlev-1-d holds one node
@@ -589,22 +589,39 @@ void build_tail(HostSym& s, int64_t budget)
 // The upper levels of a spread launch, from mid_level on: the tail and below
 // it the levels of at most kMidWidth nodes.  Their updates from lower levels
 // (pulled in one pass), and the right-looking operations of those below the
-// tail.
-void build_upper(HostSym& s)
+// tail.  Unless `whole`, they end where the lists would pass kUpperTerms
+// entries per slot of the factor.
+UpperLists build_upper(const HostSym& s, bool whole)
 {
     const int nlev = (int)s.level_ptr.size() - 1;
+    const int64_t most = kUpperTerms * (int64_t)s.Li.size();
+    // a level's right-looking operations and the updates that it pulls
+    auto terms = [&](int l) {
+        int64_t t = 0;
+        for (int x = s.level_ptr[l]; x < s.level_ptr[l + 1]; ++x) {
+            const int j = s.level_nodes[x];
+            const int64_t d = s.Lp[j + 1] - s.Lp[j];
+            t += d * (d + 1) / 2 + s.Up[s.Lp[j + 1]] - s.Up[s.Lp[j]];
+        }
+        return t;
+    };
+    UpperLists u;
+    u.whole = true;
     int M = s.tail_level;
-    while (M > 0 && s.level_ptr[M] - s.level_ptr[M - 1] <= kMidWidth) --M;
-    s.mid_level = M;
-    for (auto* v : {&s.u_node, &s.u_slot, &s.u_rl, &s.u_upd, &s.g_lev, &s.g_op, &s.g_next})
-        v->clear();
+    int64_t total = 0;
+    while (M > 0 && s.level_ptr[M] - s.level_ptr[M - 1] <= kMidWidth) {
+        total += terms(M - 1);
+        if (total > most) {
+            u.whole = whole;
+            if (!whole) break;
+        }
+        --M;
+    }
+    u.mid_level = M;
     const int x1 = s.level_ptr[M];  // first node (level order) of the upper levels
     // part 0: below the upper levels; part 1: the upper levels below the tail
     auto part = [&](int p) { return s.level[p] <= M ? 0 : s.level[p] <= s.tail_level ? 1 : 2; };
-    s.u_node.reserve(8 * (size_t)(s.nn - x1));
-    s.u_slot.reserve(8 * s.Li.size());
-    s.u_rl.reserve(2 * s.Li.size());
-    s.u_upd.reserve(2 * s.Ua.size());
+    u.node.reserve(8 * (size_t)(s.nn - x1));
     std::vector<int32_t> rest;  // part 1 of a list, appended to its part 0
     auto close = [&](std::vector<int32_t>& list) {
         const int32_t mid = (int32_t)(list.size() / 2);
@@ -614,35 +631,37 @@ void build_upper(HostSym& s)
     };
     for (int x = x1; x < s.nn; ++x) {
         const int j = s.level_nodes[x];
-        const int32_t r0 = (int32_t)(s.u_rl.size() / 2);
+        // the tail alone pulls from the upper levels too (one workgroup)
+        const int parts = part(j) == 2 ? 2 : 1;
+        const int32_t r0 = (int32_t)(u.rl.size() / 2);
         for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q) {
             const int k = part(s.Ri[q]);
-            if (k > 1) continue;
-            auto& list = k ? rest : s.u_rl;
+            if (k >= parts) continue;
+            auto& list = k ? rest : u.rl;
             list.push_back(s.Ri[q]);
             list.push_back(s.Rs[q]);
         }
-        const int32_t r1 = close(s.u_rl);
-        s.u_node.insert(s.u_node.end(), {j, s.perm[j], s.ydiag[j], (int32_t)(s.u_rl.size() / 2),
-                                         r0, r1, s.Lp[j], s.Lp[j + 1]});
+        const int32_t r1 = close(u.rl);
+        u.node.insert(u.node.end(), {j, s.perm[j], s.ydiag[j], (int32_t)(u.rl.size() / 2), r0, r1,
+                                     s.Lp[j], s.Lp[j + 1]});
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) {
-            const int32_t u0 = (int32_t)(s.u_upd.size() / 2);
+            const int32_t u0 = (int32_t)(u.upd.size() / 2);
             for (int v = s.Up[q]; v < s.Up[q + 1]; ++v) {
                 const int k = part(s.owner[s.Ub[v]]);
-                if (k > 1) continue;
-                auto& list = k ? rest : s.u_upd;
+                if (k >= parts) continue;
+                auto& list = k ? rest : u.upd;
                 list.push_back(s.Ua[v]);
                 list.push_back(s.Ub[v]);
             }
-            const int32_t u1 = close(s.u_upd);
-            s.u_slot.insert(s.u_slot.end(), {q, s.perm[j], s.perm[s.Li[q]], s.ylo[q], s.yup[q],
-                                             u0, u1, (int32_t)(s.u_upd.size() / 2)});
+            const int32_t u1 = close(u.upd);
+            u.slot.insert(u.slot.end(), {q, s.perm[j], s.perm[s.Li[q]], s.ylo[q], s.yup[q], u0, u1,
+                                         (int32_t)(u.upd.size() / 2)});
         }
     }
     if (M >= s.tail_level) {  // no level between
-        s.g_op.assign(4, -1);
-        s.g_next.assign(1, 0);
-        return;
+        u.op.assign(4, -1);
+        u.next.assign(1, 0);
+        return u;
     }
     LevelTerms lt((int32_t)s.Li.size(), s.nn);
     for (int l = M; l < s.tail_level && l < nlev; ++l) {
@@ -652,25 +671,26 @@ void build_upper(HostSym& s)
             lt.add_node(j, s.Lp[j], s.Lp[j + 1], [&](int32_t t) { return s.Li[t]; },
                         [&](int32_t k) { return s.Lp[k]; });
         }
-        const int32_t op0 = (int32_t)s.g_next.size();
+        const int32_t op0 = (int32_t)u.next.size();
         // room for the padding; the destination -1 marks it
-        s.g_op.resize(4 * ((size_t)op0 + lt.terms.size() + 63), -1);
-        s.g_next.resize((size_t)op0 + lt.terms.size() + 63, 0);
+        u.op.resize(4 * ((size_t)op0 + lt.terms.size() + 63), -1);
+        u.next.resize((size_t)op0 + lt.terms.size() + 63, 0);
         lt.place(64, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
-            int32_t* r = &s.g_op[4 * ((size_t)op0 + i)];
+            int32_t* r = &u.op[4 * ((size_t)op0 + i)];
             r[0] = d;
             r[1] = q.a;
             r[2] = q.b;
             r[3] = q.j;
-            s.g_next[(size_t)op0 + i] = next;
+            u.next[(size_t)op0 + i] = next;
         });
-        s.g_op.resize(4 * ((size_t)op0 + lt.total));
-        s.g_next.resize((size_t)op0 + lt.total);
-        s.g_lev.insert(s.g_lev.end(), {op0, lt.ns, lt.nd, 0, lt.ns2, lt.nd2, 0, 0});
+        u.op.resize(4 * ((size_t)op0 + lt.total));
+        u.next.resize((size_t)op0 + lt.total);
+        u.lev.insert(u.lev.end(), {op0, lt.ns, lt.nd, 0, lt.ns2, lt.nd2, 0, 0});
     }
     // stands in for the first operation of an empty last level
-    s.g_op.insert(s.g_op.end(), 4, -1);
-    s.g_next.push_back(0);
+    u.op.insert(u.op.end(), 4, -1);
+    u.next.push_back(0);
+    return u;
 }
 
 // The tail's operations by level (layouts documented with DevSym).

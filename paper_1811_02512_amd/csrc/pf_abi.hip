@@ -117,6 +117,17 @@ int newton_interleave(const HostSym& h, int B)
     return C;
 }
 
+int upper_lists(HostSym& h, bool whole, const char* fn)
+{
+    try {
+        if (h.up.whole != whole) h.up = build_upper(h, whole);
+    } catch (const std::exception& ex) {
+        return fail(PF_E_INVALID, std::string(fn) + ": " + ex.what());
+    }
+    h.want_whole = whole;
+    return PF_OK;
+}
+
 bool ready(const pf_symbolic s, const char* fn)
 {
     if (!s) {
@@ -269,6 +280,8 @@ int pf_symbolic_set_spread(pf_symbolic s, int workgroups)
     if (!s) return fail(PF_E_INVALID, "pf_symbolic_set_spread: NULL symbolic");
     if (workgroups < 0 || workgroups > 1024)
         return fail(PF_E_INVALID, "pf_symbolic_set_spread: workgroups must be 0..1024");
+    if (workgroups > 1)
+        if (const int rc = upper_lists(s->h, true, "pf_symbolic_set_spread")) return rc;
     s->h.spread = workgroups;
     return PF_OK;
 }
@@ -300,6 +313,11 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     HostSym& h = s->h;
     pf_info info;
     pf_symbolic_info(s, &info);
+    // a buffer that was sized before a spread was set holds the lists without it
+    if (bytes < info.dev_bytes && h.want_whole) {
+        if (const int rc = upper_lists(h, false, "pf_symbolic_upload")) return rc;
+        pf_symbolic_info(s, &info);
+    }
     if (bytes < info.dev_bytes)
         return fail(PF_E_WORKSPACE, "pf_symbolic_upload: buffer smaller than info.dev_bytes");
     if (reinterpret_cast<uintptr_t>(d_buf) & 255)
@@ -363,15 +381,15 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     d.t_rl = reinterpret_cast<const int2*>(put(h.t_rl));
     d.t_lev = reinterpret_cast<const int4*>(put(h.t_lev));
     d.t_op = reinterpret_cast<const uint2*>(put(h.t_op));
-    d.mid_level = h.mid_level;
-    d.u_slots = (int32_t)(h.u_slot.size() / 8);
-    d.u_node = reinterpret_cast<const int4*>(put(h.u_node));
-    d.u_slot = reinterpret_cast<const int4*>(put(h.u_slot));
-    d.u_rl = reinterpret_cast<const int2*>(put(h.u_rl));
-    d.u_upd = reinterpret_cast<const int2*>(put(h.u_upd));
-    d.g_lev = reinterpret_cast<const int4*>(put(h.g_lev));
-    d.g_op = reinterpret_cast<const int4*>(put(h.g_op));
-    d.g_next = put(h.g_next);
+    d.mid_level = h.up.mid_level;
+    d.u_slots = (int32_t)(h.up.slot.size() / 8);
+    d.u_node = reinterpret_cast<const int4*>(put(h.up.node));
+    d.u_slot = reinterpret_cast<const int4*>(put(h.up.slot));
+    d.u_rl = reinterpret_cast<const int2*>(put(h.up.rl));
+    d.u_upd = reinterpret_cast<const int2*>(put(h.up.upd));
+    d.g_lev = reinterpret_cast<const int4*>(put(h.up.lev));
+    d.g_op = reinterpret_cast<const int4*>(put(h.up.op));
+    d.g_next = put(h.up.next);
     d.sub_cut = h.sub_cut;
     d.sub_roots = h.sub_roots;
     d.sub_idx = put(h.sub_idx);

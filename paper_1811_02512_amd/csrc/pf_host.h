@@ -52,6 +52,9 @@ inline dim3 item_grid(int64_t items, int B, int* per_case)
     *per_case = xcd ? (int)nb : 0;
     return xcd ? dim3((unsigned)lin) : dim3((unsigned)nb, B);
 }
+// Builds the upper levels' lists for the next upload, whole where a launch is
+// to spread the grid (what is on the device stays as it is).
+int upper_lists(pf::HostSym& h, bool whole, const char* fn);
 // Blocks for B cases in groups of C placed one XCD round apart.
 int grid_blocks(int B, int C);
 bool valid_interleave(int C);

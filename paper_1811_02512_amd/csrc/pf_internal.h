@@ -63,7 +63,8 @@ namespace pf {
 //     to the tail; [s0, s1) = its slots
 //   u_slot[t] (2 x int4, slots in the order of their nodes): {s, bus_j, bus_k,
 //     ylo}, {yup, u0, u1, u2}: its update pairs in u_upd, as upd's, [u0, u1)
-//     from below mid_level, [u1, u2) from there to the tail
+//     from below mid_level, [u1, u2) from there to the tail (in both lists
+//     the second part is kept for the tail's nodes alone)
 //   g_lev[2 i], g_lev[2 i + 1] (level mid_level + i): {op0, ns, nd, 0}, {ns2,
 //     nd2, 0, 0}: its operations g_op = {d, a, b, j}, as t_lev's with global
 //     slots and positions, the slots padded to a wavefront with d = -1 where
@@ -141,6 +142,13 @@ struct DevSym {
 // LDS budget of the tail until the caller sets one.
 constexpr int64_t kDefaultTailBudget = 64 * 1024;
 
+// Lists of the upper levels (DevSym's u_* and g_*).
+struct UpperLists {
+    int32_t mid_level = 0;
+    bool whole = false;  // down to the first level wider than kMidWidth
+    std::vector<int32_t> node, slot, rl, upd, lev, op, next;
+};
+
 struct HostSym {
     int32_t n = 0, m = 0, nn = 0, slack = 0, ordering = 0;
     std::vector<int32_t> from, to;
@@ -157,8 +165,8 @@ struct HostSym {
     int64_t tail_budget = kDefaultTailBudget;
     std::vector<int32_t> t_node, t_slot, t_rl, t_lev, t_op;
     // upper levels (DevSym); rebuilt with the tail
-    int32_t mid_level = 0;
-    std::vector<int32_t> u_node, u_slot, u_rl, u_upd, g_lev, g_op, g_next;
+    UpperLists up;
+    bool want_whole = false;  // a launch spreads this grid: build them whole
     // subtrees below a cut level (DevSym); rebuilt with the tail
     int32_t sub_cut = 0, sub_roots = 0;
     std::vector<int32_t> sub_idx, sub_ptr, sub_cum;
@@ -224,9 +232,16 @@ void default_mapping(HostSym& s);
 void build_tail(HostSym& s, int64_t budget);
 void build_tail_ops(HostSym& s);
 // The upper levels' lists: in a spread launch, the highest levels below the
-// tail of at most kMidWidth nodes are factorised right-looking.
+// tail of at most kMidWidth nodes are factorised right-looking.  An operation
+// takes 20 bytes, and in a grid with much fill there are hundreds per slot (a
+// 100 x 100 mesh: 5.7 million, 164 MB and 0.4 s of analysis beside 61 MB and
+// 0.3 s without).  Whole lists are therefore for grids that a launch spreads,
+// where they pay (there 131 -> 11 ms a solve); without, the lists end at
+// kUpperTerms entries per slot of the factor, which the generated grids of up
+// to 20,000 buses do not reach (2.4 at most).
 constexpr int kMidWidth = 600;
-void build_upper(HostSym& s);
+constexpr int kUpperTerms = 4;
+UpperLists build_upper(const HostSym& s, bool whole);
 // Subtrees of the levels below the tail for spread launches: the highest cut
 // at or below the tail level with at least kSubMinRoots roots (none if no
 // such level).

@@ -1640,6 +1640,10 @@ int pf_multi_set_spread(pf_multi p, int workgroups)
         return fail(PF_E_INVALID, "pf_multi_set_spread: workgroups must be 0..65535");
     p->spread = workgroups;
     plan_blocks(p);
+    for (size_t c = 0; c < p->syms.size(); ++c)
+        if (p->counts[c] > 1)
+            if (const int rc = upper_lists(p->syms[c]->h, true, "pf_multi_set_spread"))
+                return rc;
     p->uploaded = false;  // the block table on the device is stale: upload again
     return PF_OK;
 }

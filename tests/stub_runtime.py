@@ -64,14 +64,13 @@ class Info(C.Structure):  # pf_info
 class Sym:
     """A grid's symbolic, in host memory standing for the device's."""
 
-    def __init__(self, g, threads=0, budget=65536, upload=True):
+    def __init__(self, g, threads=0, budget=65536):
         i32 = lambda a: np.ascontiguousarray(a, np.int32)
         f, t = i32(g.f), i32(g.t)
         self.h = C.c_void_p()
         assert lib.pf_analyze(g.n, f.size, vp(f), vp(t), 0, 0, C.byref(self.h)) == 0
         assert lib.pf_symbolic_set_launch(self.h, threads, C.c_int64(budget), 1) == 0
-        if upload:
-            self.upload()
+        assert self.upload() == 0
 
     @property
     def info(self):
