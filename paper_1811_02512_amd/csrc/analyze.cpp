@@ -61,8 +61,9 @@ struct LevelTerms {
     std::vector<int32_t> dst, third, count, at, seq;
     std::vector<uint64_t> keys;
     int32_t slots = 0;
-    // ns: slots (padded), nd: slots and diagonals, total: all positions
-    int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0, total = 0;
+    // ns: slots (padded), nd: slots and diagonals, total: all positions; ls, ld:
+    // slots and diagonals with more than kTailSerial terms
+    int32_t ns = 0, nd = 0, ns2 = 0, nd2 = 0, ls = 0, ld = 0, total = 0;
 
     LevelTerms(int32_t slots_, int32_t nodes)
         : count((size_t)slots_ + nodes, 0),
@@ -96,7 +97,8 @@ struct LevelTerms {
             }
         }
     }
-    // place(position, destination, term, offset of its next term or 0)
+    // place(position, destination, term, offset of its next term or 0, terms
+    // of the destination that follow)
     template <class F>
     void place(int32_t pad, F&& fn)
     {
@@ -109,10 +111,11 @@ struct LevelTerms {
         std::sort(keys.begin(), keys.end());
         for (int32_t i = 0; i < n; ++i) dst[i] = (int32_t)(uint32_t)keys[i];
         int32_t real = 0;
-        ns2 = nd2 = 0;
+        ns2 = nd2 = ls = ld = 0;
         for (int32_t d : dst) {
             real += d < slots;
             (d < slots ? ns2 : nd2) += count[d] > 1;
+            (d < slots ? ls : ld) += count[d] > kTailSerial;
         }
         ns = n > real ? (real + pad - 1) / pad * pad : real;
         nd = ns + n - real;
@@ -135,7 +138,7 @@ struct LevelTerms {
             const int32_t p = k == 0 ? first : k == 1 ? second : third[i] + k - 2;
             const bool last = k + 1 == count[q.d];
             const int32_t nx = k == 0 ? second : third[i] + k - 1;
-            fn(p, q.d < slots ? q.d : q.d - slots, q, last ? 0 : nx - p);
+            fn(p, q.d < slots ? q.d : q.d - slots, q, last ? 0 : nx - p, count[q.d] - 1 - k);
         }
         for (int32_t d : dst) count[d] = 0;
     }
@@ -510,6 +513,7 @@ void build_tail(HostSym& s, int64_t budget)
     s.t_slot.clear();
     s.t_rl.clear();
     s.t_lev.clear();
+    s.tail_longs = 0;
     s.t_op.clear();
     build_subtrees(s);
     s.up = build_upper(s, s.want_whole);
@@ -675,7 +679,7 @@ UpperLists build_upper(const HostSym& s, bool whole)
         // room for the padding; the destination -1 marks it
         u.op.resize(4 * ((size_t)op0 + lt.terms.size() + 63), -1);
         u.next.resize((size_t)op0 + lt.terms.size() + 63, 0);
-        lt.place(64, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
+        lt.place(64, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next, int32_t) {
             int32_t* r = &u.op[4 * ((size_t)op0 + i)];
             r[0] = d;
             r[1] = q.a;
@@ -717,14 +721,17 @@ void build_tail_ops(HostSym& s)
             lt.add_node(x - x0, slot0(x - x0), slot1(x - x0), high, slot0);
         const size_t op0 = s.t_op.size() / 2;
         s.t_op.resize(s.t_op.size() + 2 * lt.terms.size());
-        lt.place(1, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next) {
-            put(op0 + i, d, q.a, q.b, q.j, next);
+        lt.place(1, [&](int32_t i, int32_t d, const LevelTerms::Term& q, int32_t next,
+                        int32_t left) {
+            put(op0 + i, d, q.a, q.b, q.j, i < lt.nd + lt.ns2 + lt.nd2 ? next : left);
         });
         int32_t* r = &s.t_lev[8 * (size_t)tl];
         r[0] = (int32_t)op0;
         r[1] = lt.ns;
         r[2] = lt.nd;
         r[3] = lt.ns2 | lt.nd2 << 16;
+        r[6] = lt.ls | lt.ld << 16;
+        s.tail_longs |= lt.ls + lt.ld > 0;
     }
     // backward: the slots whose higher neighbour is on the level and below
     // the clique, by that neighbour; S(j) lies on one path to the root, so a

@@ -375,6 +375,7 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     d.tail_slots = h.tail_slots;
     d.tail_lds = h.tail_lds;
     d.tail_clique = h.tail_clique;
+    d.tail_longs = h.tail_longs;
     d.ef_lds = 0;
     d.t_node = reinterpret_cast<const int4*>(put(h.t_node));
     d.t_slot = reinterpret_cast<const int4*>(put(h.t_slot));

@@ -861,19 +861,54 @@ __device__ __forceinline__ TailOp tail_op(const uint2& q)
 
 // The tail's level loops: each lane of a wavefront holds the table entry of
 // one of 64 levels (read back by lane index, where all lanes are active), and
-// a thread's operations of the next kTailAhead levels are requested together
+// a thread's operations of the next four levels are requested together
 // while the current ones run (a level takes less time than a load that misses
-// L1), an absent one's place taken by the level's first.
-constexpr int kTailAhead = 4;
+// L1), an absent one's place taken by the level's first.  The form for tails
+// with long destinations looks one level ahead, for its code's size: with four
+// the Newton kernel had 192 instead of 138 KB of it, and the ordinary form ran
+// 1 to 2% slower beside it.
+constexpr int tail_ahead(bool longs) { return longs ? 1 : 4; }
+
+// Walks a tail destination's operations: its first, its second (at `at`) and
+// further ones up to kTailSerial.
+template <class F>
+__device__ __forceinline__ void tail_terms(const DevSym& S, const uint2& first,
+                                           const uint2& second, int at, F&& term)
+{
+    TailOp e = tail_op(first);
+    term(e);
+    if (!e.next) return;
+    e = tail_op(second);
+    term(e);
+    if (!e.next) return;
+    at += e.next;
+    for (int k = 2; k < kTailSerial; ++k, ++at) {
+        e = tail_op(S.t_op[at]);
+        term(e);
+        if (!e.next) return;
+    }
+}
+
+// The operations of a long destination after those, `lanes` of them at a time:
+// runs term(op) for this lane's (lane < lanes); second at `at`.
+template <class F>
+__device__ __forceinline__ void tail_rest(const DevSym& S, int at, int lane, int lanes, F&& term)
+{
+    const int third = at + tail_op(S.t_op[at]).next;
+    const int end = third + tail_op(S.t_op[third]).next + 1;
+    for (int p = third + kTailSerial - 2 + lane; p < end; p += lanes) term(tail_op(S.t_op[p]));
+}
 
 // Runs fn(op) for the backward operations of the tail levels [0, nt),
 // downward, one thread each, or with FWD, fn(op, second, index of second) for
 // the updates of diagonals, upward, one thread per destination (second: its
-// second term on the level, if op.next says that there is one); a workgroup
-// barrier after every level.
-template <bool FWD, class F>
-__device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
+// second term on the level, if op.next says that there is one), then, by
+// wavefronts, with LONG, rest(d, index of second) for what long destinations d
+// have left; a workgroup barrier after every level.
+template <bool FWD, bool LONG, class F, class R>
+__device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn, R&& rest)
 {
+    constexpr int ahead = tail_ahead(LONG);
     const int T = wg_size();
     struct Head {
         int op0, n, two, n2;  // first operation, count; the same of second ones
@@ -881,12 +916,14 @@ __device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
     for (int i0 = 0; i0 < nt; i0 += kWave) {
         const int m = nt - i0 < kWave ? nt - i0 : kWave;
         Head mine{0, 0, 0, 0};
+        int longs = 0;
         {
             const int l = threadIdx.x & (kWave - 1);
             const int i = i0 + (l < m ? l : m - 1);
             const int4 h = S.t_lev[FWD ? 2 * i : 2 * (nt - 1 - i) + 1];
             if (FWD) mine = {h.x + h.y, h.z - h.y, h.x + h.z + (h.w & 0xffff), h.w >> 16};
             else mine = {h.x, h.y, 0, 0};
+            if (LONG) longs = S.t_lev[2 * i + 1].z >> 16;
         }
         auto head = [&](int l) {
             const int k = l < m ? l : m - 1;
@@ -901,32 +938,38 @@ __device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
             if constexpr (FWD) fn(q, r, h.two + t);
             else fn(q);
         };
-        uint2 q[kTailAhead], r[kTailAhead];
+        uint2 q[ahead], r[ahead];
 #pragma unroll
-        for (int k = 0; k < kTailAhead; ++k) {
+        for (int k = 0; k < ahead; ++k) {
             const Head h = head(k);
             q[k] = first(h, threadIdx.x);
             if (FWD) r[k] = second(h, threadIdx.x);
         }
-        for (int i = 0; i < m; i += kTailAhead) {
-            uint2 qn[kTailAhead], rn[kTailAhead];
+        for (int i = 0; i < m; i += ahead) {
+            uint2 qn[ahead], rn[ahead];
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
-                const Head h = head(i + k + kTailAhead);
+            for (int k = 0; k < ahead; ++k) {
+                const Head h = head(i + k + ahead);
                 qn[k] = first(h, threadIdx.x);
                 if (FWD) rn[k] = second(h, threadIdx.x);
             }
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
+            for (int k = 0; k < ahead; ++k) {
                 if (i + k >= m) break;
                 const Head h = head(i + k);
                 if ((int)threadIdx.x < h.n) go(h, threadIdx.x, q[k], r[k]);
                 for (int t = threadIdx.x + T; t < h.n; t += T)
                     go(h, t, first(h, t), FWD ? second(h, t) : make_uint2(0, 0));
                 __syncthreads();
+                if constexpr (LONG) {
+                    const int nl = __builtin_amdgcn_readlane(longs, i + k);
+                    for (int t = (int)threadIdx.x / kWave; t < nl; t += T / kWave)
+                        rest(tail_op(first(h, t)).d, h.two + t);
+                    if (nl > 0) __syncthreads();
+                }
             }
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
+            for (int k = 0; k < ahead; ++k) {
                 q[k] = qn[k];
                 if (FWD) r[k] = rn[k];
             }
@@ -937,10 +980,14 @@ __device__ __forceinline__ void for_tail_ops(const DevSym& S, int nt, F&& fn)
 // Runs the right-looking updates of the tail levels [0, nt), upward, with a
 // workgroup barrier after every level: quad(op, second, index of second, slot)
 // with four lanes per destination on levels that a quarter of the workgroup's
-// threads cover, else lane(same) with one thread per destination.
-template <class Q, class F>
-__device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& quad, F&& lane)
+// threads cover, else lane(same) with one thread per destination; then, by
+// wavefronts, with LONG, rest(d, index of second, slot) for what long
+// destinations d have left.
+template <bool LONG, class Q, class F, class R>
+__device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& quad, F&& lane,
+                                                 R&& rest)
 {
+    constexpr int ahead = tail_ahead(LONG);
     const int T = wg_size(), nq = T >> 2;
     const int lq = (int)threadIdx.x >> 2;
     struct Head {
@@ -957,9 +1004,12 @@ __device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& qu
     for (int i0 = 0; i0 < nt; i0 += kWave) {
         const int m = nt - i0 < kWave ? nt - i0 : kWave;
         int4 mine;
+        int longs = 0;
         {
             const int l = threadIdx.x & (kWave - 1);
-            mine = S.t_lev[2 * (i0 + (l < m ? l : m - 1))];
+            const int i = i0 + (l < m ? l : m - 1);
+            mine = S.t_lev[2 * i];
+            if (LONG) longs = S.t_lev[2 * i + 1].z;
         }
         auto head = [&](int l) {
             const int k = l < m ? l : m - 1;
@@ -969,23 +1019,23 @@ __device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& qu
         };
         // this thread's destination on a level
         auto mine_of = [&](const Head& h) { return h.n <= nq ? lq : (int)threadIdx.x; };
-        uint2 q[kTailAhead], r[kTailAhead];
+        uint2 q[ahead], r[ahead];
 #pragma unroll
-        for (int k = 0; k < kTailAhead; ++k) {
+        for (int k = 0; k < ahead; ++k) {
             const Head h = head(k);
             q[k] = S.t_op[h.one(mine_of(h))];
             r[k] = S.t_op[h.two(mine_of(h))];
         }
-        for (int i = 0; i < m; i += kTailAhead) {
-            uint2 qn[kTailAhead], rn[kTailAhead];
+        for (int i = 0; i < m; i += ahead) {
+            uint2 qn[ahead], rn[ahead];
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
-                const Head h = head(i + k + kTailAhead);
+            for (int k = 0; k < ahead; ++k) {
+                const Head h = head(i + k + ahead);
                 qn[k] = S.t_op[h.one(mine_of(h))];
                 rn[k] = S.t_op[h.two(mine_of(h))];
             }
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
+            for (int k = 0; k < ahead; ++k) {
                 if (i + k >= m) break;
                 const Head h = head(i + k);
                 const int t = mine_of(h);
@@ -998,9 +1048,18 @@ __device__ __forceinline__ void for_tail_updates(const DevSym& S, int nt, Q&& qu
                              u < h.ns);
                 }
                 __syncthreads();
+                if constexpr (LONG) {
+                    const int nl = __builtin_amdgcn_readlane(longs, i + k);
+                    const int ls = nl & 0xffff, all = ls + (nl >> 16);
+                    for (int u = (int)threadIdx.x / kWave; u < all; u += T / kWave) {
+                        const int x = u < ls ? u : h.ns + u - ls;
+                        rest(tail_op(S.t_op[h.one(x)]).d, h.two(x), u < ls);
+                    }
+                    if (all > 0) __syncthreads();
+                }
             }
 #pragma unroll
-            for (int k = 0; k < kTailAhead; ++k) {
+            for (int k = 0; k < ahead; ++k) {
                 q[k] = qn[k];
                 r[k] = rn[k];
             }
@@ -1533,21 +1592,6 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
     }
     __syncthreads();
     if (K == 0) return;
-    // The terms of a destination from its first operation on.
-    auto terms = [&](const uint2& q, const uint2& second, auto&& at2, auto&& term) {
-        TailOp e = tail_op(q);
-        term(e);
-        if (!e.next) return;
-        e = tail_op(second);
-        term(e);
-        if (!e.next) return;
-        int at = at2();
-        do {
-            at += e.next;
-            e = tail_op(S.t_op[at]);
-            term(e);
-        } while (e.next);
-    };
     // A quad of lanes per destination, a row of the result each: lanes 0 and
     // 1 the rows of W_d -= W_a D_j^-1 V_b (or of the diagonal), lanes 2 and 3
     // those of V_d -= W_b D_j^-1 V_a (or the entries of z_d -= W_a D_j^-1
@@ -1555,28 +1599,49 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
     // block.
     const int row = (int)threadIdx.x & 1;
     const bool hi = ((int)threadIdx.x & 2) != 0;
-    auto quad = [&](const uint2& q, const uint2& second, auto&& at2, bool slot) {
-        const int d = tail_op(q).d;
-        const bool zrow = hi && !slot;
-        double* const dst = slot ? reinterpret_cast<double*>(L.r + (2 * hi + row) * TS + d)
-                                 : hi ? L.y + 2 * d + row : L.d + 4 * d + 2 * row;
-        double a0 = dst[0], a1 = dst[1];
-        terms(q, second, at2, [&](const TailOp& e) {
-            const double2 l = L.r[row * TS + (hi ? e.b : e.a)];
-            const double2* const right =
-                zrow ? reinterpret_cast<const double2*>(L.y) + e.j
-                     : L.r + 2 * TS + (hi ? e.a : e.b);
-            const double2 u = right[0], v = right[zrow ? 0 : TS];
-            const double2 t = L.over(l, e.j);
-            a0 = fma(-t.x, u.x, fma(-t.y, zrow ? v.y : v.x, a0));
-            a1 = fma(-t.x, u.y, fma(-t.y, v.y, a1));
-        });
+    // this lane's first entry of destination d
+    auto target = [&](int d, bool slot) {
+        return slot ? reinterpret_cast<double*>(L.r + (2 * hi + row) * TS + d)
+                    : hi ? L.y + 2 * d + row : L.d + 4 * d + 2 * row;
+    };
+    auto take = [&](const TailOp& e, bool zrow, double& a0, double& a1) {
+        const double2 l = L.r[row * TS + (hi ? e.b : e.a)];
+        const double2* const right = zrow ? reinterpret_cast<const double2*>(L.y) + e.j
+                                          : L.r + 2 * TS + (hi ? e.a : e.b);
+        const double2 u = right[0], v = right[zrow ? 0 : TS];
+        const double2 t = L.over(l, e.j);
+        a0 = fma(-t.x, u.x, fma(-t.y, zrow ? v.y : v.x, a0));
+        a1 = fma(-t.x, u.y, fma(-t.y, v.y, a1));
+    };
+    auto finish = [&](double* dst, int d, bool slot, double a0, double a1) {
         dst[0] = a0;
-        if (!zrow) dst[1] = a1;
+        if (slot || !hi) dst[1] = a1;
         if (!slot) {
             // the pivot's determinant from its two rows
             const double b0 = dpp_peer<0xB1>(a0), b1 = dpp_peer<0xB1>(a1);
             if (!hi && row == 0) L.q[d] = 1.0 / bdet({a0, a1, b0, b1});
+        }
+    };
+    auto quad = [&](const uint2& q, const uint2& second, auto&& at2, bool slot) {
+        const int d = tail_op(q).d;
+        double* const dst = target(d, slot);
+        double a0 = dst[0], a1 = dst[1];
+        tail_terms(S, q, second, at2(), [&](const TailOp& e) { take(e, hi && !slot, a0, a1); });
+        finish(dst, d, slot, a0, a1);
+    };
+    // A long destination's rest: a quad of the wavefront per operation, their
+    // sums added up over the quads.
+    auto rest = [&](int d, int at2, bool slot) {
+        double a0 = 0.0, a1 = 0.0;
+        tail_rest(S, at2, ((int)threadIdx.x & (kWave - 1)) >> 2, kWave / 4,
+                  [&](const TailOp& e) { take(e, hi && !slot, a0, a1); });
+        for (int k = 4; k < kWave; k *= 2) {
+            a0 += __shfl_xor(a0, k, kWave);
+            a1 += __shfl_xor(a1, k, kWave);
+        }
+        if (((int)threadIdx.x & (kWave - 1)) < 4) {
+            double* const dst = target(d, slot);
+            finish(dst, d, slot, dst[0] + a0, dst[1] + a1);
         }
     };
     // One thread per destination, one form for both kinds, so that a wavefront
@@ -1597,7 +1662,7 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
         const double2 u = *a0, v = *a1;
         Blk A = {u.x, u.y, v.x, v.y};
         Blk B = as_block(*b0, *b1);
-        terms(q, second, at2, [&](const TailOp& e) {
+        tail_terms(S, q, second, at2(), [&](const TailOp& e) {
             const double2* const x0 =
                 slot ? L.r + 2 * TS + e.a : reinterpret_cast<const double2*>(L.y) + e.j;
             const double2* const x1 = slot ? L.r + 3 * TS + e.a : x0;
@@ -1611,7 +1676,11 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
         if (slot) *b1 = make_double2(B.c, B.d);
         else L.q[d] = 1.0 / bdet(A);
     };
-    for_tail_updates(S, nT, quad, lane);
+    // only a tail with long destinations takes the form that looks for them (a
+    // path of 150 buses, no long ones: 356 us, in that form 366; 198 leaves on
+    // one bus: 314 us walked one after the other, so 222)
+    if (S.tail_longs) for_tail_updates<true>(S, nT, quad, lane, rest);
+    else for_tail_updates<false>(S, nT, quad, lane, rest);
     for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
         if (it < K) {
             const Blk D = bload(L.d + 4 * it);
@@ -1747,13 +1816,13 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         }
         __syncthreads();
     }
-    for_tail_ops<false>(S, nT - KC, [&](const uint2& q) {
+    for_tail_ops<false, false>(S, nT - KC, [&](const uint2& q) {
         const TailOp o = tail_op(q);
         const Blk U = L.U(o.a);
         const double2 x = L.yv(o.b), y = L.yv(o.d);
         L.sety(o.d, fma(-U.a, x.x, fma(-U.b, x.y, y.x)),
                fma(-U.c, x.x, fma(-U.d, x.y, y.y)));
-    });
+    }, [](int, int) {});
     if (xs) {
         double2 xr[4];
 #pragma unroll

@@ -270,21 +270,25 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
     // the factorisation's lists carry the rhs terms z_k -= w_kj (z_j / d_j)
     const int nT = S.nlev - S.tail_level, KC = S.tail_clique;
     const int kf = S.tail_nodes - KC;
-    for_tail_ops<true>(S, nT - KC, [&](const uint2& q, const uint2& second, int at) {
-        TailOp o = tail_op(q);
-        const int d = o.d;
-        double z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], sy[d]);
-        if (o.next) {
-            o = tail_op(second);
+    auto one = [&](const uint2& q, const uint2& second, int at) {
+        const int d = tail_op(q).d;
+        double z = sy[d];
+        tail_terms(S, q, second, at, [&](const TailOp& o) {
             z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
-            while (o.next) {
-                at += o.next;
-                o = tail_op(S.t_op[at]);
-                z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
-            }
-        }
+        });
         sy[d] = z;
-    });
+    };
+    auto rest = [&](int d, int at) {
+        const int lane = (int)threadIdx.x & (kWave - 1);
+        double z = 0.0;
+        tail_rest(S, at, lane, kWave, [&](const TailOp& o) {
+            z = fma(-t.wu[o.a].x, t.d[o.j] * sy[o.j], z);
+        });
+        z = gsum(z, kWave);
+        if (lane == 0) sy[d] += z;
+    };
+    if (S.tail_longs) for_tail_ops<true, true>(S, nT - KC, one, rest);
+    else for_tail_ops<true, false>(S, nT - KC, one, rest);
     for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) sy[jl] *= t.d[jl];
     if (KC > 0 && threadIdx.x < kWave) {
         // the clique (every node adjacent to all above it) column by column
@@ -372,10 +376,10 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         }
         __syncthreads();
     }
-    for_tail_ops<false>(S, nT - KC, [&](const uint2& q) {
+    for_tail_ops<false, false>(S, nT - KC, [&](const uint2& q) {
         const TailOp o = tail_op(q);
         sy[o.d] = fma(-t.wu[o.a].y, sy[o.b], sy[o.d]);
-    });
+    }, [](int, int) {});
     __syncthreads();
     for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x)
         x[S.t_node[3 * jl].x] = sy[jl];

@@ -47,11 +47,15 @@ namespace pf {
 //     every destination's first, ns on slots (W_d -= W_a D_j^-1 V_b, V_d -=
 //     W_b D_j^-1 V_a), to nd on diagonals and the rhs (a = b: D_d -= W_a
 //     D_j^-1 V_a, z_d -= W_a D_j^-1 z_j); then the second ones of the first
-//     ns2 slots and the first nd2 diagonals, then further ones; next > 0: the
-//     destination's next operation is that many places on
-//   t_lev[2 l + 1] = {op0, nb, 0, 0}: the backward operations of level l
-//     below the clique: x_d -= U_a x_b for every slot a whose higher
-//     neighbour b is on the level (d owns the slot)
+//     ns2 slots and the first nd2 diagonals, then further ones, each
+//     destination's together; next > 0 in a first or second one: the
+//     destination's next operation is that many places on, in a further one:
+//     as many more follow.  Destinations with more operations come first.
+//   t_lev[2 l + 1] = {op0, nb, ls | ld << 16, 0}: the backward operations of
+//     level l below the clique: x_d -= U_a x_b for every slot a whose higher
+//     neighbour b is on the level (d owns the slot); and the destinations of
+//     the level with more than kTailSerial operations: the first ls slots
+//     and the first ld diagonals (tail_longs: whether any level has some)
 // Upper levels [mid_level, nlev) of a launch spread over several workgroups:
 // all nodes' diagonals, rhs entries and slots there take the updates of lower
 // levels in one pass; then the levels below the tail (the narrow ones) are
@@ -105,7 +109,7 @@ struct DevSym {
     const int2* upd;         // n_upd
     // LDS tail
     int32_t tail_level, tail_nodes, tail_slots, tail_lds;
-    int32_t tail_clique;
+    int32_t tail_clique, tail_longs;
     int32_t ef_lds;  // bytes of the LDS copy of (e, f) per bus the Newton mismatch reads, 0 = none
     const int4* t_node;      // 3 K
     const int4* t_slot;      // TS
@@ -162,6 +166,7 @@ struct HostSym {
     std::vector<int32_t> node_info, slot_info, rl, upd;  // packed (int32 view)
     // tail
     int32_t tail_level = 0, tail_nodes = 0, tail_slots = 0, tail_lds = 0, tail_clique = 0;
+    int32_t tail_longs = 0;
     int64_t tail_budget = kDefaultTailBudget;
     std::vector<int32_t> t_node, t_slot, t_rl, t_lev, t_op;
     // upper levels (DevSym); rebuilt with the tail
@@ -214,6 +219,12 @@ struct HostSym {
 // determinant per node (an odd count of the latter padded to 16 bytes).
 inline int64_t tail_bytes(int64_t K, int64_t TS) { return TS * 64 + K * 48 + (K + 1) / 2 * 16; }
 
+// Operations of a tail destination that one thread or quad takes one after the
+// other; what follows is shared by a wavefront.  The generated grids have at
+// most 4 on a destination and level; one wavefront's share costs a barrier and
+// a sum over its lanes.
+constexpr int kTailSerial = 8;
+
 // Tail nodes and slots have 12-bit local indices (t_op); the largest LDS
 // budget holds fewer of either.
 constexpr int64_t kTailIndexMax = 4095;
@@ -233,12 +244,12 @@ void build_tail(HostSym& s, int64_t budget);
 void build_tail_ops(HostSym& s);
 // The upper levels' lists: in a spread launch, the highest levels below the
 // tail of at most kMidWidth nodes are factorised right-looking.  An operation
-// takes 20 bytes, and in a grid with much fill there are hundreds per slot (a
-// 100 x 100 mesh: 5.7 million, 164 MB and 0.4 s of analysis beside 61 MB and
-// 0.3 s without).  Whole lists are therefore for grids that a launch spreads,
-// where they pay (there 131 -> 11 ms a solve); without, the lists end at
-// kUpperTerms entries per slot of the factor, which the generated grids of up
-// to 20,000 buses do not reach (2.4 at most).
+// takes 20 bytes, and in a grid with much fill there are tens to hundreds per
+// slot (a 100 x 100 mesh: 5.7 million, 113 MB and 0.4 s of analysis beside 69
+// MB and 0.2 s without).  Whole lists are therefore for grids that a launch
+// spreads, where they pay (there 131 -> 11 ms a solve); without, the lists end
+// at kUpperTerms entries per slot of the factor, which the generated grids of
+// up to 20,000 buses do not reach (at most 2.2 with a tail, 3.1 without).
 constexpr int kMidWidth = 600;
 constexpr int kUpperTerms = 4;
 UpperLists build_upper(const HostSym& s, bool whole);
