@@ -15,17 +15,19 @@ LIB = os.path.join(PKG, "libpf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 ARCH = "gfx950"
-# HIP translation units: shared host ABI, Newton path, fast decoupled, state estimation
-KERNEL_FILES = ("pf_abi.hip", "pf_newton.hip", "pf_fdpf.hip", "pf_se.hip")
+# HIP translation units: shared host ABI, Newton path, separate Jacobian and
+# factorisation, fast decoupled, state estimation
+KERNEL_FILES = ("pf_abi.hip", "pf_newton.hip", "pf_steps.hip", "pf_fdpf.hip", "pf_se.hip")
 # Packed fp32 instructions are kept off for every device compile.
-# DEVICE_OPT: the iteration kernels' loops would have the sine's constants
-# hoisted out of them, some 30 vector registers for the whole iteration;
-# without that pass the fast decoupled kernels (111 to 115 registers, else 128
-# and spills) keep two workgroups per compute unit, and Newton's need 227
-# instead of 251.
 DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-Xclang", "-target-feature", "-Xclang",
                 "-packed-fp32-ops"]
-DEVICE_OPT = ["-mllvm", "-disable-machine-licm"]
+# The iteration kernels' loops would have the sine's constants hoisted out of
+# them, some 30 vector registers for the whole iteration; without that pass the
+# fast decoupled kernels (114 to 118 registers, else 128 and spills) keep two
+# workgroups per compute unit, and Newton's run 1% faster (200 buses, 487 x 33).
+# The other files keep the pass: the factorisation of a band of 500 buses takes
+# 6.6 ms with it and 7.2 without, a Jacobian row of 200 entries 58 and 63 us.
+FILE_OPT = {f: ["-mllvm", "-disable-machine-licm"] for f in ("pf_newton.hip", "pf_fdpf.hip")}
 USAGE = "-Rpass-analysis=kernel-resource-usage"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-I", INCLUDE, "-I", CSRC]
 
@@ -72,8 +74,8 @@ def build(verbose: bool = False) -> str:
         objs.append(obj)
     for src in KERNEL_FILES:
         obj = os.path.join(BUILD, src + ".o")
-        _run([HIPCC, *COMMON, *DEVICE_FLAGS, *DEVICE_OPT, USAGE, "-c", os.path.join(CSRC, src),
-              "-o", obj])
+        _run([HIPCC, *COMMON, *DEVICE_FLAGS, *FILE_OPT.get(src, []), USAGE, "-c",
+              os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", *DEVICE_FLAGS, "-o", tmp, *objs])
