@@ -73,24 +73,32 @@ __device__ __forceinline__ double2 fd_entries(const DevSym& S, int t0, int t1, i
 //   w_kj = a_kj - sum_i w_ki u_ij (k in S(j)),  u_jk = w_kj / d_j.
 // Bound by its chains of loads (list, then factor entries), so four terms are
 // requested at a time, the next four's indices under them: both matrices of
-// 384 cases of 2,000 buses 183 -> 155 us.
+// 384 cases of 2,000 buses 183 -> 155 us.  A wavefront without a second term
+// takes the one (a radial grid of 2,000 buses 1,954 us four at a time, 1,792 so).
 __device__ __forceinline__ void fd_factor_node(const DevSym& S, const NodeRec& rec, int lane,
                                                int g, double* m, int* s_bad)
 {
     const int j = rec.a.x;
     double2* sl = reinterpret_cast<double2*>(m + S.fd_lu);
     double ds = 0.0;
-    const int r1 = rec.a.w;
-    for (int r = rec.a.z + lane; r < r1; r += 4 * g) {
-        int at[4];
-        double2 wu[4];
+    const int r0 = rec.a.z + lane, r1 = rec.a.w;
+    if (!__any(r0 + g < r1)) {  // a radial grid's nodes: no lane has a second one
+        if (r0 < r1) {
+            const double2 wu = sl[S.rl[r0].y];
+            ds = wu.x * wu.y;
+        }
+    } else {
+        for (int r = r0; r < r1; r += 4 * g) {
+            int at[4];
+            double2 wu[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) at[k] = S.rl[r + k * g < r1 ? r + k * g : r].y;
+            for (int k = 0; k < 4; ++k) at[k] = S.rl[r + k * g < r1 ? r + k * g : r].y;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) wu[k] = sl[at[k]];
+            for (int k = 0; k < 4; ++k) wu[k] = sl[at[k]];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (r + k * g < r1) ds = fma(wu[k].x, wu[k].y, ds);
+            for (int k = 0; k < 4; ++k)
+                if (r + k * g < r1) ds = fma(wu[k].x, wu[k].y, ds);
+        }
     }
     if (g > 1) ds = gsum(ds, g);
     const double D = m[j] - ds;
