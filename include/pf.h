@@ -159,7 +159,10 @@ int pf_symbolic_export(const pf_symbolic sym, int32_t* perm, int32_t* parent,
                        int32_t* Lp, int32_t* Li);
 /* Thread mapping: lanes per node (1,2,4,...,64) for each level, used by the
  * level-scheduled kernels.  Defaults come from a work model; an autotuner may
- * replace them.  Takes effect at the next pf_symbolic_upload.             */
+ * replace them.  Takes effect at the next pf_symbolic_upload.  On the levels
+ * of the LDS tail pf_solve, pf_adjoint and pf_fdpf_factor alone read it;
+ * a spread launch's factorisation reads it up to its first right-looking
+ * level.                                                                  */
 int pf_symbolic_set_mapping(pf_symbolic sym, const int32_t* lanes_per_level);
 /* Launch shape of the level-scheduled kernels: threads per workgroup (64,
  * 128, 256 or 512; 0 = by batch size: 512 up to 512 cases, else 256) and the LDS

@@ -7,8 +7,10 @@ batch) with HIP events and keeps the fastest setting of:
   * case interleave of the workspace (1, 2, 4, 8),
   * for a single case, the workgroups its launch is spread over (one, or a
     cooperative launch of 16 ... 256 sharing the levels below the LDS tail),
-  * lanes per node for each level class (levels grouped by width), by
-    coordinate descent over {1, 2, 4, ..., 64}.
+  * lanes per node for each class of the levels below the LDS tail (levels
+    grouped by width), by coordinate descent over {1, 2, 4, ..., 64}; the
+    tail's levels run without them in this launch and keep their defaults,
+    which the solves and the adjoint read.
 Every setting computes the same factorisation; the lanes per node only change
 the order in which partial sums are combined, so settings agree to rounding
 and each one is bitwise reproducible.  The tuner never changes the symbolic
@@ -114,7 +116,8 @@ def tune(sym, yval, bus_type, Psp, Qsp, Vm0, Va0, tol=1e-8, max_iter=20, reps=2,
     sym.set_spread(G)
     mapping = base_map.copy()
     best_ms = best[0]
-    classes = level_classes(sym)
+    below = sym.info.nlevels - sym.info.tail_levels
+    classes = [(w, idx[idx < below]) for w, idx in level_classes(sym) if idx.min() < below]
     for _ in range(passes):
         improved = False
         for (lo, hi), idx in classes:
