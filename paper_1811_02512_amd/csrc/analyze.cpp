@@ -490,14 +490,16 @@ void build_tail(HostSym& s, int64_t budget)
     if (budget > 0) {
         while (L > 0) {
             const int l = L - 1;
-            int64_t k2 = K, t2 = TS;
+            int64_t k2 = K, t2 = TS, ops = 0;
             for (int x = s.level_ptr[l]; x < s.level_ptr[l + 1]; ++x) {
                 const int j = s.level_nodes[x];
+                const int64_t d = s.Lp[j + 1] - s.Lp[j];
                 ++k2;
-                t2 += s.Lp[j + 1] - s.Lp[j];
+                t2 += d;
+                ops += d * (d + 1) / 2;
             }
             if (tail_bytes(k2, t2) + pv_mask_bytes(s.n) > budget || t2 > kTailIndexMax ||
-                k2 > kTailIndexMax)
+                k2 > kTailIndexMax || ops > kTailOpsMax)
                 break;
             K = k2;
             TS = t2;

@@ -225,9 +225,12 @@ inline int64_t tail_bytes(int64_t K, int64_t TS) { return TS * 64 + K * 48 + (K 
 // a sum over its lanes.
 constexpr int kTailSerial = 8;
 
-// Tail nodes and slots have 12-bit local indices (t_op); the largest LDS
-// budget holds fewer of either.
+// Tail nodes and slots have 12-bit local indices and offsets within a level's
+// operations 16 bits (t_op).  The largest LDS budget holds fewer of all: 2,528
+// slots, and a level at most 35,000 operations, as a row of d slots lies under
+// a clique of d (d - 1) / 2.
 constexpr int64_t kTailIndexMax = 4095;
+constexpr int64_t kTailOpsMax = 65535;
 
 // LDS bytes of the PV bitmask the Newton kernel keeps after the tail (one bit
 // per bus, whole 64-bit ballot words).
