@@ -149,8 +149,7 @@ struct LevelTerms {
 size_t HostSym::dev_bytes() const
 {
     const std::vector<int32_t>* arrs[] = {&yptr,      &ycol,      &ybr_ptr, &ybr,    &perm,
-                                          &pos,       &Lp,        &Li,      &ylo,    &yup,
-                                          &ydiag,     &Rp,        &Ri,      &Rs,     &level_ptr,
+                                          &pos,       &Lp,        &Li,      &ydiag,  &level_ptr,
                                           &level_nodes, &level_g, &node_info, &slot_info, &rl,
                                           &upd,       &t_node,    &t_slot,  &t_rl,
                                           &t_lev,     &t_op,      &from,    &to,     &sub_idx,
@@ -552,12 +551,12 @@ void build_tail(HostSym& s, int64_t budget)
     int32_t ts = 0;
     for (int j : tnodes)
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) sloc[q] = ts++;
-    s.t_node.assign(12 * (size_t)K, 0);
+    s.t_node.assign(8 * (size_t)K, 0);
     s.t_slot.assign(4 * (size_t)TS, 0);
     int32_t run = 0;
     for (size_t jl = 0; jl < tnodes.size(); ++jl) {
         const int j = tnodes[jl];
-        int32_t* r = &s.t_node[12 * jl];
+        int32_t* r = &s.t_node[8 * jl];
         r[0] = j;
         r[1] = s.perm[j];
         r[2] = s.ydiag[j];
@@ -571,16 +570,11 @@ void build_tail(HostSym& s, int64_t budget)
                 s.t_rl.push_back(s.Rs[q]);
             }
         r[6] = (int32_t)(s.t_rl.size() / 2);
-        for (int pass = 0; pass < 2; ++pass) {  // tail descendants below the clique first
-            for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q) {
-                const int i = s.Ri[q];
-                if (loc[i] >= 0 && in_clique(i) == (pass == 1)) {
-                    s.t_rl.push_back(loc[i]);
-                    s.t_rl.push_back(sloc[s.Rs[q]]);
-                }
+        for (int q = s.Rp[j]; q < s.Rp[j + 1]; ++q)
+            if (in_clique(j) && loc[s.Ri[q]] >= 0 && !in_clique(s.Ri[q])) {
+                s.t_rl.push_back(loc[s.Ri[q]]);
+                s.t_rl.push_back(sloc[s.Rs[q]]);
             }
-            if (pass == 0) r[8] = (int32_t)(s.t_rl.size() / 2);
-        }
         r[7] = (int32_t)(s.t_rl.size() / 2);
         for (int q = s.Lp[j]; q < s.Lp[j + 1]; ++q) {
             int32_t* t = &s.t_slot[4 * (size_t)sloc[q]];
@@ -705,8 +699,8 @@ void build_tail_ops(HostSym& s)
     const int nT = (int)s.level_ptr.size() - 1 - s.tail_level;
     const int K = s.tail_nodes, TS = s.tail_slots, kf = K - s.tail_clique;
     const int x0 = s.level_ptr[s.tail_level];
-    auto slot0 = [&](int jl) { return s.t_node[12 * (size_t)jl + 3]; };
-    auto slot1 = [&](int jl) { return s.t_node[12 * (size_t)jl + 4]; };
+    auto slot0 = [&](int jl) { return s.t_node[8 * (size_t)jl + 3]; };
+    auto slot1 = [&](int jl) { return s.t_node[8 * (size_t)jl + 4]; };
     auto high = [&](int t) { return s.t_slot[4 * (size_t)t + 1]; };
     std::vector<int32_t> own(TS);
     for (int jl = 0; jl < K; ++jl)

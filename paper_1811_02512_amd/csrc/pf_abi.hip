@@ -357,12 +357,7 @@ int pf_symbolic_upload(pf_symbolic s, void* d_buf, size_t bytes, void* stream)
     d.pos = put(h.pos);
     d.Lp = put(h.Lp);
     d.Li = put(h.Li);
-    d.ylo = put(h.ylo);
-    d.yup = put(h.yup);
     d.ydiag = put(h.ydiag);
-    d.Rp = put(h.Rp);
-    d.Ri = put(h.Ri);
-    d.Rs = put(h.Rs);
     d.level_ptr = put(h.level_ptr);
     d.level_nodes = put(h.level_nodes);
     d.level_g = put(h.level_g);

@@ -1578,7 +1578,7 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
         if (par.rank() != 0) return;
         for (int it = threadIdx.x; it < K + TS; it += T) {
             if (it < K) {
-                const int j = S.t_node[3 * it].x;
+                const int j = S.t_node[2 * it].x;
                 L.setD(it, w.blk(4 * (int64_t)j));
                 const double2 z = FWD ? wr.v2(rhs + 2 * (int64_t)j) : make_double2(0.0, 0.0);
                 L.sety(it, z.x, z.y);
@@ -1707,7 +1707,7 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
             w.put(lu + 8 * (int64_t)s + 4, L.U(t));
         }
         for (int jl = threadIdx.x; jl < K; jl += blockDim.x) {
-            const int j = S.t_node[3 * jl].x;
+            const int j = S.t_node[2 * jl].x;
             w.put(4 * (int64_t)j, L.Dinv(jl));
             if (FWD) wr.put2(rhs + 2 * (int64_t)j, L.yv(jl));
         }
@@ -1756,7 +1756,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
     double* const sy = L.y;
     const int kf = K - KC;
     if (KC > 0) {
-        const int c0 = S.t_node[3 * kf].w;
+        const int c0 = S.t_node[2 * kf].w;
         if (KC <= kWave) {
             if (threadIdx.x < kWave) {
                 const int k = threadIdx.x;
@@ -1794,7 +1794,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         __syncthreads();
         // the clique's terms of every node below it
         for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
-            const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
+            const int t0 = S.t_node[2 * jl].w, t1 = S.t_node[2 * jl + 1].x;
             double2 y = L.yv(jl);
             bool more = true;
             for (int t = t1 - 1; more && t >= t0; t -= 4) {  // the clique's are the last ones
@@ -1835,7 +1835,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         for (int r = 0; r < 4; ++r) {
             const int jl = threadIdx.x + r * blockDim.x;
             if (jl < K) {
-                const int4 t0 = S.t_node[3 * jl];
+                const int4 t0 = S.t_node[2 * jl];
                 xs[t0.x] = xr[r];
                 if (UPDATE)
                     apply_step(w, bus_off + 8 * (int64_t)t0.y, type(t0.y), xr[r].x, xr[r].y);
@@ -1843,7 +1843,7 @@ __device__ __forceinline__ void tail_backward(const DevSym& S, const View& w, in
         }
     } else {
         for (int jl = threadIdx.x; jl < K; jl += blockDim.x) {
-            const int4 t0 = S.t_node[3 * jl];
+            const int4 t0 = S.t_node[2 * jl];
             const double x0 = sy[2 * jl], x1 = sy[2 * jl + 1];
             w.put2(rhs + 2 * (int64_t)t0.x, make_double2(x0, x1));
             if (UPDATE) apply_step(w, bus_off + 8 * (int64_t)t0.y, type(t0.y), x0, x1);

@@ -257,7 +257,7 @@ __device__ __forceinline__ void fd_tail_load(const DevSym& S, const double* m, c
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
     for (int i = threadIdx.x; i < S.tail_slots; i += blockDim.x) t.wu[i] = sl[S.t_slot[i].x];
-    for (int i = threadIdx.x; i < S.tail_nodes; i += blockDim.x) t.d[i] = m[S.t_node[3 * i].x];
+    for (int i = threadIdx.x; i < S.tail_nodes; i += blockDim.x) t.d[i] = m[S.t_node[2 * i].x];
 }
 
 // Forward substitution of the tail levels in LDS: each tail node first takes
@@ -269,7 +269,7 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
 {
     const double2* sl = reinterpret_cast<const double2*>(m + S.fd_lu);
     for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x) {
-        const int4 a = S.t_node[3 * jl], b = S.t_node[3 * jl + 1];
+        const int4 a = S.t_node[2 * jl], b = S.t_node[2 * jl + 1];
         double z = rhs[a.x];
         const int r1 = b.z;
         int r = b.y;
@@ -320,7 +320,7 @@ __device__ __forceinline__ void fd_forward_tail(const DevSym& S, const double* m
         // the clique (every node adjacent to all above it) column by column
         // on the first wavefront, without workgroup barriers; a node per lane
         // in registers, as far as the lanes go, the next column in flight
-        const int c0 = S.t_node[3 * kf].w;
+        const int c0 = S.t_node[2 * kf].w;
         if (KC <= kWave) {
             const int k = threadIdx.x;
             auto column = [&](int q) {
@@ -360,7 +360,7 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         // is final, y_k -= u_kq x_q for every clique node k below q; then the
         // clique's terms of every node below it
         if (threadIdx.x < kWave) {
-            const int c0 = S.t_node[3 * kf].w;
+            const int c0 = S.t_node[2 * kf].w;
             if (KC <= kWave) {
                 const int k = threadIdx.x;
                 auto column = [&](int q) {
@@ -385,7 +385,7 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
         }
         __syncthreads();
         for (int jl = threadIdx.x; jl < kf; jl += blockDim.x) {
-            const int t0 = S.t_node[3 * jl].w, t1 = S.t_node[3 * jl + 1].x;
+            const int t0 = S.t_node[2 * jl].w, t1 = S.t_node[2 * jl + 1].x;
             double y = sy[jl];
             bool more = true;
             for (int q = t1 - 1; more && q >= t0; q -= 4) {  // the clique's are the last ones
@@ -408,7 +408,7 @@ __device__ __forceinline__ void fd_backward_tail(const DevSym& S, const FdTail& 
     }, [](int, int) {});
     __syncthreads();
     for (int jl = threadIdx.x; jl < S.tail_nodes; jl += blockDim.x)
-        x[S.t_node[3 * jl].x] = sy[jl];
+        x[S.t_node[2 * jl].x] = sy[jl];
     __syncthreads();
 }
 

@@ -30,11 +30,10 @@ namespace pf {
 // values fit in LDS, are factorised and solved in LDS.  Every higher
 // neighbour of a tail node is itself in the tail.  Local numbering: tail
 // nodes 0..K-1 in level order, tail slots 0..TS-1 in node order.
-//   t_node[jl] (3 x int4): {j, bus, ydiag, sl0}, {sl1, rn0, rn1, rt1}, {rmid, 0, 0, 0}
+//   t_node[jl] (2 x int4): {j, bus, ydiag, sl0}, {sl1, rn0, rn1, rt1}
 //     [sl0, sl1) local slots, [rn0, rn1) lower neighbours outside the tail
-//     as (i, slot) global pairs in t_rl, [rn1, rt1) lower neighbours inside
-//     the tail as (local i, local slot) pairs in t_rl, those below the
-//     clique first: [rn1, rmid) below, [rmid, rt1) in the clique
+//     as (i, slot) global pairs in t_rl; [rn1, rt1), of a node of the clique,
+//     those in the tail below the clique as (local i, local slot) pairs
 //   t_slot[t] (int4): {s, kl, jl, 0}
 //     s = global slot, kl = local node of k, jl = local node owning the slot
 //   The clique is the last tail_clique local nodes: a chain of single-node
@@ -91,13 +90,7 @@ struct DevSym {
     // filled pattern: S(p) = Li[Lp[p] .. Lp[p+1])
     const int32_t* Lp;       // nn+1
     const int32_t* Li;       // nnz_l
-    const int32_t* ylo;      // nnz_l: Y entry (bus k, bus p) for slot (p;k), -1 if fill
-    const int32_t* yup;      // nnz_l: Y entry (bus p, bus k), -1 if fill
     const int32_t* ydiag;    // nn: Y entry (bus p, bus p)
-    // lower neighbours R(p): descendants i with p in S(i), ascending i
-    const int32_t* Rp;       // nn+1
-    const int32_t* Ri;       // nnz_l: i
-    const int32_t* Rs;       // nnz_l: slot of p in S(i)
     // hierarchical partition
     const int32_t* level_ptr;    // nlev+1
     const int32_t* level_nodes;  // nn
@@ -111,7 +104,7 @@ struct DevSym {
     int32_t tail_level, tail_nodes, tail_slots, tail_lds;
     int32_t tail_clique, tail_longs;
     int32_t ef_lds;  // bytes of the LDS copy of (e, f) per bus the Newton mismatch reads, 0 = none
-    const int4* t_node;      // 3 K
+    const int4* t_node;      // 2 K
     const int4* t_slot;      // TS
     const int2* t_rl;
     const int4* t_lev;       // 2 (nlev - tail_level)
@@ -158,8 +151,11 @@ struct HostSym {
     std::vector<int32_t> from, to;
     std::vector<int32_t> yptr, ycol, ybr_ptr, ybr;
     std::vector<int32_t> perm, pos, parent, level;
-    std::vector<int32_t> Lp, Li, ylo, yup, ydiag;
+    std::vector<int32_t> Lp, Li, ydiag;
+    // Y entries (bus k, bus p) and (bus p, bus k) of slot (p; k), -1 if fill
+    std::vector<int32_t> ylo, yup;
     std::vector<int32_t> owner;  // position that owns each slot
+    // lower neighbours: descendants i with p in S(i), ascending, and p's slot there
     std::vector<int32_t> Rp, Ri, Rs;
     std::vector<int32_t> Up, Ua, Ub;
     std::vector<int32_t> level_ptr, level_nodes, level_g;

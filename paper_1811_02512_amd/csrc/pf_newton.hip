@@ -518,17 +518,16 @@ __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
             const int a = a0 + grp;
             double z0 = 0.0, z1 = 0.0;
             const int jl = kf + (a < KC ? a : 0);
-            const int4 t1 = S.t_node[3 * jl + 1];
-            const int rmid = S.t_node[3 * jl + 2].x;
+            const int4 t1 = S.t_node[2 * jl + 1];
             if (a < KC) {
                 for (int r = t1.y + lane; r < t1.z; r += g) {  // outside the tail
                     const int2 e = S.t_rl[r];
                     const double2 p = x2[e.x];
                     madd(z0, z1, w.blk(lu + 8 * (int64_t)e.y + kUp), p.x, p.y);
                 }
-                for (int r = t1.z + lane; r < rmid; r += g) {  // the tail below the clique
+                for (int r = t1.z + lane; r < t1.w; r += g) {  // the tail below the clique
                     const int2 e = S.t_rl[r];
-                    const int i = S.t_node[3 * e.x].x;
+                    const int i = S.t_node[2 * e.x].x;
                     const int sl = S.t_slot[e.y].x;
                     const double2 p = x2[i];
                     madd(z0, z1, w.blk(lu + 8 * (int64_t)sl + kUp), p.x, p.y);
@@ -536,7 +535,7 @@ __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
             }
             gsum2(z0, z1, g);
             if (a < KC && lane == 0) {
-                const int j = S.t_node[3 * jl].x;
+                const int j = S.t_node[2 * jl].x;
                 const double2 v = x2[j];
                 x2[j] = make_double2(v.x - z0, v.y - z1);
             }
@@ -548,7 +547,7 @@ __device__ void clique_solve(const DevSym& S, const View& w, double2* x2)
         const bool mine = lane < KC;
         int ja = 0, lpa = 0;
         if (mine) {
-            ja = S.t_node[3 * (kf + lane)].x;
+            ja = S.t_node[2 * (kf + lane)].x;
             lpa = S.Lp[ja];
         }
         Blk D = bzero();

@@ -38,8 +38,8 @@ int main()
     const int x0 = s.level_ptr[tl], K = s.tail_nodes;
     std::map<int, int> loc, sloc;  // local node of a position, local slot of a slot
     for (int jl = 0; jl < K; ++jl) {
-        need(s.t_node[12 * jl] == s.level_nodes[x0 + jl], "tail node", jl);
-        loc[s.t_node[12 * jl]] = jl;
+        need(s.t_node[8 * jl] == s.level_nodes[x0 + jl], "tail node", jl);
+        loc[s.t_node[8 * jl]] = jl;
     }
     for (int q = 0; q < s.tail_slots; ++q) sloc[s.t_slot[4 * q]] = q;
     need((int)sloc.size() == s.tail_slots, "tail slots", 0);
