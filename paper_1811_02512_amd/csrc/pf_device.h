@@ -861,13 +861,15 @@ __device__ __forceinline__ TailOp tail_op(const uint2& q)
 
 // The tail's level loops: each lane of a wavefront holds the table entry of
 // one of 64 levels (read back by lane index, where all lanes are active), and
-// a thread's operations of the next four levels are requested together
-// while the current ones run (a level takes less time than a load that misses
-// L1), an absent one's place taken by the level's first.  The form for tails
-// with long destinations looks one level ahead, for its code's size: with four
-// the Newton kernel had 192 instead of 138 KB of it, and the ordinary form ran
-// 1 to 2% slower beside it.
-constexpr int tail_ahead(bool longs) { return longs ? 1 : 4; }
+// a thread's operations of the next two levels are requested together while
+// the current ones run (a level takes less time than a load that misses L1),
+// an absent one's place taken by the level's first.  Two, four and eight
+// levels: 2,000 buses x 384 outages 1,446, 1,478 and 1,505 us, 2,000 x 1,024
+// 1,729, 1,742 and 1,737, one 10,000-bus case 1,224, 1,224 and 1,236; each level
+// is a copy of the loop's code.  The form for tails with long destinations
+// looks one ahead: with four the Newton kernel had 192 instead of 138 KB of
+// code, and the ordinary form ran 1 to 2% slower beside it.
+constexpr int tail_ahead(bool longs) { return longs ? 1 : 2; }
 
 // Walks a tail destination's operations: its first, its second (at `at`) and
 // further ones up to kTailSerial.
