@@ -37,8 +37,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = tuple("paper_1811_02512_amd/csrc/" + f for f in (
-    "pf_abi.hip", "pf_newton.hip", "pf_fdpf.hip", "pf_se.hip", "pf_device.h", "pf_host.h",
-    "pf_kernels.h", "pf_internal.h", "analyze.cpp"))
+    "pf_abi.hip", "pf_newton.hip", "pf_steps.hip", "pf_fdpf.hip", "pf_se.hip", "pf_device.h",
+    "pf_host.h", "pf_kernels.h", "pf_internal.h", "analyze.cpp"))
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_newton_10k_x256_hbm_traffic.md")
 ALL_LEGS = ("c5", "c1", "c2", "c3", "c4", "fdpf", "graph", "screen", "se")
 HOST_THREADS = 16  # also the oracle's thread pool

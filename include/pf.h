@@ -188,10 +188,11 @@ int pf_symbolic_set_launch(pf_symbolic sym, int threads, int64_t tail_lds_budget
  * barriers, while the tail runs on the first (the paper's nodal parallelism
  * across the device for one case, Sec. III); the count is capped by the
  * workgroups the device keeps resident at once.  Results equal the
- * one-workgroup path's to rounding: the arithmetic of every node is the
- * same, but |V| is read from the bus record rather than recomputed from
- * (e, f).  A launch recorded into a graph (stream capture) and every batch
- * (B > 1) use the one-workgroup kernel.  Takes effect at the next call.
+ * one-workgroup path's to rounding: |V| is read from the bus record rather
+ * than recomputed from (e, f), and the narrow levels below the tail take
+ * their updates level by level rather than node by node.  A launch recorded
+ * into a graph (stream capture) and every batch (B > 1) use the one-workgroup
+ * kernel.  Takes effect at the next call.
  * A spread launch has the narrow levels below the tail by lists of their
  * operations, which are large in a grid with much fill: there they are cut
  * short unless a spread was set, by this call or by pf_multi_set_spread,
@@ -212,8 +213,8 @@ int pf_symbolic_upload(pf_symbolic sym, void* d_buf, size_t bytes, void* stream)
 void pf_symbolic_destroy(pf_symbolic sym);
 
 /* ---- FormMatrixA (Sec. III-A: admittances on edges, shunts on vertices) --
- * One thread per (case, bus) gathers its row from its shunt and incident
- * branches: Y_ii = y_sh,i + sum (y_e + j b_e/2), Y_ik = -sum y_e,
+ * A bus's row is gathered from its shunt and incident branches (four threads
+ * per case and bus): Y_ii = y_sh,i + sum (y_e + j b_e/2), Y_ik = -sum y_e,
  * y_e = 1/(r_e + j x_e); parallel branches are summed in branch order.
  * d_r, d_x, d_b: double[B][m] with branch_stride (0 = shared, else >= m).
  * d_ysh: bus shunts y_sh = g + jb as (g, b) pairs, double[B][n][2] with
@@ -252,8 +253,10 @@ int pf_jacobian(const pf_symbolic sym, int B, const double* d_yval, int64_t y_st
 /* ---- FactorizeGraphA (Sec. III-B, eqs. 1-3) --------------------------------
  * In-place block LDU of B matrices in the filled layout, level by level
  * (hierarchical parallel), nodes of a level in parallel (nodal parallel).
- * Each node pulls the updates of its descendants (no atomics, results are
- * bitwise reproducible).  No pivoting (Sec. III-B divides by the pivot as
+ * Below the LDS tail each node pulls the updates of its descendants, in it a
+ * level's updates go to the nodes above, each destination's in a fixed order
+ * (no atomics; results are bitwise reproducible and do not depend on the
+ * workgroup's size).  No pivoting (Sec. III-B divides by the pivot as
  * it stands): d_status[b] (int32, may be NULL) is set to PF_OK, or to
  * PF_E_ZERO_PIVOT when a pivot block's determinant is zero or not finite;
  * d_pivot[b] (int32, may be NULL) to -1, or to the position of the first

@@ -365,7 +365,8 @@ int analyze(int n, int m, const int32_t* from, const int32_t* to, int slack, int
     s.ylo.resize(nnzl);
     s.yup.resize(nnzl);
     {
-        std::vector<int32_t> cur(s.yptr.begin(), s.yptr.end() - 1), transposed(s.ycol.size()), at(n, -1);
+        std::vector<int32_t> cur(s.yptr.begin(), s.yptr.end() - 1), at(n, -1);
+        std::vector<int32_t> transposed(s.ycol.size());
         for (int i = 0; i < n; ++i)
             for (int q = s.yptr[i]; q < s.yptr[i + 1]; ++q) transposed[q] = cur[s.ycol[q]]++;
         for (int p = 0; p < nn; ++p) {

@@ -5,13 +5,13 @@
 // internal linkage (one copy per translation unit).
 //
 // Kernel map (paper sections in brackets):
-//   k_ybus        FormMatrixA, one thread per (case, bus row)      [III-A]
+//   k_ybus        FormMatrixA, four threads per (case, bus row)    [III-A]
 //   k_mismatch    injections, mismatch, max-norm, one WG per case  [II-A]
 //   k_jacobian    Jacobian blocks into the filled layout            [III]
 //   k_factor      FactorizeGraphA, level by level, one WG per case  [III-B]
 //   k_solve       forward / normalisation / backward substitution  [III-C]
 //   k_newton      the whole Newton loop of one case per workgroup   [III]
-//   k_adj_*       adjoint parameter gradients (beyond the paper)
+//   k_adjoint, k_adj_*  adjoint gradients (beyond the paper)
 //   k_fd_*, k_fdpf  fast decoupled matrices, LDL^T, iteration       [III, Table III]
 //   k_branch_flows  post-convergence branch flows                   [II-A]
 //   k_se_*        WLS state estimation: state, measurements, gain   [IV]

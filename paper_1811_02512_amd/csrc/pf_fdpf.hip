@@ -134,12 +134,11 @@ __device__ __forceinline__ void fd_factor_node(const DevSym& S, const NodeRec& r
     }
 }
 
-// Forward substitution and normalisation on component comp of the rhs:
+// Forward substitution and normalisation:
 //   y_j = (1/d_j) (b_j - sum_{i in R(j)} w_ji y_i), levels [0, l1) upward.
 // Four entries per lane per batch with the next batch's indices in flight;
-// the node's own b_j and 1/d_j are requested first.
-// b holds the right-hand side and x the half step's work vector, both by
-// position.
+// the node's own b_j and 1/d_j are requested first.  b holds the right-hand
+// side and x the half step's work vector, both by position.
 __device__ __forceinline__ void fd_forward(const DevSym& S, const double* m, const double* b,
                                            double* x, int l1)
 {
@@ -529,7 +528,8 @@ __device__ void fdpf_case(const DevSym& S, const FdLds& L, const double* yv, con
             }
             __syncthreads();
         }
-        mismatch_pass<2>(S, yv, efl ? efs : efg, out, pvm, Psp, Qsp, mx, nan, fresh_thread(), wg_size());
+        mismatch_pass<2>(S, yv, efl ? efs : efg, out, pvm, Psp, Qsp, mx, nan, fresh_thread(),
+                         wg_size());
         int any_nan = 0;
         nrm = block_max(mx, nan, any_nan);
         if (any_nan || !isfinite(nrm)) {
@@ -577,8 +577,9 @@ __device__ void fdpf_case(const DevSym& S, const FdLds& L, const double* yv, con
 // diagonal entry, then one per slot: the chain of loads from the slot to its
 // branches bounds it (a thread per node, slot after slot: 2,000 buses x 384
 // cases 116 us, now 61).
-__global__ void k_fd_matrices(DevSym S, int B, int per_case, int slots, const double* __restrict__ r,
-                              const double* __restrict__ x, const double* __restrict__ b,
+__global__ void k_fd_matrices(DevSym S, int B, int per_case, int slots,
+                              const double* __restrict__ r, const double* __restrict__ x,
+                              const double* __restrict__ b,
                               int64_t bstride, const double* __restrict__ ysh,
                               int64_t sh_stride, const int8_t* __restrict__ type,
                               int64_t type_stride, double* __restrict__ mat, int64_t mstride)
@@ -663,10 +664,13 @@ __global__ __launch_bounds__(kLevelThreads, 4) void k_fdpf(DevSym S, FdLds L, Ne
 //   S_ft = V_f conj((y + jb/2) V_f - y V_t)
 //        = |V_f|^2 (g - j(b' + b/2)) - |V_f||V_t| e^{j d} (g - jb'),
 // d = theta_f - theta_t, and the same from the other end with -d: one sine for
-// both ends.  The outputs are not read here: stored past the caches.  The
-// gathered voltages bound it, not the sines (one or two: the same 119 us at
-// 10,000 buses x 512 cases; several cases per thread: 141 and more): with a
-// case's workgroups on one XCD 81 us; 63 us for the bytes.
+// both ends.  The outputs are not read here: stored past the caches, which
+// leaves the voltages of a batch called again there.  The gathered voltages
+// bound it, not the sines (one or two: the same 119 us at 10,000 buses x 512
+// cases; several cases per thread: 141 and more): with a case's workgroups on
+// one XCD 81 us; 63 us for the bytes.  Whole calls back to back: the same batch
+// 146 -> 104 us, six batches in turn, none of whose voltages stay in the
+// caches, 181 -> 133.
 __global__ void k_branch_flows(int m, int B, int per_case, const int32_t* __restrict__ from,
                                const int32_t* __restrict__ to, const double* __restrict__ r,
                                const double* __restrict__ x, const double* __restrict__ b,

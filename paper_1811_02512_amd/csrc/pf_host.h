@@ -44,11 +44,12 @@ int launch_threads(const pf::HostSym& h, int B);
 // Grid of a per-item kernel (an item: a bus, a branch, a slot; 256 threads per
 // workgroup) over B cases, and the workgroups per case it hands to the kernel
 // (item_block): one dimension, a case on one XCD, from eight cases on where
-// three quarters of the XCDs' turns are taken.  Below that the last turn's idle XCDs cost more than
-// the shared fetches save: admittances, Jacobian and fast decoupled matrices
-// of 10,000 buses, so / two-dimensional, 6 cases 16, 17, 11 / 15, 16, 10 us, 9
-// cases 22, 25, 17 / 18, 22, 15, 12 cases 23, 26, 17 / 23, 27, 19, 14 cases 23, 26, 18 / 26, 30, 21, 18 cases
-// 28, 34, 26 / 30, 36, 27, 33 cases 38, 51, 38 / 46, 57, 50.
+// three quarters of the XCDs' turns are taken.  Below that the last turn's
+// idle XCDs cost more than the shared fetches save.  Admittances, Jacobian and
+// fast decoupled matrices of 10,000 buses (us), so / two-dimensional: 6 cases
+// 16, 17, 11 / 15, 16, 10; 9 cases 22, 25, 17 / 18, 22, 15; 12 cases 23, 26, 17 /
+// 23, 27, 19; 14 cases 23, 26, 18 / 26, 30, 21; 18 cases 28, 34, 26 / 30, 36,
+// 27; 33 cases 38, 51, 38 / 46, 57, 50.
 inline dim3 item_grid(int64_t items, int B, int* per_case)
 {
     const int64_t nb = (items + 255) / 256, full = ((int64_t)B + 7) / 8 * 8, lin = nb * full;

@@ -242,7 +242,10 @@ void default_mapping(HostSym& s);
 void build_tail(HostSym& s, int64_t budget);
 void build_tail_ops(HostSym& s);
 // The upper levels' lists: in a spread launch, the highest levels below the
-// tail of at most kMidWidth nodes are factorised right-looking.  An operation
+// tail of at most kMidWidth nodes are factorised right-looking.  300, 600 and
+// 1,200: one 10,000-bus case 1,248, 1,231 and 1,194 us, 64 mixed grids 3,359,
+// 3,412 and 3,494: wider levels gain where 32 workgroups have them to
+// themselves and lose where few share a grid.  An operation
 // takes 20 bytes, and in a grid with much fill there are tens to hundreds per
 // slot (a 100 x 100 mesh: 5.7 million, 113 MB and 0.4 s of analysis beside 69
 // MB and 0.2 s without).  Whole lists are therefore for grids that a launch

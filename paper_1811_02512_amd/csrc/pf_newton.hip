@@ -289,8 +289,9 @@ __device__ __forceinline__ void ybus_row(const DevSym& S, int i, int sub, int ns
 }
 
 // A case's rows on one XCD (item_block): 2,000 buses x 384 cases 98 -> 59 us.
-__global__ void k_ybus(DevSym S, int B, int per_case, const double* __restrict__ r, const double* __restrict__ x,
-                       const double* __restrict__ bc, int64_t bstride,
+__global__ void k_ybus(DevSym S, int B, int per_case, const double* __restrict__ r,
+                       const double* __restrict__ x, const double* __restrict__ bc,
+                       int64_t bstride,
                        const double* __restrict__ ysh, int64_t sh_stride,
                        double* __restrict__ yval, int64_t ystride)
 {

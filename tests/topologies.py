@@ -25,6 +25,7 @@ def grid_of(n, edges, seed=1):
     kind[1:n // 4] = gridgen.BUS_PV
     return gridgen.Grid(
         n=n, f=f, t=t, r=rng.uniform(0.001, 0.003, m), x=rng.uniform(0.01, 0.03, m),
-        b=rng.uniform(0.0, 0.005, m), bus_type=kind, vset=np.where(kind == gridgen.BUS_PQ, 1.0, 1.02),
+        b=rng.uniform(0.0, 0.005, m), bus_type=kind,
+        vset=np.where(kind == gridgen.BUS_PQ, 1.0, 1.02),
         Pd=rng.uniform(0.0, 0.05, n), Qd=rng.uniform(0.0, 0.02, n),
         Pg=np.where(kind == gridgen.BUS_PV, 0.1, 0.0), pts=np.zeros((n, 2)))
