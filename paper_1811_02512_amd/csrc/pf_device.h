@@ -1681,9 +1681,9 @@ __device__ __forceinline__ void upper_factor(const DevSym& S, const SRC& src, co
     // only a tail with long destinations takes the form that looks for them (a
     // path of 150 buses, no long ones: 356 us, in that form 366; 198 leaves on
     // one bus: 314 us walked one after the other, so 222)
-    // A spread launch's factors to keep, once a solve, take it always: the code
-    // of a second form there slowed the 64 mixed grids by 1%.
-    constexpr bool always = P::kSpread && WRITE;
+    // A spread launch takes it always: the code of a second form there slowed
+    // one 10,000-bus case by 1% (1,222 -> 1,234 us) and the 64 mixed grids as much.
+    constexpr bool always = P::kSpread;
     if (always || S.tail_longs) for_tail_updates<true>(S, nT, quad, lane, rest);
     else if constexpr (!always) for_tail_updates<false>(S, nT, quad, lane, rest);
     for (int it = threadIdx.x; it < K + TS; it += blockDim.x) {
