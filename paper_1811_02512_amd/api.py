@@ -69,8 +69,10 @@ class Symbolic:
 
     def renew(self, before):
         """Uploads again, to a new buffer, if the lists that a spread launch
-        reads have grown from `before` bytes (a grid with much fill)."""
-        if self.buf is not None and self.info.dev_bytes != before:
+        reads have grown from `before` bytes (a grid with much fill); not under
+        stream capture, where the shorter lists serve."""
+        if (self.buf is not None and self.info.dev_bytes != before and
+                not torch.cuda.is_current_stream_capturing()):
             self.kept.append(self.buf)
             self.buf = None
             self.upload(self.device)

@@ -46,7 +46,8 @@ struct LdsLimit {
     int64_t bytes;
 };
 std::mutex g_limits_mu;
-std::vector<LdsLimit> g_limits;  // one entry per device and kernel asked for
+LdsLimit g_limits[1024];  // one entry per device and kernel asked for
+int g_limit_count = 0;
 
 int64_t raise_lds(int dev, const void* kernel)
 {
@@ -77,10 +78,11 @@ int64_t lds_limit(const void* kernel)
         return 0;
     }
     std::lock_guard<std::mutex> lock(g_limits_mu);
-    for (const LdsLimit& l : g_limits)
-        if (l.dev == dev && l.kernel == kernel) return l.bytes;
-    g_limits.push_back({dev, kernel, raise_lds(dev, kernel)});
-    return g_limits.back().bytes;
+    for (int k = 0; k < g_limit_count; ++k)
+        if (g_limits[k].dev == dev && g_limits[k].kernel == kernel) return g_limits[k].bytes;
+    const LdsLimit l{dev, kernel, raise_lds(dev, kernel)};
+    if (g_limit_count < (int)(sizeof g_limits / sizeof g_limits[0])) g_limits[g_limit_count++] = l;
+    return l.bytes;
 }
 
 int compute_units()

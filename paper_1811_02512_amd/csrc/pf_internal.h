@@ -247,7 +247,7 @@ void build_tail_ops(HostSym& s);
 // 3,412 and 3,494: wider levels gain where 32 workgroups have them to
 // themselves and lose where few share a grid.  An operation
 // takes 20 bytes, and in a grid with much fill there are tens to hundreds per
-// slot (a 100 x 100 mesh: 5.7 million, 113 MB and 0.4 s of analysis beside 69
+// slot (a 100 x 100 mesh: 5.7 million, 113 MB and 0.4 s of analysis beside 65
 // MB and 0.2 s without).  Whole lists are therefore for grids that a launch
 // spreads, where they pay (there 131 -> 11 ms a solve); without, the lists end
 // at kUpperTerms entries per slot of the factor, which the generated grids of
